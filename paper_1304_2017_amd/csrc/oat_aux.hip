@@ -315,7 +315,7 @@ hipError_t launch_adj_gather(const Problem &P, const double *acc, void *img, int
                              hipStream_t s)
 {
     dim3 grid((P.nx + 63) / 64, (P.ny + 3) / 4, P.nz), block(256);
-    const int sl = adj_slices(P.nbx * P.nby * P.nbz, P.nq);
+    const int sl = adj_grid(P.nbx * P.nby * P.nbz, P.nq).slices;
     if (img_dtype == 0)
         hipLaunchKernelGGL(adj_gather_kernel<0>, grid, block, 0, s, P, acc, sl, img);
     else

@@ -72,13 +72,72 @@ inline int fill_slices(int nbricks, int items, int min_items, int max_slices, in
 // G on the arc-table and bounds paths (one workgroup per CU): transducers
 // per slice >= 64.
 inline int fwd_slices(int nbricks, int nq) { return brick_slices(nbricks, nq, 64); }
-// G on the segment table runs two workgroups per CU (rounds of 512): up to 8
-// slices of at least 64 transducers.
+// Whole-transducer slices of G on the segment table, which runs two
+// workgroups per CU (rounds of 512): up to 8 of at least 64 transducers.
 inline int seg_fwd_slices(int nbricks, int nq) { return fill_slices(nbricks, nq, 64, 8, 512); }
-// G^T (one workgroup per CU): up to 8 slices of at least 2 windows; each
-// slice keeps its own FP64 brick sums ([slice][brick][BOX3]; the same slicing
-// for every table mode).
+// Whole-window slices of G^T (one workgroup per CU): up to 8 of at least 2
+// windows.
 inline int adj_slices(int nbricks, int nq) { return fill_slices(nbricks, adj_windows(nq), 2, 8, 256); }
+
+// Work split of G on the segment table: `slices` workgroups per brick, each
+// with `per` transducers.  parts = 0: the slices above, one unit per wave at
+// a time.  parts > 0: every unit is taken in `parts` parts (its segment
+// windows dealt round-robin), so that a workgroup has about 64 items for its
+// 16 waves, and the parts of a unit share its shell sums in LDS (integers:
+// bit for bit the sums of one wave).
+//
+// Grids of at least 4096 workgroups keep whole units: a workgroup's staging
+// of its box (a few us) and its last, part-idle units are then small, and at
+// 256^3 / 2048 splitting costs 0.8% (68.5 against 68.0 ms).  Smaller grids
+// leave CUs idle or end in a ragged last round: they take about 1024
+// workgroups and at most 32 transducers each (16: 6% slower at 128^3 / 1024
+// BF16, 64: the same; more workgroups: 60 x 61 x 45 / 300 24% slower from
+// the staging).  32^3 / 64: 925 -> 44 us; 128 x 105 x 117 / 1024 BF16:
+// 3.82 -> 3.50 ms.
+constexpr int FWD_SPLIT_Q = 32;
+constexpr int FWD_SPLIT_WORDS = 3328;   // shell sums of a slice: 26 KB, so two boxes share a CU
+struct FwdGrid {
+    int slices, per, parts;
+};
+inline FwdGrid seg_fwd_grid(int nbricks, int nq, int window)
+{
+    const int sl = seg_fwd_slices(nbricks, nq);
+    if ((long long)nbricks * sl >= 4096) return FwdGrid{sl, (nq + sl - 1) / sl, 0};
+    const int fit = FWD_SPLIT_WORDS / window < FWD_SPLIT_Q ? FWD_SPLIT_WORDS / window : FWD_SPLIT_Q;
+    const long long want = (long long)nbricks * nq / 1024;
+    const int per = want < 1 ? 1 : (want > fit ? fit : (int)want);
+    const int parts = 64 / per;
+    return FwdGrid{(nq + per - 1) / per, per, parts > 16 ? 16 : parts};
+}
+
+// Work split of G^T: `slices` workgroups per brick, each with `per`
+// transducers (whole windows, or a power-of-two fraction of one) and its own
+// FP64 brick sums ([slice][brick][BOX3]; the same slices for every table
+// mode, so their results agree bit for bit).  On the segment table a unit is
+// taken in `parts` parts, about 64 items a workgroup, all adding into the
+// one box.
+//
+// Grids of at least 2048 workgroups keep whole windows (8 rounds and a short
+// tail).  Smaller ones halve the window down to 32 transducers until they
+// have 2048 (1024: 3% slower at 117 x 128 x 99 / 1000 BF16, 4096: 4%; 16
+// transducers: 6% slower on a 96^3 / 512 reconstruction), and on to single
+// transducers until every CU has a workgroup.  32^3 / 64: 910 -> 96 us;
+// 117 x 128 x 99 / 1000 BF16: 5.30 -> 4.60 ms; 90 x 120 x 200 / 360 ring
+// views: 6.35 -> 3.57 ms.
+struct AdjGrid {
+    int slices, per, parts;
+};
+inline AdjGrid adj_grid(int nbricks, int nq)
+{
+    const int sl = adj_slices(nbricks, nq), nwin = adj_windows(nq), wps = (nwin + sl - 1) / sl;
+    if ((long long)nbricks * sl >= 2048) return AdjGrid{sl, wps * ADJ_WINDOW, 1};
+    int per = ADJ_WINDOW;
+    auto grid = [&]() { return (long long)nbricks * ((nq + per - 1) / per); };
+    while (per > 32 && grid() < 2048) per /= 2;
+    while (per > 1 && grid() < 256) per /= 2;
+    const int parts = per >= 64 ? 1 : (64 / per > 16 ? 16 : 64 / per);
+    return AdjGrid{(nq + per - 1) / per, per, parts};
+}
 
 // Per-transducer record (grid units: positions are (r - r_0)/dx).
 struct alignas(16) DetRec {

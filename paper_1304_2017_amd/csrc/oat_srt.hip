@@ -13,6 +13,7 @@
 // Every point's position is a deterministic function of (q, k, i, j) and
 // the same code evaluates it in both kernels, so each point belongs to
 // exactly one brick of G and the adjoint uses the identical point set.
+#include <algorithm>
 #include <type_traits>
 
 #include "oat_internal.hpp"
@@ -702,8 +703,8 @@ __device__ __forceinline__ int wave_max_i(int v)
 template <bool ADJ, class PFn, class SFn>
 __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, const int lo[3],
                                          const int hi[3], int *gbase, const float *gp,
-                                         float gscale, float gscale2, int &klo_out, PFn &&pfn,
-                                         SFn &&sfn)
+                                         float gscale, float gscale2, int part, int parts,
+                                         int &klo_out, PFn &&pfn, SFn &&sfn)
 {
     const DetRec &d = P.det[q];
     const double uq[3] = {d.uq[0], d.uq[1], d.uq[2]};
@@ -716,7 +717,8 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
     unit_shells(P, uq, lo, hi, klo, khi);
     klo_out = klo;
     const int lane = lane_id();
-    const long long s0 = P.seg_off[unit], s1 = P.seg_off[unit + 1];
+    const long long s0 = P.seg_off[unit] + part * WAVE, s1 = P.seg_off[unit + 1];
+    const int step = parts * WAVE;
     if (s0 >= s1) return;
     // Each shell's first candidate ring, as the bounds walk found it when
     // the table was built (the same FP32 operations).
@@ -735,10 +737,10 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
     }
     // The next window's entries are loaded while this window runs.
     unsigned nxt = s0 + lane < s1 ? P.seg[s0 + lane] : 0u;
-    for (long long c = s0; c < s1; c += WAVE) {
+    for (long long c = s0; c < s1; c += step) {
         const bool v = c + lane < s1;
         const unsigned ent = nxt;
-        const long long en = c + WAVE + lane;
+        const long long en = c + step + lane;
         nxt = en < s1 ? P.seg[en] : 0u;
         const int so = (int)(ent & ((1u << SEG_SHELL_BITS) - 1u));
         const int rrel = (int)((ent >> SEG_SHELL_BITS) & ((1u << SEG_RING_BITS) - 1u));
@@ -872,13 +874,14 @@ srt_fwd_kernel(Problem P, const void *__restrict__ img, float *__restrict__ part
 // waves per workgroup and two workgroups per CU (at most 64 VGPRs, the LDS
 // of two boxes).  Per wave, dynamic LDS holds the unit's first candidate
 // ring per shell (window ints) and its fixed-point shell sums (window
-// 64-bit integers).
+// 64-bit integers).  SPLIT: the waves share units (seg_fwd_grid, parts > 0),
+// and the shell sums are per transducer of the slice.
 constexpr int FWD_SEG_WAVES = 16;
 
-template <int IMG_DT>
+template <int IMG_DT, bool SPLIT>
 __global__ void __launch_bounds__(FWD_SEG_WAVES *WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)))
 srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ part,
-                   int *__restrict__ klo_out, int q_per_slice)
+                   int *__restrict__ klo_out, int q_per_slice, int parts)
 {
     constexpr int NW = FWD_SEG_WAVES;
     __shared__ float box[BOX_WORDS];
@@ -886,13 +889,14 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
     __shared__ float wmax[NW];
     __shared__ int wbad[NW];
     __shared__ double fx_scale, fx_unscale;
+    __shared__ int klo_s[SPLIT ? FWD_SPLIT_Q : 1];
     extern __shared__ double dyn_lds[];
     const int win = P.window;
     const int b = blockIdx.x;
     int lo[3], hi[3], n0[3], n1[3];
     brick_box(P, b, lo, hi, n0, n1);
     const int qb = (int)blockIdx.y * q_per_slice, qe = min(P.nq, qb + q_per_slice);
-    if (threadIdx.x == 0) q_next = qb;
+    if (threadIdx.x == 0) q_next = SPLIT ? 0 : qb;
     // the box's largest |node| (and whether any node is not finite) sets
     // the fixed-point scale of the shell sums below
     float amax = 0.f;
@@ -957,8 +961,14 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
         fx_scale = bad ? __longlong_as_double(0x7ff8000000000000ll) : ldexp(1.0, 43 - e);
         fx_unscale = bad ? fx_scale : ldexp(1.0, e - 43);
     }
-    unsigned long long *gw = reinterpret_cast<unsigned long long *>(dyn_lds) + (size_t)wave * win;
-    int *gbase = reinterpret_cast<int *>(dyn_lds + (size_t)NW * win) + wave * win;
+    // SPLIT: one row of shell sums per transducer of the slice, shared by the
+    // waves that take its parts; otherwise one per wave.
+    const int NR = SPLIT ? q_per_slice : NW;
+    unsigned long long *gws = reinterpret_cast<unsigned long long *>(dyn_lds);
+    int *gbase = reinterpret_cast<int *>(dyn_lds + (size_t)NR * win) + wave * win;
+    if (SPLIT)
+        for (int j = threadIdx.x; j < (qe - qb) * win; j += blockDim.x) gws[j] = 0ull;
+    unsigned long long *gw = gws + (size_t)wave * win;
     __syncthreads();
     // (uniform: kept in scalar registers)
     auto uniform = [](double x) {
@@ -968,12 +978,24 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
             (unsigned)__builtin_amdgcn_readfirstlane((int)b));
     };
     const double fxs = uniform(fx_scale), fxi = uniform(fx_unscale);
+    auto unscaled = [&](unsigned long long u) {
+        const long long sj = (long long)u;
+        return (float)(fma((double)(int)(sj >> 32), 0x1p32, (double)(unsigned)sj) * fxi);
+    };
+    const int n_items = SPLIT ? (qe - qb) * parts : qe;
     for (;;) {
-        int q = 0;
+        int q = 0, pt = 0;
         if (lane == 0) q = atomicAdd(&q_next, 1);
         q = __builtin_amdgcn_readfirstlane(q);
-        if (q >= qe) break;
-        for (int j = lane; j < win; j += WAVE) gw[j] = 0ull;
+        if (q >= n_items) break;
+        if (SPLIT) {
+            const int i = q / parts;
+            pt = q - i * parts;
+            q = qb + i;
+            gw = gws + (size_t)i * win;
+        } else {
+            for (int j = lane; j < win; j += WAVE) gw[j] = 0ull;
+        }
         wave_sync();
         int klo = 0;
         float racc = 0.f;
@@ -1024,16 +1046,27 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
             racc = 0.f;
             prev = 0xffffffffu;
         };
-        walk_seg<false>(P, q, (size_t)b * P.nq + q, lo, hi, gbase, nullptr, 1.f, 1.f, klo, point,
-                        segment);
+        walk_seg<false>(P, q, (size_t)b * P.nq + q, lo, hi, gbase, nullptr, 1.f, 1.f, SPLIT ? pt : 0,
+                        SPLIT ? parts : 1, klo, point, segment);
         wave_sync();
-        float *dst = part + ((size_t)b * P.nq + q) * win;
-        for (int j = lane; j < win; j += WAVE) {
-            const long long sj = (long long)gw[j];
-            dst[j] = (float)(fma((double)(int)(sj >> 32), 0x1p32, (double)(unsigned)sj) * fxi);
+        if (SPLIT) {
+            if (lane == 0) klo_s[q - qb] = klo;   // the same value from each part
+            // the wave reconverges here: a loop that lane 0 leaves alone to
+            // store, with the other lanes back at its head, never ends
+            wave_sync();
+            continue;
         }
+        float *dst = part + ((size_t)b * P.nq + q) * win;
+        for (int j = lane; j < win; j += WAVE) dst[j] = unscaled(gw[j]);
         if (lane == 0) klo_out[(size_t)b * P.nq + q] = klo;
         wave_sync();
+    }
+    if (SPLIT) {
+        __syncthreads();
+        float *dst = part + ((size_t)b * P.nq + qb) * win;   // the slice's rows are consecutive
+        for (int j = threadIdx.x; j < (qe - qb) * win; j += blockDim.x) dst[j] = unscaled(gws[j]);
+        for (int i = threadIdx.x; i < qe - qb; i += blockDim.x)
+            klo_out[(size_t)b * P.nq + qb + i] = klo_s[i];
     }
 }
 
@@ -1116,7 +1149,7 @@ __device__ __forceinline__ void field_scale(double bound, float &g1, float &g2, 
 template <int TM, bool CALIB, int NW>
 __global__ void __launch_bounds__(NW *WAVE) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4)))
 srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc,
-               float *__restrict__ rcal, int win_per_slice)
+               float *__restrict__ rcal, int q_per_slice, int parts)
 {
     // The segment-table walk needs only the point level's LDS, which leaves
     // room for 16 waves beside the box.
@@ -1133,12 +1166,16 @@ srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc
     brick_box(P, b, lo, hi, n0, n1);
     const int nwin = adj_windows(P.nq);
     const int wave = threadIdx.x / WAVE, lane = lane_id();
+    // Transducers of this workgroup's slice (blockIdx.y), which is a run of
+    // whole windows or a part of one; each slice has its own FP64 brick sums.
+    const int qb = (int)blockIdx.y * q_per_slice, qe = min(P.nq, qb + q_per_slice);
+    const int w0 = qb / ADJ_WINDOW, w1 = (qe - 1) / ADJ_WINDOW + 1;
     // Order in which the waves take a window's transducers (wave 0 writes
     // it): with the segment table by decreasing segment count, so the
     // longest units start first and the waves reach the window's barrier
     // close together; otherwise in index order.
     auto order_window = [&](int wn) {
-        const int qa = wn * ADJ_WINDOW, cnt = min(ADJ_WINDOW, P.nq - qa);
+        const int qa = max(qb, wn * ADJ_WINDOW), cnt = min(qe, (wn + 1) * ADJ_WINDOW) - qa;
         if constexpr (TM == TM_SEG && !CALIB) {
             for (int i = lane; i < cnt; i += WAVE) {
                 const size_t u = (size_t)b * P.nq + qa + i;
@@ -1158,24 +1195,20 @@ srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc
             for (int i = lane; i < cnt; i += WAVE) qperm[i] = qa + i;
         }
     };
-    // Windows of this workgroup's slice (blockIdx.y); each slice has its own
-    // FP64 brick sums.
-    const int w0 = (int)blockIdx.y * win_per_slice, w1 = min(nwin, w0 + win_per_slice);
     for (int t = threadIdx.x; t < BOX_WORDS; t += blockDim.x) box[t] = 0ull;
     if (threadIdx.x == 0) q_next = 0;
     if (wave == 0) order_window(w0);
     __syncthreads();
     WL &W = wl[wave];
     for (int win = w0; win < w1; ++win) {
-        const int q0 = win * ADJ_WINDOW;
+        const int q0 = max(qb, win * ADJ_WINDOW), q1 = min(qe, (win + 1) * ADJ_WINDOW);
         float g1, g2;
         double unscale;
         if (CALIB) {
             window_scale((double)P.w_max, 30, g1, g2, unscale);
         } else {
             float m = 0.f;
-            for (int j = lane; j < ADJ_WINDOW && q0 + j < P.nq; j += WAVE)
-                m = fmaxf(m, P.gp_rowmax[q0 + j]);
+            for (int q = q0 + lane; q < q1; q += WAVE) m = fmaxf(m, P.gp_rowmax[q]);
             for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
             field_scale((double)P.adj_r[(size_t)b * nwin + win] * (double)m, g1, g2, unscale);
         }
@@ -1183,12 +1216,16 @@ srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc
         // it finishes one (an LDS counter): the waves reach the flush
         // together whatever the units cost.  The LDS sums are exact
         // integers, so the order of the units does not change them.
-        const int cntw = min(ADJ_WINDOW, P.nq - q0);
+        const int cntw = (q1 - q0) * (TM == TM_SEG ? parts : 1);
         for (;;) {
-            int i = 0;
+            int i = 0, pt = 0;
             if (lane == 0) i = atomicAdd(&q_next, 1);
             i = __builtin_amdgcn_readfirstlane(i);
             if (i >= cntw) break;
+            if (TM == TM_SEG && parts > 1) {
+                pt = i % parts;
+                i /= parts;
+            }
             const int q = qperm[i];
             int klo = 0;
             if (CALIB) {
@@ -1215,7 +1252,7 @@ srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc
                     auto point = [&](const Pt &t, float wv) { scatter1(t, (wv * g1) * g2); };
                     auto segment = [](int, int, float) {};
                     walk_seg<false>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, nullptr, 1.f,
-                                    1.f, klo, point, segment);
+                                    1.f, pt, parts, klo, point, segment);
                 } else {
                     auto scatter = [&](const Pt &a, const Pt &c, float wv, int, int) {
                         if (a.own) scatter1(a, (wv * g1) * g2);
@@ -1253,8 +1290,8 @@ srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc
                 if constexpr (TM == TM_SEG) {
                     auto point = [&](const Pt &t, float wv) { scatter1(t, wv); };
                     auto segment = [](int, int, float) {};
-                    walk_seg<true>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, gp, g1, g2, klo,
-                                   point, segment);
+                    walk_seg<true>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, gp, g1, g2, pt,
+                                   parts, klo, point, segment);
                 } else {
                     auto scatter = [&](const Pt &a, const Pt &c, float wv, int, int) {
                         if (a.own) scatter1(a, wv);
@@ -1337,17 +1374,22 @@ static void fwd_launch(const Problem &P, const void *img, int img_dtype, float *
                        hipStream_t s)
 {
     const int nb = P.nbx * P.nby * P.nbz;
-    const int sl = TM == TM_SEG ? seg_fwd_slices(nb, P.nq) : fwd_slices(nb, P.nq);
-    const int qps = (P.nq + sl - 1) / sl;
     if constexpr (TM == TM_SEG) {
-        dim3 grid(P.nbx * P.nby * P.nbz, sl), block(FWD_SEG_WAVES * WAVE);
-        const size_t dyn = (size_t)FWD_SEG_WAVES * P.window * (sizeof(double) + sizeof(int));
-        if (img_dtype == 0)
-            hipLaunchKernelGGL(srt_fwd_seg_kernel<0>, grid, block, dyn, s, P, img, part, klo, qps);
+        const FwdGrid fg = seg_fwd_grid(nb, P.nq, P.window);
+        dim3 grid(nb, fg.slices), block(FWD_SEG_WAVES * WAVE);
+        const size_t rows = fg.parts > 0 ? fg.per : FWD_SEG_WAVES;
+        const size_t dyn = (rows * sizeof(double) + FWD_SEG_WAVES * sizeof(int)) * P.window;
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, dyn, s, P, img, part, klo, fg.per, fg.parts);
+        };
+        if (fg.parts > 0)
+            img_dtype == 0 ? launch(srt_fwd_seg_kernel<0, true>) : launch(srt_fwd_seg_kernel<1, true>);
         else
-            hipLaunchKernelGGL(srt_fwd_seg_kernel<1>, grid, block, dyn, s, P, img, part, klo, qps);
+            img_dtype == 0 ? launch(srt_fwd_seg_kernel<0, false>)
+                           : launch(srt_fwd_seg_kernel<1, false>);
     } else {
-        dim3 grid(P.nbx * P.nby * P.nbz, sl), block(FWD_WAVES * WAVE);
+        const int sl = fwd_slices(nb, P.nq), qps = (P.nq + sl - 1) / sl;
+        dim3 grid(nb, sl), block(FWD_WAVES * WAVE);
         if (img_dtype == 0)
             hipLaunchKernelGGL((srt_fwd_kernel<0, TM>), grid, block, 0, s, P, img, part, klo, qps);
         else
@@ -1378,25 +1420,29 @@ hipError_t launch_srt_fwd(const Problem &P, const void *img, int img_dtype, floa
 template <bool CALIB>
 static void adj_launch(const Problem &P, const float *gp, double *acc, float *r, hipStream_t s)
 {
-    const int nb = P.nbx * P.nby * P.nbz, nwin = adj_windows(P.nq);
-    const int sl = adj_slices(nb, P.nq), wps = (nwin + sl - 1) / sl;
-    dim3 grid(nb, sl), b12(12 * WAVE), b16(16 * WAVE);
+    const int nb = P.nbx * P.nby * P.nbz;
+    AdjGrid ag = adj_grid(nb, P.nq);
+    if (CALIB) {   // R is a maximum over whole windows
+        const int per = std::max(ag.per, ADJ_WINDOW);
+        ag = AdjGrid{(P.nq + per - 1) / per, per, 1};
+    }
+    dim3 grid(nb, ag.slices), b12(12 * WAVE), b16(16 * WAVE);
     switch (table_mode(P)) {
     case TM_SEG:
         if (CALIB)
             hipLaunchKernelGGL((srt_adj_kernel<TM_SEG, true, 12>), grid, b12, 0, s, P, gp, acc, r,
-                               wps);
+                               ag.per, ag.parts);
         else
             hipLaunchKernelGGL((srt_adj_kernel<TM_SEG, false, 16>), grid, b16, 0, s, P, gp, acc, r,
-                               wps);
+                               ag.per, ag.parts);
         break;
     case TM_ARC:
         hipLaunchKernelGGL((srt_adj_kernel<TM_ARC, CALIB, 12>), grid, b12, 0, s, P, gp, acc, r,
-                           wps);
+                           ag.per, ag.parts);
         break;
     default:
         hipLaunchKernelGGL((srt_adj_kernel<TM_BOUNDS, CALIB, 12>), grid, b12, 0, s, P, gp, acc, r,
-                           wps);
+                           ag.per, ag.parts);
         break;
     }
 }

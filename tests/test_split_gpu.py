@@ -1,0 +1,52 @@
+"""Small grids, where G and G^T split their units over workgroups and waves: slices of one
+transducer, slices that do not divide the transducers or the windows of 128, units with fewer
+segments than parts, one-cell bricks.  Against the FP64 oracle at the gates of the other parity
+tests (1e-5 in FP32, 5e-7 for G alone; 2e-3 and half a BF16 unit for BF16 storage), and bit for
+bit over the table paths for G^T."""
+import math
+
+import numpy as np
+import pytest
+
+from checks import BF16_ELEM, check
+from oracle import ref
+from paper_1304_2017_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _geometry(nx, ny, nz, q, dx=0.5, rs=25.0):
+    xyz = synth.fibonacci_sphere(q, rs)
+    return synth.Geometry(nx, ny, nz, dx, synth.centred_origin(nx, dx), synth.centred_origin(ny, dx),
+                          synth.centred_origin(nz, dx), xyz, 256, 0.1, 0.0, 1.5, 1.0,
+                          np.full(q, 4 * math.pi * rs * rs / q))
+
+
+@pytest.mark.parametrize("shape,q", [((20, 20, 20), 1), ((1, 2, 3), 3), ((21, 20, 41), 37),
+                                     ((32, 19, 40), 129), ((40, 21, 20), 300)])
+def test_small_grids_split_units(shape, q):
+    import torch
+    from paper_1304_2017_amd.oat import Plan
+    geom = _geometry(*shape, q)
+    gd = geom.as_dict()
+    rng = np.random.default_rng(q)
+    img = rng.normal(size=geom.shape).astype(np.float32)
+    y = rng.normal(size=(q, geom.n_t)).astype(np.float32)
+    plan = Plan(geom, 0)
+    assert plan.stats()["segment_table_entries"] > 0
+    x, yd = torch.from_numpy(img).cuda(), torch.from_numpy(y).cuda()
+    g, p, a = plan.project(x, srt_only=True), plan.project(x), plan.backproject(yd)
+    check(f"G {shape}/{q}", g.cpu().numpy(), ref.srt(gd, img.astype(np.float64)), 5e-7)
+    check(f"H {shape}/{q}", p.cpu().numpy(), ref.project(gd, img.astype(np.float64)), 1e-5)
+    check(f"H^T {shape}/{q}", a.cpu().numpy(), ref.backproject(gd, y.astype(np.float64)), 1e-5)
+    xb = x.bfloat16()
+    pb = plan.project(xb)
+    check(f"H bf16 {shape}/{q}", pb.float().cpu().numpy(),
+          ref.project(gd, xb.double().cpu().numpy()), 2e-3, BF16_ELEM)
+    for _ in range(2):      # order-independent sums: the same bits again
+        assert torch.equal(plan.project(x), p) and torch.equal(plan.backproject(yd), a)
+    for tables in (dict(segment_table=0), dict(segment_table=0, arc_table=0)):
+        other = Plan(geom, 0, **tables)
+        assert torch.equal(other.backproject(yd), a)
+        other.close()
+    plan.close()
