@@ -222,15 +222,17 @@ int oat_deconvolve(oat_plan *plan, const void *u, oat_dtype u_dtype, void *p, oa
  * f_l = f_min + l df for l = 0 .. n_f - 1 (the listings' frequency grid).
  * alpha_n is the voxel's absorbed-energy density; r_n are the plan's nodes.
  * img: device [nz][ny][nx] (oat_dtype); u: device [n_det][n_f] complex FP32,
- * interleaved (re, im).  Every term is evaluated (a dense sum); phases and
- * sums are FP64; each run of frequencies starts from an FP32 exponential
- * (about 1 ulp) and steps it in FP64 (H_sph) or in FP32 (H_sph^T).
+ * interleaved (re, im).  A transducer's sum over frequencies is a function
+ * of the distance alone: larger problems form it once per transducer, as
+ * polynomials on intervals of the distance, and H_sph bins the voxels'
+ * weights into the same intervals' moments; smaller ones evaluate every
+ * (transducer, frequency, voxel) term.  Phases and sums are FP64 on both
+ * paths; errors against FP64 are about 3e-8 (H_sph) and 5e-8 (H_sph^T) of
+ * the output's 2-norm with the polynomials, 1e-7 and 1e-6 with the plain sums.
  * 1 <= n_f <= 4096, f_min >= 0, df > 0,
  * flags: 0 or OAT_FLAG_DETERMINISTIC.  The two calls share a workspace in
- * the plan and may allocate or grow it: oat_sph_project for a larger n_f,
- * oat_sph_backproject for an image of fewer than 512K voxels, whose
- * transducers it splits into slices of FP64 partial images (added in slice
- * order).  Results are deterministic. */
+ * the plan and may allocate or grow it.  Results are deterministic (sums in a
+ * fixed order, or of integers). */
 int oat_sph_project(oat_plan *plan, const void *img, oat_dtype img_dtype, void *u, int n_f,
                     double f_min, double df, uint32_t flags, void *stream);
 
@@ -265,15 +267,14 @@ int oat_plan_set_aperture(oat_plan *plan, double width, double height, int m);
  * hipMalloc.  Same arguments, operation and results (bit for bit) as
  * oat_sph_backproject, which may grow the plan's workspace; this variant
  * calls no hipMalloc, hipFree or allocating library routine and never waits
- * for the device.  Images of fewer than 512K voxels split the transducers
- * into slices whose FP64 partial images go to a fixed 8 MiB scratch array in
- * device memory, one per GPU (resolved at the first oat_plan_create on that
- * GPU and held until the process ends); every image this library accepts
- * needs at most 2 x 523776 x 8 bytes of it, and a larger need is rejected
- * with OAT_ERR_ARG.  Every slice value is written before it is read, so the
- * scratch needs no clearing.  All calls on one GPU share that scratch: calls
- * that overlap in time on one GPU (other streams, other plans, other
- * threads) race and give wrong results. */
+ * for the device.  Its tables and partial sums go to a fixed 64 MiB scratch
+ * array in device memory, one per GPU (resolved at the first oat_plan_create
+ * on that GPU and held until the process ends); the transducers' tables are
+ * taken in batches that fit it, and a need that does not is rejected with
+ * OAT_ERR_ARG (no image this library accepts has one).  Every value is
+ * written before it is read, so the scratch needs no clearing.  All calls on
+ * one GPU share that scratch: calls that overlap in time on one GPU (other
+ * streams, other plans, other threads) race and give wrong results. */
 int oat_sph_backproject_noalloc(oat_plan *plan, const void *u, int n_f, double f_min, double df,
                                 void *img, oat_dtype img_dtype, uint32_t flags, void *stream);
 

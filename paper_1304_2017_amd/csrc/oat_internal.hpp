@@ -244,6 +244,7 @@ struct Problem {
     // of a transducer sum to 1); point-like transducers: one node r_q, 1.
     const double4 *sph_pts;
     int sph_ns;
+    double sph_rf;         // half diagonal of the faces (mm; 0 point-like)
     // Segment table (null when the plan has none): the segments of unit u
     // that hold points owned by the brick are entries seg_off[u] ..
     // seg_off[u+1]-1, one 32-bit word each (seg_pack): the shell offset
@@ -297,22 +298,19 @@ hipError_t launch_eir_spectrum(const double *h, int taps, int N, double2 *Ht, do
 hipError_t launch_deconvolve(const Problem &P, const void *u, int u_dt, void *p, int p_dt,
                              const double2 *Ht, const double2 *tw, double2 *F, int N, double fc,
                              hipStream_t s);
-// Spherical-voxel model (oat_sph.hip); part holds sph_workspace_bytes.
-size_t sph_workspace_bytes(const Problem &P, int n_f);
+// Spherical-voxel model (oat_sph.hip); part and work hold
+// sph_workspace_bytes and sph_adj_workspace_bytes (0: none needed).
+size_t sph_workspace_bytes(const Problem &P, int n_f, double f_min, double df);
 hipError_t launch_sph_project(const Problem &P, const void *img, int img_dt, float2 *u, int n_f,
                               double f_min, double df, double2 *part, hipStream_t s);
-// Adjoint: small images split the transducers into sph_adj_slices(P) slices
-// whose FP64 partial images go to work (sph_adj_workspace_bytes; none for
-// one slice).
-int sph_adj_slices(const Problem &P);
-size_t sph_adj_workspace_bytes(const Problem &P);
+size_t sph_adj_workspace_bytes(const Problem &P, int n_f, double f_min, double df);
 hipError_t launch_sph_backproject(const Problem &P, const float2 *u, int n_f, double f_min,
                                   double df, void *img, int img_dt, double *work, hipStream_t s);
-// The adjoint's slice sums never exceed 2 x 523776 doubles: sph_adj_slices
-// splits only images of fewer than 1024 workgroups of 512 voxels, and over
-// every such voxel count N the product slices x N peaks at two slices of
-// 523776 voxels.  So this fixed scratch holds them for every image.
-constexpr size_t SPH_SCRATCH_BYTES = size_t(8) << 20;
+// Fixed scratch that holds the adjoint's workspace for every call: the dense
+// path's slices x voxels peak at 2 x 523776 doubles (8 MiB); the table
+// path's partial sums are at most 1024 tiles of 2048 doubles (16 MiB) and
+// its basis 256 KiB, and its table batches are sized to the rest.
+constexpr size_t SPH_SCRATCH_BYTES = size_t(64) << 20;
 // Device address of the fixed scratch on `device`, which must be current.
 // Resolved by hipGetSymbolAddress on the first call for that device, cached
 // afterwards (thread-safe).

@@ -659,6 +659,7 @@ int oat_plan_create_ex(const oat_geometry *g, int device, const oat_plan_options
     P.n_segref = (int)segref.size();
     P.sph_pts = plan->d_sph_pts;
     P.sph_ns = 1;
+    P.sph_rf = 0.0;
     plan->det = det;
     P.adj_r = nullptr;
     P.tab_off = nullptr;
@@ -912,7 +913,7 @@ int oat_sph_project(oat_plan *plan, const void *img, oat_dtype img_dtype, void *
     if (rc) return rc;
     int prev;
     if ((rc = with_device(plan, prev))) return rc;
-    if ((rc = ensure_sph_workspace(plan, sph_workspace_bytes(plan->P, n_f), "oat_sph_project"))) {
+    if ((rc = ensure_sph_workspace(plan, sph_workspace_bytes(plan->P, n_f, f_min, df), "oat_sph_project"))) {
         (void)hipSetDevice(prev);
         return rc;
     }
@@ -930,7 +931,7 @@ int oat_sph_backproject(oat_plan *plan, const void *u, int n_f, double f_min, do
     if (rc) return rc;
     int prev;
     if ((rc = with_device(plan, prev))) return rc;
-    if ((rc = ensure_sph_workspace(plan, sph_adj_workspace_bytes(plan->P),
+    if ((rc = ensure_sph_workspace(plan, sph_adj_workspace_bytes(plan->P, n_f, f_min, df),
                                    "oat_sph_backproject"))) {
         (void)hipSetDevice(prev);
         return rc;
@@ -980,6 +981,7 @@ int oat_plan_set_aperture(oat_plan *plan, double width, double height, int m)
     plan->d_sph_pts = buf;
     plan->P.sph_pts = buf;
     plan->P.sph_ns = point ? 1 : m * m;
+    plan->P.sph_rf = point ? 0.0 : R;
     plan->ap_w = point ? 0.0 : width;
     plan->ap_h = point ? 0.0 : height;
     plan->ap_m = mm;
@@ -993,7 +995,7 @@ int oat_sph_backproject_noalloc(oat_plan *plan, const void *u, int n_f, double f
     int rc = check_sph(plan, u, img, (int)img_dtype, n_f, f_min, df, flags,
                        "oat_sph_backproject_noalloc");
     if (rc) return rc;
-    const size_t need = sph_adj_workspace_bytes(plan->P);
+    const size_t need = sph_adj_workspace_bytes(plan->P, n_f, f_min, df);
     if (need > SPH_SCRATCH_BYTES)
         return fail(OAT_ERR_ARG, "oat_sph_backproject_noalloc: the image needs " +
                                      std::to_string(need) + " bytes of scratch, more than the " +
