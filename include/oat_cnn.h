@@ -61,6 +61,31 @@ size_t oat_mse_workspace(void);
 int oat_mse(const void *y, oat_dtype ydt, const void *target, oat_dtype tdt, int64_t n,
             float *loss, void *dy, void *workspace, void *stream);
 
+/* The whole network z = x + C3(relu(C2(relu(C1(x))))), 3x3x3 kernels, 16
+ * channels, on one volume [d][h][w] with BF16 activations, and its parameter
+ * gradients.  C1 and C3 (one channel on one side) use the FP32 weights as they
+ * are, C2 rounds its weights to BF16; sums are FP32.  Every layer's output is
+ * rounded to BF16 once, C3's before x is added.
+ *
+ * oat_net_forward: x of xdt (rounded to BF16 if FP32), z BF16.  a1 and a2
+ * receive the activations after C1 and C2, BF16, channel-last [d][h][w][16].
+ * oat_net_backward: gradients of w1 [16][1][27], w2 [16][16][27],
+ * w3 [1][16][27] and the biases for dz = dloss/dz (BF16), from the forward's x
+ * (as BF16), a1 and a2; every gradient is overwritten; deterministic.
+ *
+ * a1, a2, workspace and the 16-value biases must be 16-byte aligned.  The
+ * workspace holds oat_net_workspace(d, h, w, backward) bytes (0: sizes out of
+ * range, d, h, w >= 1).  z must not overlap x. */
+size_t oat_net_workspace(int d, int h, int w, int backward);
+int oat_net_forward(const void *x, oat_dtype xdt, int d, int h, int w, const float *w1,
+                    const float *b1, const float *w2, const float *b2, const float *w3,
+                    const float *b3, void *a1, void *a2, void *z, void *workspace,
+                    size_t workspace_bytes, void *stream);
+int oat_net_backward(const void *x, const void *a1, const void *a2, const void *dz, int d, int h,
+                     int w, const float *w2, const float *w3, float *dw1, float *dw2, float *dw3,
+                     float *db1, float *db2, float *db3, void *workspace, size_t workspace_bytes,
+                     void *stream);
+
 #ifdef __cplusplus
 }
 #endif

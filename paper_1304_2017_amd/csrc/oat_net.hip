@@ -1,0 +1,671 @@
+// The learned preconditioner z = x + C3(relu(C2(relu(C1(x))))) on gfx950, BF16
+// activations: forward pass and parameter gradients as a handful of launches
+// (include/oat_cnn.h).  The 16-channel activations are kept channel-last,
+// [z][y][x][16]: a voxel is 32 bytes, so halo tiles load and results store in
+// whole vectors, and a voxel's channels are the k values of an MFMA operand.
+//
+// Operand layout of v_mfma_f32_16x16x32_bf16: lane l holds row (A) or column
+// (B) l % 16 and 8 k values of group g = l / 16; the result holds column l % 16
+// and rows 4 g .. 4 g + 3.  Which k a group's slots stand for is free as long
+// as A and B agree.
+//
+// The one-channel layers and their weights' gradients used to run on the VALU
+// with FP32 weights.  Their FP32 weights are split here into three BF16 terms
+// w = w1 + w2 + w3 (exact to 2^-27): BF16 products are exact in FP32, so the
+// sums are as accurate as FP32 multiply-adds.  The 16 -> 16 layer rounds its
+// weights to BF16, as in oat_conv3d_forward.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <string>
+
+#include "oat.h"
+#include "oat_cnn.h"
+#include "oat_internal.hpp"
+
+namespace {
+
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+typedef unsigned short u16;
+
+__device__ __forceinline__ bf16x8 as_op(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
+__device__ __forceinline__ float bf_f(unsigned bits) { return __uint_as_float(bits << 16); }
+__device__ __forceinline__ unsigned f_bf(float v)
+{
+    return (unsigned)__builtin_bit_cast(u16, (__bf16)v);   // round to nearest even
+}
+__device__ __forceinline__ f32x4 mfma(u32x4 a, u32x4 b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_op(a), as_op(b), c, 0, 0, 0);
+}
+
+// The s-th BF16 term of w (s = 0, 1, 2).
+__device__ __forceinline__ unsigned split_term(float w, int s)
+{
+    unsigned b = f_bf(w);
+    for (int i = 0; i < s; ++i) {
+        const float r = w - bf_f(b);
+        w = fabsf(w) <= 3.4e38f ? r : 0.f;   // a non-finite weight has no remainder
+        b = f_bf(w);
+    }
+    return b;
+}
+
+// One-channel input value as FP32, then BF16 bits (FP32 inputs are rounded).
+__device__ __forceinline__ unsigned in_bits(const void *x, size_t i, int dt)
+{
+    return dt == 0 ? f_bf(((const float *)x)[i]) : (unsigned)((const u16 *)x)[i];
+}
+
+// ---------------------------------------------------------------------------
+// 16 -> 16: weight fragments.  The taps of a row dy come as 5 k-blocks of two
+// taps: (dz, dx = 0 | dx = 1) for dz = 0, 1, 2, then dx = 2 of dz = 0 | 1 and of
+// dz = 2 | nothing.  k slot 8 (g & 1) + j of tap half g >> 1 is channel
+// 8 (g & 1) + j.  frag[dy * 5 + f][lane], row (output channel) lane % 16.
+// ---------------------------------------------------------------------------
+constexpr int NFRAG = 15;
+
+__device__ __forceinline__ void block_tap(int f, int half, int &dz, int &dx)
+{
+    if (f < 3) {
+        dz = f;
+        dx = half;
+    } else {
+        dz = f == 3 ? half : 2;
+        dx = (f == 4 && half) ? -1 : 2;   // -1: no tap
+    }
+}
+
+// flip: weights of the data backward, W'[o][i][t] = w[i][o][26 - t].
+__device__ void write_fragments(const float *__restrict__ w, int flip, u32x4 *__restrict__ frag)
+{
+    for (int e = threadIdx.x; e < NFRAG * 64; e += blockDim.x) {
+        const int lane = e & 63, dy = (e >> 6) / 5, f = (e >> 6) % 5;
+        const int co = lane & 15, g = lane >> 4;
+        int dz, dx;
+        block_tap(f, g >> 1, dz, dx);
+        u32x4 v = {0u, 0u, 0u, 0u};
+        if (dx >= 0) {
+            const int t = 9 * dz + 3 * dy + dx;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const int ci = 8 * (g & 1) + j;
+                const float a = flip ? w[(ci * 16 + co) * 27 + 26 - t] : w[(co * 16 + ci) * 27 + t];
+                v[j >> 1] |= f_bf(a) << (16 * (j & 1));
+            }
+        }
+        frag[e] = v;
+    }
+}
+
+// Four channels of a voxel: bias, ReLU or mask (zero where mask <= 0), one
+// rounding, one 8-byte store.
+__device__ __forceinline__ void store4(u16 *__restrict__ y, size_t vox, int g, f32x4 v, f32x4 bias,
+                                       bool relu, const u16 *__restrict__ mask)
+{
+    const size_t o = vox * 16 + 4 * g;
+    u32x2 m = {0u, 0u};
+    if (mask) m = *reinterpret_cast<const u32x2 *>(mask + o);
+    unsigned b[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        float f = v[r] + bias[r];
+        if (relu) f = fmaxf(f, 0.f);
+        if (mask && !(bf_f((m[r >> 1] >> (16 * (r & 1))) & 0xffffu) > 0.f)) f = 0.f;
+        b[r] = f_bf(f);
+    }
+    *reinterpret_cast<u32x2 *>(y + o) = u32x2{b[0] | (b[1] << 16), b[2] | (b[3] << 16)};
+}
+
+// ---------------------------------------------------------------------------
+// 1 -> 16 (C1, and the data backward of C3 with flipped weights).  A tile of
+// 32 x 8 x 4 voxels; B: column = voxel, k = tap (27 of 32), gathered from the
+// halo tile in LDS; A: the weights' three terms.  Workgroup (0, 0, 0) also
+// writes the 16 -> 16 fragments of the layer that follows.
+// Bound by its 32 bytes a voxel of output.
+// ---------------------------------------------------------------------------
+constexpr int C1X = 32, C1Y = 8, C1Z = 4, C1_THREADS = 256;
+constexpr int C1P = C1X + 4, C1HY = C1Y + 2, C1HZ = C1Z + 2;   // LDS row pitch, halo rows and planes
+
+__global__ void __launch_bounds__(C1_THREADS)
+net_c1_kernel(const void *__restrict__ x, int xdt, int D, int H, int W, const float *__restrict__ w,
+              int flip, const float *__restrict__ bias, u16 *__restrict__ y, int relu,
+              const u16 *__restrict__ mask, const float *__restrict__ w16, u32x4 *__restrict__ frag)
+{
+    __shared__ u16 xs[C1HZ * C1HY * C1P];
+    const int x0 = blockIdx.x * C1X, y0 = blockIdx.y * C1Y, z0 = blockIdx.z * C1Z;
+    const size_t plane = (size_t)H * W;
+    for (int i = threadIdx.x; i < C1HZ * C1HY * (C1X + 2); i += C1_THREADS) {
+        const int xx = i % (C1X + 2), r = i / (C1X + 2), yy = r % C1HY, zz = r / C1HY;
+        const int gx = x0 - 1 + xx, gy = y0 - 1 + yy, gz = z0 - 1 + zz;
+        unsigned v = 0;
+        if (gx >= 0 && gx < W && gy >= 0 && gy < H && gz >= 0 && gz < D)
+            v = in_bits(x, gz * plane + (size_t)gy * W + gx, xdt);
+        xs[r * C1P + xx] = (u16)v;
+    }
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    u32x4 a[3];
+    int off[8];
+#pragma unroll
+    for (int s = 0; s < 3; ++s) a[s] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int t = 8 * g + j, tt = t < 27 ? t : 26;   // (the slots past 26 have zero weights)
+        off[j] = ((tt / 9) * C1HY + (tt / 3) % 3) * C1P + tt % 3 + col;
+        if (t < 27) {
+            const float f = w[col * 27 + (flip ? 26 - t : t)];
+#pragma unroll
+            for (int s = 0; s < 3; ++s) a[s][j >> 1] |= split_term(f, s) << (16 * (j & 1));
+        }
+    }
+    f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
+    if (bias) b4 = *reinterpret_cast<const f32x4 *>(bias + 4 * g);
+    if (frag && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) write_fragments(w16, flip, frag);
+    __syncthreads();
+    // wave = plane z of the tile; 16 groups of 16 voxels along x
+    const int gz = z0 + wave;
+    if (gz >= D) return;
+#pragma unroll
+    for (int k = 0; k < 2 * C1Y; ++k) {
+        const int ly = k >> 1, lx = (k & 1) * 16;
+        const int gy = y0 + ly, gx = x0 + lx + col;
+        const int base = (wave * C1HY + ly) * C1P + lx;
+        u32x4 v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            v[j] = (unsigned)xs[base + off[2 * j]] | ((unsigned)xs[base + off[2 * j + 1]] << 16);
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        acc = mfma(a[2], v, acc);
+        acc = mfma(a[1], v, acc);
+        acc = mfma(a[0], v, acc);
+        if (gy < H && gx < W) store4(y, gz * plane + (size_t)gy * W + gx, g, acc, b4, relu, mask);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// 16 -> 16.  A workgroup takes 16 x 8 x 8 voxels, a wave one plane (8 rows of
+// 16): A = weights (rows co), B = voxels.  A row's operands are read once per
+// input row and serve the three output rows that it touches, so the LDS
+// supplies 50 operands for 120 MFMAs.  The halo tile sits in LDS as two
+// planes of 8 channels, 16 bytes a voxel: 16 lanes read 256 consecutive bytes.
+// ---------------------------------------------------------------------------
+constexpr int C2X = 16, C2Y = 8, C2Z = 8, C2_THREADS = 512;
+constexpr int C2HX = C2X + 2, C2HY = C2Y + 2, C2HZ = C2Z + 2, C2HV = C2HX * C2HY * C2HZ;
+
+__global__ void __launch_bounds__(C2_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
+net_c2_kernel(const u16 *__restrict__ x, int D, int H, int W, const u32x4 *__restrict__ frag,
+              const float *__restrict__ bias, u16 *__restrict__ y, int relu,
+              const u16 *__restrict__ mask)
+{
+    __shared__ u32x4 xs[2 * C2HV];
+    const int x0 = blockIdx.x * C2X, y0 = blockIdx.y * C2Y, z0 = blockIdx.z * C2Z;
+    const size_t plane = (size_t)H * W;
+    for (int i = threadIdx.x; i < 2 * C2HV; i += C2_THREADS) {
+        const int half = i & 1, v = i >> 1;
+        const int xx = v % C2HX, r = v / C2HX, yy = r % C2HY, zz = r / C2HY;
+        const int gx = x0 - 1 + xx, gy = y0 - 1 + yy, gz = z0 - 1 + zz;
+        u32x4 d = {0u, 0u, 0u, 0u};
+        if (gx >= 0 && gx < W && gy >= 0 && gy < H && gz >= 0 && gz < D)
+            d = *reinterpret_cast<const u32x4 *>(x + (gz * plane + (size_t)gy * W + gx) * 16 + half * 8);
+        xs[half * C2HV + v] = d;
+    }
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    u32x4 a[NFRAG];
+#pragma unroll
+    for (int i = 0; i < NFRAG; ++i) a[i] = frag[i * 64 + lane];
+    f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
+    if (bias) b4 = *reinterpret_cast<const f32x4 *>(bias + 4 * g);
+    __syncthreads();
+    const int gz = z0 + wave;
+    if (gz >= D) return;
+    // operand addresses of input row 0 of plane dz = 0: blocks 0..2 (dx = g >> 1),
+    // block 3 (dz = g >> 1, dx = 2), block 4 (dz = 2, dx = 2)
+    const int h = (g & 1) * C2HV + wave * C2HY * C2HX + col;
+    const u32x4 *__restrict__ p0 = xs + h + (g >> 1);
+    const u32x4 *__restrict__ p3 = xs + h + (g >> 1) * C2HY * C2HX + 2;
+    const u32x4 *__restrict__ p4 = xs + h + 2 * C2HY * C2HX + 2;
+    f32x4 acc[C2Y];
+#pragma unroll
+    for (int r = 0; r < C2Y; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int yi = 0; yi < C2HY; ++yi) {
+        u32x4 v[5];
+#pragma unroll
+        for (int f = 0; f < 3; ++f) v[f] = p0[(f * C2HY + yi) * C2HX];
+        v[3] = p3[yi * C2HX];
+        v[4] = p4[yi * C2HX];
+#pragma unroll
+        for (int f = 0; f < 5; ++f)
+#pragma unroll
+            for (int dy = 0; dy < 3; ++dy) {
+                const int r = yi - dy;
+                if (r >= 0 && r < C2Y) acc[r] = mfma(a[dy * 5 + f], v[f], acc[r]);
+            }
+    }
+    const int gx = x0 + col;
+    if (gx >= W) return;
+#pragma unroll
+    for (int r = 0; r < C2Y; ++r)
+        if (y0 + r < H)
+            store4(y, gz * plane + (size_t)(y0 + r) * W + gx, g, acc[r], b4, relu, mask);
+}
+
+// ---------------------------------------------------------------------------
+// 16 -> 1 with the skip: z = x + r, r = C3(a) rounded to BF16 as a stored
+// layer would be.  A column of 32 x 16 voxels marches along z.  Per input
+// plane the matrix cores form Y[tap][voxel] = sum_ci w[ci][tap] a[voxel][ci]
+// once per halo voxel (k = channel, twice: the slots 16 .. 31 carry the second
+// weight term), into LDS; every thread then adds the 27 shifted values to the
+// three output planes that the input plane touches.
+// ---------------------------------------------------------------------------
+constexpr int C3X = 32, C3Y = 16, C3_THREADS = 512, C3_WAVES = C3_THREADS / 64;
+constexpr int C3HX = C3X + 2, C3HY = C3Y + 2, C3HV = C3HX * C3HY;   // 612
+constexpr int C3P = 628;                         // row pitch of Y: 4 rows apart are 16 banks apart
+constexpr int C3G = (C3HV + 15) / 16;            // groups of 16 voxels
+constexpr int C3GW = (C3G + C3_WAVES - 1) / C3_WAVES;
+
+__global__ void __launch_bounds__(C3_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
+net_c3_kernel(const u16 *__restrict__ a, const void *__restrict__ x, int xdt, int D, int H, int W,
+              const float *__restrict__ w, const float *__restrict__ bias, u16 *__restrict__ z, int zr)
+{
+    __shared__ float ys[27 * C3P];
+    const int x0 = blockIdx.x * C3X, y0 = blockIdx.y * C3Y, z0 = blockIdx.z * zr;
+    const int z1 = min(D, z0 + zr);
+    const size_t plane = (size_t)H * W;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    // weights: [tap tile][terms 1 and 2 | term 3]
+    u32x4 wt[2][2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            wt[m][p] = u32x4{0u, 0u, 0u, 0u};
+            const int t = 16 * m + col;
+            if (t < 27 && (p == 0 || g < 2))
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    wt[m][p][j >> 1] |= split_term(w[(8 * (g & 1) + j) * 27 + t], p == 0 ? g >> 1 : 2)
+                                        << (16 * (j & 1));
+        }
+    // this wave's halo voxels: groups wave, wave + 8, ...
+    int idx[C3GW];        // offset in the plane, -1 outside the volume
+#pragma unroll
+    for (int k = 0; k < C3GW; ++k) {
+        const int v = (wave + k * C3_WAVES) * 16 + col;
+        const int gx = x0 - 1 + v % C3HX, gy = y0 - 1 + v / C3HX;
+        idx[k] = (v < C3HV && gx >= 0 && gx < W && gy >= 0 && gy < H) ? gy * W + gx : -1;
+    }
+    const int lx = threadIdx.x % C3X, ly = threadIdx.x / C3X;
+    const int gx = x0 + lx, gy = y0 + ly;
+    const float b0 = bias ? bias[0] : 0.f;
+    const float *__restrict__ yr = ys + ly * C3HX + lx;
+    float acc[3] = {b0, b0, b0};   // output planes zi - 1, zi, zi + 1 of input plane zi
+    u32x4 v[C3GW];
+    auto load = [&](int zi) {
+#pragma unroll
+        for (int k = 0; k < C3GW; ++k) {
+            v[k] = u32x4{0u, 0u, 0u, 0u};
+            if (idx[k] >= 0 && zi >= 0 && zi < D)
+                v[k] = *reinterpret_cast<const u32x4 *>(a + (zi * plane + idx[k]) * 16 + (g & 1) * 8);
+        }
+    };
+    load(z0 - 1);
+    for (int zi = z0 - 1; zi <= z1; ++zi) {
+#pragma unroll
+        for (int k = 0; k < C3GW; ++k) {
+            const int grp = wave + k * C3_WAVES;
+            if (grp >= C3G) break;
+            f32x4 r0 = {0.f, 0.f, 0.f, 0.f}, r1 = r0;
+            r0 = mfma(wt[0][1], v[k], r0);
+            r1 = mfma(wt[1][1], v[k], r1);
+            r0 = mfma(wt[0][0], v[k], r0);
+            r1 = mfma(wt[1][0], v[k], r1);
+            float *dst = ys + grp * 16 + col;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                dst[(4 * g + r) * C3P] = r0[r];
+                if (16 + 4 * g + r < 27) dst[(16 + 4 * g + r) * C3P] = r1[r];
+            }
+        }
+        if (zi < z1) load(zi + 1);   // in flight while the sums run
+        __syncthreads();
+#pragma unroll
+        for (int dz = 0; dz < 3; ++dz) {
+            float s = acc[2 - dz];
+#pragma unroll
+            for (int t = 0; t < 9; ++t) s += yr[(9 * dz + t) * C3P + (t / 3) * C3HX + t % 3];
+            acc[2 - dz] = s;
+        }
+        __syncthreads();
+        const int zo = zi - 1;
+        if (zo >= z0 && gx < W && gy < H) {
+            const size_t o = zo * plane + (size_t)gy * W + gx;
+            z[o] = (u16)f_bf(bf_f(in_bits(x, o, xdt)) + bf_f(f_bf(acc[0])));
+        }
+        acc[0] = acc[1];
+        acc[1] = acc[2];
+        acc[2] = b0;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Weight gradients: sums over voxels, the k of the MFMAs.  Channel-last tiles
+// become operands (row or column = channel, k = voxels) by transposed LDS reads:
+// ds_read_b64_tr_b16 gives lane i of a group of 16 channel i of the 4 voxels
+// whose 4 x 16 values the group's lanes address.  A step takes the 32 voxels of
+// two rows: slots 0 .. 3 of group g are voxels 4 g .. 4 g + 3 of the first row,
+// slots 4 .. 7 those of the second.  Workgroups keep their sums in registers
+// over all their tiles and write one partial each; the partials are added in
+// workgroup order (deterministic).
+// ---------------------------------------------------------------------------
+constexpr int GX = 16, GY = 8, GZ = 4, G_THREADS = 256, G_GRID = 512;
+constexpr int GHX = GX + 2, GHY = GY + 2, GHZ = GZ + 2, GHV = GHX * GHY * GHZ, GV = GX * GY * GZ;
+constexpr int NJ1 = 16 * 27 + 16, NJ2 = 16 * 16 * 27 + 16, NJ3 = 16 * 27 + 1;   // C1, C2, C3
+constexpr int NJ = NJ1 + NJ2 + NJ3;
+
+__device__ __forceinline__ u32x2 tr_read(const u16 *p)
+{
+    const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+        (__attribute__((address_space(3))) s16x4 *)p);
+    return __builtin_bit_cast(u32x2, v);
+}
+
+// A 16-channel halo or core tile, 32 bytes a voxel, zero outside the volume.
+template <int NX, int NY, int NZ>
+__device__ __forceinline__ void load_cl(u32x4 *__restrict__ dst, const u16 *__restrict__ src, int D,
+                                        int H, int W, int x0, int y0, int z0)
+{
+    for (int i = threadIdx.x; i < 2 * NX * NY * NZ; i += G_THREADS) {
+        const int v = i >> 1, xx = v % NX, r = v / NX, yy = r % NY, zz = r / NY;
+        const int gx = x0 + xx, gy = y0 + yy, gz = z0 + zz;
+        u32x4 d = {0u, 0u, 0u, 0u};
+        if (gx >= 0 && gx < W && gy >= 0 && gy < H && gz >= 0 && gz < D)
+            d = *reinterpret_cast<const u32x4 *>(src + (((size_t)gz * H + gy) * W + gx) * 16 + (i & 1) * 8);
+        dst[i] = d;
+    }
+}
+
+__device__ __forceinline__ void tile_origin(int tile, int tx, int ty, int &x0, int &y0, int &z0)
+{
+    x0 = tile % tx * GX;
+    y0 = tile / tx % ty * GY;
+    z0 = tile / (tx * ty) * GZ;
+}
+
+// C2: dW[co][ci][tap] = sum_v dy[v][co] x[v + tap][ci]; wave w takes taps w,
+// w + 4, ..., and wave 3 the bias (a tap whose x is 1).
+__global__ void __launch_bounds__(G_THREADS)
+net_wgrad16_kernel(const u16 *__restrict__ x, const u16 *__restrict__ dy, int D, int H, int W, int tx,
+                   int ty, int tiles, float *__restrict__ part)
+{
+    __shared__ u32x4 xs[2 * GHV], gs[2 * GV];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    // address of this lane's 8 bytes of a transposed read at voxel 0
+    const u16 *__restrict__ xl = reinterpret_cast<const u16 *>(xs) + (4 * g + (col >> 2)) * 16 + (col & 3) * 4;
+    const u16 *__restrict__ gl = reinterpret_cast<const u16 *>(gs) + (4 * g + (col >> 2)) * 16 + (col & 3) * 4;
+    f32x4 acc[7];
+    int toff[7];
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+        const int t = min(wave + 4 * k, 26);
+        acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+        toff[k] = (((t / 9) * GHY + (t / 3) % 3) * GHX + t % 3) * 16;
+    }
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        int x0, y0, z0;
+        tile_origin(tile, tx, ty, x0, y0, z0);
+        __syncthreads();
+        load_cl<GHX, GHY, GHZ>(xs, x, D, H, W, x0 - 1, y0 - 1, z0 - 1);
+        load_cl<GX, GY, GZ>(gs, dy, D, H, W, x0, y0, z0);
+        __syncthreads();
+#pragma unroll 2
+        for (int s = 0; s < GV / 32; ++s) {   // rows 2 s and 2 s + 1 of the tile
+            const int lz = s / (GY / 2), ly = s % (GY / 2) * 2;
+            const u32x2 a0 = tr_read(gl + (lz * GY + ly) * GX * 16),
+                        a1 = tr_read(gl + (lz * GY + ly + 1) * GX * 16);
+            const u32x4 av = {a0[0], a0[1], a1[0], a1[1]};
+            const u16 *__restrict__ xr = xl + (lz * GHY + ly) * GHX * 16;
+#pragma unroll
+            for (int k = 0; k < 7; ++k) {
+                const u32x2 b0 = tr_read(xr + toff[k]), b1 = tr_read(xr + toff[k] + GHX * 16);
+                u32x4 bv = {b0[0], b0[1], b1[0], b1[1]};
+                if (k == 6 && wave == 3) bv = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+                acc[k] = mfma(av, bv, acc[k]);
+            }
+        }
+    }
+    float *dst = part + (size_t)blockIdx.x * NJ + NJ1;
+#pragma unroll
+    for (int k = 0; k < 7; ++k) {
+        const int t = wave + 4 * k;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (t < 27)
+                dst[((4 * g + r) * 16 + col) * 27 + t] = acc[k][r];
+            else if (col == 0)
+                dst[16 * 16 * 27 + 4 * g + r] = acc[k][r];
+        }
+    }
+}
+
+// One-channel layers: P[ch][tap] = sum_v s[v][ch] t[v + tap].  C1: s = dy, t = x
+// (with the bias, sum_v s[v][ch], as tap 27); C3: s = x, t = dy and tap 26 - tap
+// (with the bias, sum_v t[v]).  A: rows = taps, from three copies of t's tile
+// shifted by dx, so that runs of 4 voxels are aligned; B: s, transposed.
+template <bool C3>
+__global__ void __launch_bounds__(G_THREADS)
+net_wgrad1_kernel(const u16 *__restrict__ sv, const u16 *__restrict__ tv, int D, int H, int W, int tx,
+                  int ty, int tiles, float *__restrict__ part)
+{
+    __shared__ u32x4 ss[2 * GV];
+    __shared__ __attribute__((aligned(16))) u16 ts[3][GHZ * GHY][GX];
+    __shared__ float red[4][2][64][4];
+    __shared__ float bred[4];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
+    const u16 *__restrict__ sl = reinterpret_cast<const u16 *>(ss) + (4 * g + (col >> 2)) * 16 + (col & 3) * 4;
+    f32x4 acc[2];
+    const u16 *__restrict__ tp[2];
+    bool one[2], none[2];
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const int t = min(16 * m + col, 26);
+        acc[m] = f32x4{0.f, 0.f, 0.f, 0.f};
+        tp[m] = &ts[t % 3][(t / 9) * GHY + (t / 3) % 3][4 * g];
+        one[m] = 16 * m + col == 27;
+        none[m] = 16 * m + col > 27;
+    }
+    float bsum = 0.f;
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        int x0, y0, z0;
+        tile_origin(tile, tx, ty, x0, y0, z0);
+        __syncthreads();
+        load_cl<GX, GY, GZ>(ss, sv, D, H, W, x0, y0, z0);
+        for (int i = threadIdx.x; i < GHX * GHY * GHZ; i += G_THREADS) {
+            const int xx = i % GHX, r = i / GHX, yy = r % GHY, zz = r / GHY;
+            const int gx = x0 - 1 + xx, gy = y0 - 1 + yy, gz = z0 - 1 + zz;
+            u16 v = 0;
+            if (gx >= 0 && gx < W && gy >= 0 && gy < H && gz >= 0 && gz < D)
+                v = tv[((size_t)gz * H + gy) * W + gx];
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx)
+                if (xx - dx >= 0 && xx - dx < GX) ts[dx][r][xx - dx] = v;
+            if (C3 && xx > 0 && xx <= GX && yy > 0 && yy <= GY && zz > 0 && zz <= GZ) bsum += bf_f(v);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < GV / 32 / 4; ++k) {
+            const int s = wave * (GV / 32 / 4) + k, lz = s / (GY / 2), ly = s % (GY / 2) * 2;
+            const u32x2 b0 = tr_read(sl + (lz * GY + ly) * GX * 16),
+                        b1 = tr_read(sl + (lz * GY + ly + 1) * GX * 16);
+            const u32x4 bv = {b0[0], b0[1], b1[0], b1[1]};
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                const u16 *__restrict__ p = tp[m] + (lz * GHY + ly) * GX;
+                const u32x2 a0 = *reinterpret_cast<const u32x2 *>(p),
+                            a1 = *reinterpret_cast<const u32x2 *>(p + GX);
+                u32x4 av = {a0[0], a0[1], a1[0], a1[1]};
+                if (one[m]) av = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+                if (none[m]) av = u32x4{0u, 0u, 0u, 0u};
+                acc[m] = mfma(av, bv, acc[m]);
+            }
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[wave][m][lane][r] = acc[m][r];
+    if (C3) {
+        for (int o = 32; o > 0; o >>= 1) bsum += __shfl_xor(bsum, o);
+        if (lane == 0) bred[wave] = bsum;
+    }
+    __syncthreads();
+    float *dst = part + (size_t)blockIdx.x * NJ + (C3 ? NJ1 + NJ2 : 0);
+    for (int i = threadIdx.x; i < 512; i += G_THREADS) {
+        const int r = i & 3, l = (i >> 2) & 63, m = i >> 8;
+        const int t = 16 * m + 4 * (l >> 4) + r, ch = l & 15;
+        const float v = (red[0][m][l][r] + red[1][m][l][r]) + (red[2][m][l][r] + red[3][m][l][r]);
+        if (t < 27)
+            dst[ch * 27 + (C3 ? 26 - t : t)] = v;
+        else if (!C3 && t == 27)
+            dst[16 * 27 + ch] = v;
+    }
+    if (C3 && threadIdx.x == 0) dst[16 * 27] = (bred[0] + bred[1]) + (bred[2] + bred[3]);
+}
+
+// Gradients from the workgroups' partials, added in workgroup order: 64 columns
+// and 16 runs of workgroups per block, then the runs.
+struct NetGrads {
+    float *dw1, *dw2, *dw3, *db1, *db2, *db3;
+};
+__global__ void __launch_bounds__(1024)
+net_wgrad_sum_kernel(const float *__restrict__ part, int n, NetGrads o)
+{
+    __shared__ float red[16][64];
+    const int c = threadIdx.x & 63, run = threadIdx.x >> 6, j = blockIdx.x * 64 + c;
+    const int per = (n + 15) / 16, i0 = run * per, i1 = min(n, i0 + per);
+    float s = 0.f;
+    if (j < NJ)
+        for (int i = i0; i < i1; ++i) s += part[(size_t)i * NJ + j];
+    red[run][c] = s;
+    __syncthreads();
+    if (run > 0 || j >= NJ) return;
+    for (int r = 1; r < 16; ++r) s += red[r][c];
+    if (j < 16 * 27) o.dw1[j] = s;
+    else if (j < NJ1) o.db1[j - 16 * 27] = s;
+    else if (j < NJ1 + 16 * 16 * 27) o.dw2[j - NJ1] = s;
+    else if (j < NJ1 + NJ2) o.db2[j - NJ1 - 16 * 16 * 27] = s;
+    else if (j < NJ1 + NJ2 + 16 * 27) o.dw3[j - NJ1 - NJ2] = s;
+    else o.db3[0] = s;
+}
+
+constexpr size_t FRAG_BYTES = (sizeof(u32x4) * NFRAG * 64 + 255) / 256 * 256;
+
+int net_fail(int code, const char *msg)
+{
+    oat::set_last_error(msg);
+    return code;
+}
+
+int net_launched(const char *who)
+{
+    const hipError_t e = hipGetLastError();
+    if (e == hipSuccess) return OAT_OK;
+    oat::set_last_error((std::string(who) + ": " + hipGetErrorName(e)).c_str());
+    return OAT_ERR_DEVICE;
+}
+
+unsigned up(int n, int t) { return (unsigned)((n + t - 1) / t); }
+
+// Sizes that the kernels' 32-bit plane offsets and grids hold.
+bool net_size_ok(int d, int h, int w)
+{
+    return d >= 1 && h >= 1 && w >= 1 && (long long)h * w < (1ll << 31) &&
+           (long long)up(w, GX) * up(h, GY) * up(d, GZ) < (1ll << 31) && up(h, C1Y) <= 65535 &&
+           up(d, C1Z) <= 65535;
+}
+
+dim3 c1_grid(int d, int h, int w) { return dim3(up(w, C1X), up(h, C1Y), up(d, C1Z)); }
+dim3 c2_grid(int d, int h, int w) { return dim3(up(w, C2X), up(h, C2Y), up(d, C2Z)); }
+
+bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
+
+}  // namespace
+
+extern "C" {
+
+size_t oat_net_workspace(int d, int h, int w, int backward)
+{
+    if (!net_size_ok(d, h, w)) return 0;
+    const size_t n = (size_t)d * h * w;
+    return FRAG_BYTES + (backward ? 2 * 32 * n + sizeof(float) * (size_t)G_GRID * NJ : 0);
+}
+
+int oat_net_forward(const void *x, oat_dtype xdt, int d, int h, int w, const float *w1, const float *b1,
+                    const float *w2, const float *b2, const float *w3, const float *b3, void *a1,
+                    void *a2, void *z, void *workspace, size_t workspace_bytes, void *stream)
+{
+    if (!x || !w1 || !b1 || !w2 || !b2 || !w3 || !b3 || !a1 || !a2 || !z || !workspace)
+        return net_fail(OAT_ERR_ARG, "oat_net_forward: null pointer");
+    if (!net_size_ok(d, h, w)) return net_fail(OAT_ERR_ARG, "oat_net_forward: bad volume sizes");
+    if (xdt != OAT_F32 && xdt != OAT_BF16) return net_fail(OAT_ERR_DTYPE, "oat_net_forward: unknown dtype");
+    if (x == z || a1 == a2) return net_fail(OAT_ERR_ARG, "oat_net_forward: buffers alias");
+    if (!aligned16(a1) || !aligned16(a2) || !aligned16(workspace) || !aligned16(b1) || !aligned16(b2))
+        return net_fail(OAT_ERR_ARG, "oat_net_forward: buffers must be 16-byte aligned");
+    if (workspace_bytes < oat_net_workspace(d, h, w, 0))
+        return net_fail(OAT_ERR_ARG, "oat_net_forward: workspace too small");
+    const hipStream_t s = (hipStream_t)stream;
+    u32x4 *frag = (u32x4 *)workspace;
+    hipLaunchKernelGGL(net_c1_kernel, c1_grid(d, h, w), dim3(C1_THREADS), 0, s, x, (int)xdt, d, h, w, w1, 0,
+                       b1, (u16 *)a1, 1, (const u16 *)nullptr, w2, frag);
+    hipLaunchKernelGGL(net_c2_kernel, c2_grid(d, h, w), dim3(C2_THREADS), 0, s, (const u16 *)a1, d, h, w,
+                       (const u32x4 *)frag, b2, (u16 *)a2, 1, (const u16 *)nullptr);
+    // planes per column: enough columns for two workgroups on every CU
+    const long long cols = (long long)up(w, C3X) * up(h, C3Y);
+    int zr = 32;
+    while (zr > 4 && cols * up(d, zr) < 512) zr /= 2;
+    hipLaunchKernelGGL(net_c3_kernel, dim3(up(w, C3X), up(h, C3Y), up(d, zr)), dim3(C3_THREADS), 0, s,
+                       (const u16 *)a2, x, (int)xdt, d, h, w, w3, b3, (u16 *)z, zr);
+    return net_launched("oat_net_forward");
+}
+
+int oat_net_backward(const void *x, const void *a1, const void *a2, const void *dz, int d, int h, int w,
+                     const float *w2, const float *w3, float *dw1, float *dw2, float *dw3, float *db1,
+                     float *db2, float *db3, void *workspace, size_t workspace_bytes, void *stream)
+{
+    if (!x || !a1 || !a2 || !dz || !w2 || !w3 || !dw1 || !dw2 || !dw3 || !db1 || !db2 || !db3 || !workspace)
+        return net_fail(OAT_ERR_ARG, "oat_net_backward: null pointer");
+    if (!net_size_ok(d, h, w)) return net_fail(OAT_ERR_ARG, "oat_net_backward: bad volume sizes");
+    if (!aligned16(a1) || !aligned16(a2) || !aligned16(workspace))
+        return net_fail(OAT_ERR_ARG, "oat_net_backward: buffers must be 16-byte aligned");
+    if (workspace_bytes < oat_net_workspace(d, h, w, 1))
+        return net_fail(OAT_ERR_ARG, "oat_net_backward: workspace too small");
+    const hipStream_t s = (hipStream_t)stream;
+    const size_t n = (size_t)d * h * w;
+    u32x4 *frag = (u32x4 *)workspace;
+    u16 *d2 = (u16 *)((char *)workspace + FRAG_BYTES), *d1 = d2 + 16 * n;
+    float *part = (float *)(d1 + 16 * n);
+    const int tx = (int)up(w, GX), ty = (int)up(h, GY), tiles = tx * ty * (int)up(d, GZ);
+    const int grid = std::min(tiles, G_GRID);
+    // d2 = C3^T dz through relu(a2); its 16 -> 16 fragments are those of C2^T
+    hipLaunchKernelGGL(net_c1_kernel, c1_grid(d, h, w), dim3(C1_THREADS), 0, s, dz, (int)OAT_BF16, d, h, w,
+                       w3, 1, (const float *)nullptr, d2, 0, (const u16 *)a2, w2, frag);
+    hipLaunchKernelGGL(net_wgrad1_kernel<true>, dim3(grid), dim3(G_THREADS), 0, s, (const u16 *)a2,
+                       (const u16 *)dz, d, h, w, tx, ty, tiles, part);
+    hipLaunchKernelGGL(net_c2_kernel, c2_grid(d, h, w), dim3(C2_THREADS), 0, s, (const u16 *)d2, d, h, w,
+                       (const u32x4 *)frag, (const float *)nullptr, d1, 0, (const u16 *)a1);
+    hipLaunchKernelGGL(net_wgrad16_kernel, dim3(grid), dim3(G_THREADS), 0, s, (const u16 *)a1,
+                       (const u16 *)d2, d, h, w, tx, ty, tiles, part);
+    hipLaunchKernelGGL(net_wgrad1_kernel<false>, dim3(grid), dim3(G_THREADS), 0, s, (const u16 *)d1,
+                       (const u16 *)x, d, h, w, tx, ty, tiles, part);
+    const NetGrads o{dw1, dw2, dw3, db1, db2, db3};
+    hipLaunchKernelGGL(net_wgrad_sum_kernel, dim3((NJ + 63) / 64), dim3(1024), 0, s, (const float *)part,
+                       grid, o);
+    return net_launched("oat_net_backward");
+}
+
+}  // extern "C"

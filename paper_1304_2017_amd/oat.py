@@ -34,7 +34,8 @@ EXPORTED = ("oat_plan_create", "oat_plan_create_ex", "oat_plan_destroy", "oat_pr
             "oat_sph_backproject_noalloc", "oat_plan_set_aperture",
             # include/oat_cnn.h
             "oat_conv3d_forward", "oat_conv3d_backward_weight_workspace",
-            "oat_conv3d_backward_weight", "oat_adam_step", "oat_mse_workspace", "oat_mse")
+            "oat_conv3d_backward_weight", "oat_adam_step", "oat_mse_workspace", "oat_mse",
+            "oat_net_workspace", "oat_net_forward", "oat_net_backward")
 
 
 class OatError(RuntimeError):
@@ -124,6 +125,12 @@ def lib():
         L.oat_mse_workspace.restype = sz
         L.oat_mse.argtypes = [vp, ci, vp, ci, i64, vp, vp, vp, vp]
         L.oat_mse.restype = ci
+        L.oat_net_workspace.argtypes = [ci, ci, ci, ci]
+        L.oat_net_workspace.restype = sz
+        L.oat_net_forward.argtypes = [vp, ci, ci, ci, ci] + [vp] * 10 + [sz, vp]
+        L.oat_net_forward.restype = ci
+        L.oat_net_backward.argtypes = [vp] * 4 + [ci] * 3 + [vp] * 9 + [sz, vp]
+        L.oat_net_backward.restype = ci
         _lib = L
     return _lib
 

@@ -33,6 +33,12 @@ def _ptr(t: Optional[torch.Tensor]):
     return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p()
 
 
+def _aligned(t: torch.Tensor) -> torch.Tensor:
+    """t contiguous and 16-byte aligned (itself if it is)."""
+    t = t.contiguous()
+    return t if t.data_ptr() % 16 == 0 else t.clone()
+
+
 def _stream():
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
@@ -126,8 +132,18 @@ class Preconditioner:
     def parameters(self) -> List[torch.Tensor]:
         return self.w + self.b
 
+    def _check_parameters(self):
+        shapes = [(self.CH, 1, 27), (self.CH, self.CH, 27), (1, self.CH, 27)]
+        for w, b, sh in zip(self.w, self.b, shapes):
+            if tuple(w.shape) != sh or w.dtype != torch.float32:
+                raise ValueError(f"weight must be float32 {list(sh)}, got {w.dtype} {tuple(w.shape)}")
+            if tuple(b.shape) != sh[:1] or b.dtype != torch.float32:
+                raise ValueError(f"bias must be float32 {list(sh[:1])}")
+
     def forward(self, x: torch.Tensor, keep: bool = False) -> torch.Tensor:
         """x: [D, H, W] -> z, same shape, in the storage dtype."""
+        if self.storage == torch.bfloat16:
+            return self._forward_bf16(x, keep)
         x1 = x.to(self.storage).contiguous()[None]
         a1 = conv3d(x1, self.w[0], self.b[0], relu=True)
         a2 = conv3d(a1, self.w[1], self.b[1], relu=True)
@@ -139,6 +155,8 @@ class Preconditioner:
 
     def backward(self, dz: torch.Tensor):
         """Parameter gradients for dloss/dz (the last forward had keep=True)."""
+        if self.storage == torch.bfloat16:
+            return self._backward_bf16(dz)
         x1, a1, a2 = self._cache
         d3 = dz.to(self.storage).contiguous()[None]
         dw3, db3 = conv3d_weight_grad(a2, d3)
@@ -147,6 +165,43 @@ class Preconditioner:
         d1 = conv3d(d2, flip_transpose(self.w[1]), None, mask=a1)     # through relu(a1)
         dw1, db1 = conv3d_weight_grad(x1, d1)
         return [dw1, dw2, dw3, db1, db2, db3]
+
+    def _forward_bf16(self, x: torch.Tensor, keep: bool) -> torch.Tensor:
+        """The layers in one library call; a1 and a2 are channel-last."""
+        d, h, w = x.shape
+        self._check_parameters()
+        L = oat.lib()
+        x1 = x if x.dtype == torch.float32 and not keep else x.to(self.storage)
+        x1 = x1.contiguous()
+        a1, a2 = (torch.empty((d, h, w, self.CH), device=x.device, dtype=self.storage)
+                  for _ in range(2))
+        z = torch.empty((d, h, w), device=x.device, dtype=self.storage)
+        ws = L.oat_net_workspace(d, h, w, 0)
+        work = torch.empty(max(ws, 1), device=x.device, dtype=torch.uint8)
+        par = [_aligned(t) for pair in zip(self.w, self.b) for t in pair]
+        oat._check(L.oat_net_forward(_ptr(x1), _DT[x1.dtype], d, h, w, *[_ptr(t) for t in par],
+                                     _ptr(a1), _ptr(a2), _ptr(z), _ptr(work), ws, _stream()))
+        if keep:
+            self._cache = (x1, a1, a2)
+        return z
+
+    def _backward_bf16(self, dz: torch.Tensor):
+        x1, a1, a2 = self._cache
+        d, h, w = x1.shape
+        if tuple(dz.shape) != (d, h, w):
+            raise ValueError(f"dz must have shape {(d, h, w)}, got {tuple(dz.shape)}")
+        self._check_parameters()
+        L = oat.lib()
+        dzc = dz.to(self.storage).contiguous()
+        ws = L.oat_net_workspace(d, h, w, 1)
+        work = torch.empty(max(ws, 1), device=x1.device, dtype=torch.uint8)
+        grads = [torch.empty(t.shape, device=x1.device, dtype=torch.float32)
+                 for t in self.w + self.b]
+        w2, w3 = _aligned(self.w[1]), _aligned(self.w[2])
+        oat._check(L.oat_net_backward(_ptr(x1), _ptr(a1), _ptr(a2), _ptr(dzc), d, h, w, _ptr(w2),
+                                      _ptr(w3), *[_ptr(t) for t in grads], _ptr(work), ws,
+                                      _stream()))
+        return grads
 
     def adam(self, grads, lr: float = 1e-3, b1: float = 0.9, b2: float = 0.999, eps: float = 1e-8):
         self.step += 1
