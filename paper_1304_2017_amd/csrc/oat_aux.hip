@@ -178,36 +178,48 @@ adj_gather_kernel(Problem P, const double *__restrict__ acc, int slices, void *_
 // chunks; the transducer's data (position, weight, staged window) and the
 // x/y part of the squared distance are loaded or formed once per column.
 // For each chunk the samples a tile can touch, k in [k_lo, k_lo + win), are
-// staged in LDS per transducer (zero outside [0, K)), so each update reads
-// p_k and p_{k+1} with one LDS access.  k~ is formed in FP32; when its
+// staged in LDS per transducer (zero outside [0, K)) as pairs
+// (w p_k, w (p_{k+1} - p_k)), so each update is one 8-byte LDS read and three
+// adds and multiply-adds; coordinates are in samples, so kt + tau =
+// r^2 rsqrt(r^2) needs no scaling, and kt is taken relative to the first
+// staged sample, so its floor is the LDS index.  Bound by VALU issue (14
+// instructions an update, one of them the quarter-rate rsqrt, at 1.24 a
+// CU-cycle): 12.6 ms at 256^3 / 2048 (14.5 ms with unscaled pairs and 17
+// instructions; one branch for the column's eight voxels instead of one each:
+// 12.8 ms).  k~ is formed in FP32; when its
 // fractional part lies within the FP32 error bound of an integer, floor(k~)
 // is decided exactly as the FP64 problem statement takes it (the plan's
 // threshold table), because Eq. (disfbp) switches its forward difference at
 // integer k~.
-constexpr int FBP_LDS = 8192;   // floats of staged samples per chunk
+constexpr int FBP_LDS = 4096;   // staged samples per chunk: 32 KB, four workgroups per CU
 
 template <int P_DT, int IMG_DT>
 __global__ void __launch_bounds__(FBP_TX *FBP_TY)
 fbp_kernel(Problem P, const void *__restrict__ pres, void *__restrict__ img, int win, int chunk)
 {
-    __shared__ float sp[FBP_LDS];
-    __shared__ int2 sklo[FBP_LDS / 8];    // first staged sample, 1/2 - FP64-decision tolerance
+    // per staged sample k: (w p_k, w (p_{k+1} - p_k)); per transducer: -(tau +
+    // first staged sample), 1/2 - FP64-decision tolerance
+    __shared__ float2 sp[FBP_LDS];
+    __shared__ float2 sk[FBP_LDS / 8];
+    __shared__ int sk0[FBP_LDS / 8];      // first staged sample
     const int tx = threadIdx.x % FBP_TX, ty = threadIdx.x / FBP_TX;
     const int ix = blockIdx.x * FBP_TX + tx, iy = blockIdx.y * FBP_TY + ty;
     const int iz0 = blockIdx.z * FBP_TZ;
-    const float fx = (float)ix, fy = (float)iy;
+    // positions in samples
+    const float fx = (float)ix * P.sigma, fy = (float)iy * P.sigma;
     float fz[FBP_TZ];
 #pragma unroll
-    for (int v = 0; v < FBP_TZ; ++v) fz[v] = (float)(iz0 + v);
+    for (int v = 0; v < FBP_TZ; ++v) fz[v] = (float)(iz0 + v) * P.sigma;
     // tile centre and half-diagonal (grid units)
     const float cx = blockIdx.x * FBP_TX + 0.5f * (FBP_TX - 1), cy = blockIdx.y * FBP_TY + 0.5f * (FBP_TY - 1);
     const float cz = iz0 + 0.5f * (FBP_TZ - 1);
     const float hd = fbp_half_diag();
     const int K = P.nt;
-    // With fr = kt - k and inv = 1/(kt + tau) = ri c0 dt / dx, the two
-    // coefficients of Eq. (disfbp) are (1 - fr) inv - 1/2 and fr inv + 1/2,
-    // so a transducer adds w inv (p_k + fr (p_{k+1} - p_k)) + w (p_{k+1} - p_k) / 2.
-    // acc_a sums w ri (p_k + fr dp), acc_b sums w dp; the scale is applied once.
+    // Distances in samples, kt + tau = |r_n - r_q| sigma.  With fr = kt - k and
+    // inv = 1/(kt + tau), the two coefficients of Eq. (disfbp) are
+    // (1 - fr) inv - 1/2 and fr inv + 1/2, so a transducer adds
+    // w inv (p_k + fr (p_{k+1} - p_k)) + w (p_{k+1} - p_k) / 2.
+    // acc_a sums w inv (p_k + fr dp), acc_b sums w dp; the scale is applied once.
     float acc_a[FBP_TZ], acc_b[FBP_TZ];
 #pragma unroll
     for (int v = 0; v < FBP_TZ; ++v) acc_a[v] = acc_b[v] = 0.f;
@@ -218,66 +230,67 @@ fbp_kernel(Problem P, const void *__restrict__ pres, void *__restrict__ img, int
             const DetRec &d = P.det[q0 + j];
             const float vx = cx - d.uqf[0], vy = cy - d.uqf[1], vz = cz - d.uqf[2];
             const float dc = sqrtf(vx * vx + vy * vy + vz * vz);
-            // |FP32 kt - kt| <= 5e-7 (kt + tau) + 1e-6 (transducer position
-            // rounded to FP32, the difference, the squared norm, rsqrt to
-            // 1 ulp, the product); the tolerance is twice that at the tile's
-            // largest kt.
+            const int k0 = fbp_first_sample(dc, P.sigma, P.tau);
+            // |FP32 kt - kt| <= 5e-7 (kt + tau) + 1e-6 (sigma and the
+            // transducer position in samples rounded to FP32, the difference,
+            // the squared norm, rsqrt to 1 ulp, tau + k0; an emulation over
+            // 4M voxel-transducer pairs at each workload reaches 0.75 of it);
+            // the tolerance is twice that at the tile's largest kt.
             const float tol = fmaf(1e-6f, (dc + hd + 1.f) * P.sigma, 1e-5f);
-            sklo[j] = make_int2(fbp_first_sample(dc, P.sigma, P.tau), __float_as_int(0.5f - tol));
+            sk[j] = make_float2(-(P.tau + (float)k0), 0.5f - tol);
+            sk0[j] = k0;
         }
         __syncthreads();
         for (int t = threadIdx.x; t < nq * win; t += blockDim.x) {
-            const int j = t / win, i = t % win;
-            const int k = sklo[j].x + i;
-            float v = 0.f;
-            if (k >= 0 && k < K) {
-                const size_t idx = (size_t)(q0 + j) * K + k;
-                v = P_DT == 0 ? ((const float *)pres)[idx]
-                              : __uint_as_float(((unsigned)((const unsigned short *)pres)[idx]) << 16);
-            }
-            sp[t] = v;
+            const int j = t / win, i = t - j * win;
+            const DetRec &d = P.det[q0 + j];
+            const int k = sk0[j] + i;
+            const size_t row = (size_t)(q0 + j) * K;
+            const float p0 = k >= 0 && k < K ? load_val(pres, row + k, P_DT) : 0.f;
+            const float p1 = k >= -1 && k + 1 < K ? load_val(pres, row + k + 1, P_DT) : 0.f;
+            sp[t] = make_float2(d.fbp_w * p0, d.fbp_w * (p1 - p0));
         }
         __syncthreads();
         for (int j = 0; j < nq; ++j) {
             const DetRec &d = P.det[q0 + j];
-            const float vx = fx - d.uqf[0], vy = fy - d.uqf[1];
+            const float vx = fx - d.us[0], vy = fy - d.us[1];
             const float rxy = fmaf(vy, vy, vx * vx);
-            const int2 sk = sklo[j];
-            const float *row = sp + j * win;
+            const float2 kc = sk[j];
+            const float2 *row = sp + j * win;
 #pragma unroll
             for (int v = 0; v < FBP_TZ; ++v) {
-                const float vz = fz[v] - d.uqf[2];
+                const float vz = fz[v] - d.us[2];
                 const float r2 = fmaf(vz, vz, rxy);
-                // r2 is hundreds of cells squared: the hardware rsqrt (1 ulp)
+                // r2 is hundreds of samples squared: the hardware rsqrt (1 ulp)
                 // needs no denormal scaling.
-                const float ri = __builtin_amdgcn_rsqf(r2);
-                const float kt = fmaf(r2 * ri, P.sigma, -P.tau);
+                const float inv = __builtin_amdgcn_rsqf(r2);
+                // kt relative to the first staged sample
+                const float kt = fmaf(r2, inv, kc.x);
                 float fr = __builtin_amdgcn_fractf(kt);
-                int ki = cvt_floor(kt);
+                int li = cvt_floor(kt);
                 // Within the tolerance of an integer m, floor(kt) of the FP64
                 // problem statement is m - 1 or m: decided by the FP64 squared
                 // distance in physical units (no contraction here) against the
                 // plan's threshold for m.  Outside m = -1 .. K both candidates
                 // select zero samples.
-                if (fabsf(fr - 0.5f) > __int_as_float(sk.y)) {
-                    const int m = fr > 0.5f ? ki + 1 : ki;
+                if (fabsf(fr - 0.5f) > kc.y) {
+                    const int ml = fr > 0.5f ? li + 1 : li, m = ml + sk0[j];
                     if (m >= -1 && m <= K) {
                         const double x = P.x0 + ix * P.dxd, y = P.y0 + iy * P.dxd,
                                      z = P.z0 + (iz0 + v) * P.dxd;
                         const double wx = x - d.r[0], wy = y - d.r[1], wz = z - d.r[2];
                         const double r2d = wx * wx + wy * wy + wz * wz;
-                        ki = r2d >= P.fbp_thr[m + 1] ? m : m - 1;
-                        fr = kt - (float)ki;
+                        li = r2d >= P.fbp_thr[m + 1] ? ml : ml - 1;
+                        fr = kt - (float)li;
                     }
                 }
-                // ki - sk.x lies in 0 .. win - 2 (the window spans the tile's
-                // sample range with margins; tests/host/fbp_window_check.cpp
-                // checks it over every workload geometry); the unsigned
-                // minimum only keeps the reads inside the row.
-                const unsigned li = min((unsigned)(ki - sk.x), (unsigned)(win - 2));
-                const float p0 = row[li], dp = row[li + 1] - p0;
-                acc_a[v] = fmaf(d.fbp_w * ri, fmaf(fr, dp, p0), acc_a[v]);
-                acc_b[v] = fmaf(d.fbp_w, dp, acc_b[v]);
+                // li lies in 0 .. win - 2 (the window spans the tile's sample
+                // range with margins; tests/host/fbp_window_check.cpp checks
+                // it over every workload geometry); the unsigned minimum only
+                // keeps the reads inside the row.
+                const float2 s = row[min((unsigned)li, (unsigned)(win - 2))];
+                acc_a[v] = fmaf(inv, fmaf(fr, s.y, s.x), acc_a[v]);
+                acc_b[v] += s.y;
             }
         }
     }
@@ -286,11 +299,8 @@ fbp_kernel(Problem P, const void *__restrict__ pres, void *__restrict__ img, int
         for (int v = 0; v < FBP_TZ; ++v) {
             if (iz0 + v >= P.nz) break;
             const size_t n = ((size_t)(iz0 + v) * P.ny + iy) * P.nx + ix;
-            const float val = P.fbp_scale * fmaf(P.inv_sigma, acc_a[v], 0.5f * acc_b[v]);
-            if (IMG_DT == 0)
-                ((float *)img)[n] = val;
-            else
-                ((unsigned short *)img)[n] = to_bf16(val);
+            const float val = P.fbp_scale * fmaf(0.5f, acc_b[v], acc_a[v]);
+            store_val(img, n, IMG_DT, val);
         }
     }
 }

@@ -442,6 +442,7 @@ int oat_plan_create_ex(const oat_geometry *g, int device, const oat_plan_options
             D.e1[a] = (float)e1[a];
             D.e2[a] = (float)e2[a];
             D.uqf[a] = (float)D.uq[a];
+            D.us[a] = (float)(D.uq[a] * (dx / (g->c0 * g->dt)));
         }
         D.dist = (float)(d / dx);
         double area = g->det_area ? g->det_area[q] : 4.0 * M_PI * d * d / Q;
@@ -451,6 +452,7 @@ int oat_plan_create_ex(const oat_geometry *g, int device, const oat_plan_options
         D.r[1] = r[1];
         D.r[2] = r[2];
         D.pad2 = 0.0;
+        D.pad3 = 0.f;
     }
 
     // Quadrature tables in FP64 (Appendix; bands of arc length dx from the pole).
@@ -569,7 +571,6 @@ int oat_plan_create_ex(const oat_geometry *g, int device, const oat_plan_options
     P.d_coef = (float)(g->gamma / (4.0 * M_PI * g->c0 * g->c0) / (2.0 * g->dt));
     P.fbp_scale = (float)(-1.0 / (M_PI * g->gamma * g->c0 * g->dt));
     P.sigma = (float)(dx / (g->c0 * g->dt));
-    P.inv_sigma = (float)(g->c0 * g->dt / dx);
     P.tau = (float)(g->t0 / g->dt);
     P.x0 = g->x0;
     P.y0 = g->y0;
