@@ -289,6 +289,36 @@ __device__ __forceinline__ Pt seg_point(const float Pl[3], const int dc[3], cons
     return t;
 }
 
+// A point of a segment-table entry, which the brick owns: its cell as a node
+// index of the box (base = that of the reference point's cell) and its
+// position in the cell; the FP32 operations are seg_point's.
+struct CellPt {
+    int off;
+    float fx, fy, fz;
+};
+__device__ __forceinline__ CellPt seg_cell(const float Pl[3], int base, const SegAxes &ax, float dd,
+                                           float dj)
+{
+    float cm1, sn;
+    small_rot(dj * dd, cm1, sn);
+    const float ux = fmaf(sn, ax.B[0], fmaf(cm1, ax.A[0], Pl[0]));
+    const float uy = fmaf(sn, ax.B[1], fmaf(cm1, ax.A[1], Pl[1]));
+    const float uz = fmaf(sn, ax.B[2], fmaf(cm1, ax.A[2], Pl[2]));
+    CellPt t;
+    t.off = (__mul24(cvt_floor(uz), BOX_SZ) + base) + __mul24(cvt_floor(uy), BOX_SY) + cvt_floor(ux);
+    t.fx = __builtin_amdgcn_fractf(ux);
+    t.fy = __builtin_amdgcn_fractf(uy);
+    t.fz = __builtin_amdgcn_fractf(uz);
+    return t;
+}
+
+// A point of the other paths in the same form.
+__device__ __forceinline__ CellPt cell_of(const Pt &t)
+{
+    return CellPt{(int)(__umul24((unsigned)t.cz, BOX_SZ) + (__umul24((unsigned)t.cy, BOX_SY) + (unsigned)t.cx)),
+                  t.fx, t.fy, t.fz};
+}
+
 // One window of up to 64 segments, one per lane (v2 = the lane holds one):
 // ring (rc, rs, reference table offset sref, delta, nj, segment shift ls),
 // shell k2, its weight w2 (w g' 2^s in G^T), points jb .. jb+npts-1 of
@@ -321,8 +351,9 @@ __device__ __forceinline__ void segment_points(const Problem &P, SegLds &W, Buil
     const int np = v2 ? npts : 0;
     // jb - jref in [-16, 16], npts <= 32, shell index < 4096 (n_t <= 4096)
     const int meta = (jb - jref + 64) | (np << 7) | (k2 << 13);
-    // The segment-table passes key their owned ranges by the segment's lane.
-    const int tag = SEGB ? (lane | (jb << 8)) : (rl | (ub << 8));
+    // The segment-table passes key their owned points by the segment's lane
+    // and the offset in the segment.
+    const int tag = SEGB ? (lane | ((jb - (sg << ls2)) << 8)) : (rl | (ub << 8));
     // The segment's data goes to the wave's LDS stage, where the lanes of its
     // points read it (a broadcast read; cheaper than one bpermute per value
     // on this part).  The cell offsets are stored unpacked: the point level
@@ -332,10 +363,7 @@ __device__ __forceinline__ void segment_points(const Problem &P, SegLds &W, Buil
     W.stage[lane][1] = make_float4(xa, xb, dl2, w2);
     W.stage[lane][2] = make_float4(__int_as_float(dc[0]), __int_as_float(dc[1]),
                                    __int_as_float(dc[2]), __int_as_float(tag));
-    if (SEGB) {
-        B->rmin[lane] = 0x7fffffff;
-        B->rmax[lane] = -1;
-    }
+    if (SEGB) B->rmin[lane] = 0;
     // Level 3: each lane takes two consecutive points of a segment
     // (level_begin orders the stage writes before the reads).
     level_begin<5>(L3, (np + 1) >> 1);
@@ -368,51 +396,60 @@ __device__ __forceinline__ void segment_points(const Problem &P, SegLds &W, Buil
 #pragma unroll
             for (int h = 0; h < 2; ++h)
                 if (pt[h].own) {
-                    atomicMin(&B->rmin[rlp], ur + h);
-                    atomicMax(&B->rmax[rlp], ur + h);
+                    if (SEGB) {
+                        atomicOr(&B->rmin[rlp], 1 << (ur + h));
+                    } else {
+                        atomicMin(&B->rmin[rlp], ur + h);
+                        atomicMax(&B->rmax[rlp], ur + h);
+                    }
                 }
         }
     }
     if constexpr (SEGB) {
-        // The segment's owned points span jmin .. jmax (a superset of them
-        // when the brick cuts the segment twice; the kernels test each).
+        // One entry per run of consecutive owned points (a segment has a
+        // second run when it leaves the brick and comes back): every point of
+        // an entry is owned, and the kernels do not test it again.
         wave_sync();
-        const int jmin = B->rmin[lane], jmax = B->rmax[lane];
-        const bool has = v2 && jmax >= 0;
-        const int koff = k2 - klo, cnt = jmax - jmin + 1;
-        const int off = jmin - (sg << ls2);
-        if (has && (rrel < 0 || rrel >= (1 << SEG_RING_BITS) || koff < 0 ||
-                    koff >= (1 << SEG_SHELL_BITS) || sg >= (1 << SEG_INDEX_BITS) || off < 0 ||
-                    cnt > 32))
-            atomicOr(P.seg_flag, 1);
-        const uint64_t bal = __ballot(has);
-        if (MODE == WALK_SEGCOUNT) {
-            if (has) atomicAdd(&B->hist[cnt - 1], 1);
-        } else {
-            // Entries of equal count keep walk order: per count present in
-            // this window, the lanes holding it take consecutive places
-            // after the count's earlier entries (B->hist holds each count's
-            // next place, counts in decreasing order).
-            uint64_t pend = bal;
-            while (pend) {
-                const int first = __ffsll((long long)pend) - 1;
-                const int c = __shfl(cnt, first);
-                const uint64_t m = __ballot(has && cnt == c);
-                const int base = B->hist[c - 1];
-                if (has && cnt == c) {
-                    const long long pos = P.seg_off[unit] + base + __popcll(m & mask_below());
-                    // the count pass saw the same segments; the guard only
-                    // keeps a mismatch inside the unit's range
-                    if (pos < P.seg_off[unit + 1])
-                        P.seg[pos] = seg_pack(koff, rrel, sg, off, cnt);
+        unsigned own = v2 ? (unsigned)B->rmin[lane] : 0u;
+        wave_sync();
+        const int koff = k2 - klo;
+        for (uint64_t bal = __ballot(own != 0u); bal; bal = __ballot(own != 0u)) {
+            const bool has = own != 0u;
+            const int off = has ? __ffs(own) - 1 : 0;
+            const unsigned rest = ~(own >> off);
+            const int cnt = rest ? __ffs(rest) - 1 : 32;
+            if (has && (rrel < 0 || rrel >= (1 << SEG_RING_BITS) || koff < 0 ||
+                        koff >= (1 << SEG_SHELL_BITS) || sg >= (1 << SEG_INDEX_BITS)))
+                atomicOr(P.seg_flag, 1);
+            if (MODE == WALK_SEGCOUNT) {
+                if (has) atomicAdd(&B->hist[cnt - 1], 1);
+            } else {
+                // Entries of equal count keep walk order: per count present in
+                // this window, the lanes holding it take consecutive places
+                // after the count's earlier entries (B->hist holds each count's
+                // next place, counts in decreasing order).
+                uint64_t pend = bal;
+                while (pend) {
+                    const int first = __ffsll((long long)pend) - 1;
+                    const int c = __shfl(cnt, first);
+                    const uint64_t m = __ballot(has && cnt == c);
+                    const int base = B->hist[c - 1];
+                    if (has && cnt == c) {
+                        const long long pos = P.seg_off[unit] + base + __popcll(m & mask_below());
+                        // the count pass saw the same segments; the guard only
+                        // keeps a mismatch inside the unit's range
+                        if (pos < P.seg_off[unit + 1])
+                            P.seg[pos] = seg_pack(koff, rrel, sg, off, cnt);
+                    }
+                    wave_sync();
+                    if (lane == first) B->hist[c - 1] = base + __popcll(m);
+                    wave_sync();
+                    pend &= ~m;
                 }
-                wave_sync();
-                if (lane == first) B->hist[c - 1] = base + __popcll(m);
-                wave_sync();
-                pend &= ~m;
             }
+            scount += __popcll(bal);
+            if (has) own &= ~((cnt < 32 ? (1u << cnt) - 1u : 0xffffffffu) << off);
         }
-        scount += __popcll(bal);
         wave_sync();
     }
 }
@@ -696,8 +733,8 @@ __device__ __forceinline__ int wave_max_i(int v)
 // table: one segment per lane, 64 at a time, each lane taking its segment's
 // points one after the other (a window's segments have nearly equal counts:
 // the table orders a unit's segments by decreasing count).  The positions
-// are those of walk_unit's point level (seg_ref, seg_point), so the owned
-// point set is the same.  pfn(t, w) is called for every point of a segment
+// are those of walk_unit's point level (seg_ref, seg_point), and the table
+// lists owned points only.  pfn(t, w) is called for every point of an entry
 // with its weight (w g' in G^T), then sfn(np, so, w) once per window with
 // the lane's segment count (0: none), shell offset and weight.
 template <bool ADJ, class PFn, class SFn>
@@ -762,14 +799,12 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
         float w = rr.w;
         if (ADJ && v) w = w * ((gp[(size_t)q * P.nt + klo + so] * gscale) * gscale2);
         const SegAxes ax = seg_axes(xa, xb, e1, e2);
+        const int base = dc[2] * BOX_SZ + dc[1] * BOX_SY + dc[0];
         const int nmax = wave_max_i(np);
         // dj0 + t as an FP32 counter (exact: |dj| < 2^24), one add per point
         float fdj = (float)dj0;
         for (int t = 0; t < nmax; ++t, fdj += 1.f) {
-            if (t < np) {
-                const Pt pt = seg_point(Pl, dc, ax, rr.delta, fdj, lo, hi);
-                if (pt.own) pfn(pt, w);
-            }
+            if (t < np) pfn(seg_cell(Pl, base, ax, rr.delta, fdj), w);
         }
         sfn(np, so, w);
     }
@@ -1002,16 +1037,14 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
         // FP32 images: a point in the same cell as the lane's previous point
         // reuses its corners without reading LDS (BF16 images, with half the
         // reads, are faster without the test).
-        unsigned prev = 0xffffffffu;
+        int prev = -1;
         float c8[8];   // loaded before any use: prev starts out unmatched
-        auto point = [&](const Pt &t, float) {
+        auto point = [&](const CellPt &t, float) {
             float v000, v001, v010, v011, v100, v101, v110, v111;
-            const unsigned off = __umul24((unsigned)t.cz, BOX_SZ) +
-                                 __umul24((unsigned)t.cy, BOX_SY) + t.cx;
             if constexpr (IMG_DT == 0) {
-                if (off != prev) {
-                    prev = off;
-                    const float *pb = box + off;
+                if (t.off != prev) {
+                    prev = t.off;
+                    const float *pb = box + t.off;
                     const float *pz = pb + BOX_SZ;
                     c8[0] = pb[0], c8[1] = pb[1], c8[2] = pb[BOX_SY], c8[3] = pb[BOX_SY + 1];
                     c8[4] = pz[0], c8[5] = pz[1], c8[6] = pz[BOX_SY], c8[7] = pz[BOX_SY + 1];
@@ -1019,7 +1052,7 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
                 v000 = c8[0], v001 = c8[1], v010 = c8[2], v011 = c8[3];
                 v100 = c8[4], v101 = c8[5], v110 = c8[6], v111 = c8[7];
             } else {
-                const unsigned *pb = reinterpret_cast<const unsigned *>(box) + off;
+                const unsigned *pb = reinterpret_cast<const unsigned *>(box) + t.off;
                 const unsigned *pz = pb + BOX_SZ;
                 const unsigned w00 = pb[0], w01 = pb[BOX_SY], w10 = pz[0], w11 = pz[BOX_SY];
                 v000 = __uint_as_float(w00 << 16), v001 = __uint_as_float(w00 & 0xffff0000u);
@@ -1044,7 +1077,7 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
                                                         __double_as_longlong(0x1.8p52)));
             }
             racc = 0.f;
-            prev = 0xffffffffu;
+            prev = -1;
         };
         walk_seg<false>(P, q, (size_t)b * P.nq + q, lo, hi, gbase, nullptr, 1.f, 1.f, SPLIT ? pt : 0,
                         SPLIT ? parts : 1, klo, point, segment);
@@ -1229,9 +1262,8 @@ srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc
             const int q = qperm[i];
             int klo = 0;
             if (CALIB) {
-                auto scatter1 = [&](const Pt &t, float wv) {
-                    unsigned long long *pb = box + __umul24((unsigned)t.cz, BOX_SZ) +
-                                             __umul24((unsigned)t.cy, BOX_SY) + t.cx;
+                auto scatter1 = [&](const CellPt &t, float wv) {
+                    unsigned long long *pb = box + t.off;
                     unsigned long long *pz = pb + BOX_SZ;
                     const float gx = 1.f - t.fx, gy = 1.f - t.fy, gz = 1.f - t.fz;
                     const float w00 = gy * gz * wv, w01 = t.fy * gz * wv, w10 = gy * t.fz * wv,
@@ -1249,26 +1281,22 @@ srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc
                     add(pz + BOX_SY + 1, t.fx * w11);
                 };
                 if constexpr (TM == TM_SEG) {
-                    auto point = [&](const Pt &t, float wv) { scatter1(t, (wv * g1) * g2); };
+                    auto point = [&](const CellPt &t, float wv) { scatter1(t, (wv * g1) * g2); };
                     auto segment = [](int, int, float) {};
                     walk_seg<false>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, nullptr, 1.f,
                                     1.f, pt, parts, klo, point, segment);
                 } else {
                     auto scatter = [&](const Pt &a, const Pt &c, float wv, int, int) {
-                        if (a.own) scatter1(a, (wv * g1) * g2);
-                        if (c.own) scatter1(c, (wv * g1) * g2);
+                        if (a.own) scatter1(cell_of(a), (wv * g1) * g2);
+                        if (c.own) scatter1(cell_of(c), (wv * g1) * g2);
                     };
                     walk_unit<false, TM, WALK_POINTS>(P, q, (size_t)b * P.nq + q, lo, hi, W,
                                                        nullptr, nullptr, 1.f, 1.f, klo, scatter);
                 }
             } else {
-                auto scatter1 = [&](const Pt &t, float wv) {
-                    // word index, then bytes (one multiply-add fewer than
-                    // scaling each term)
-                    const unsigned wi = __umul24((unsigned)t.cz, BOX_SZ) +
-                                        (__umul24((unsigned)t.cy, BOX_SY) + (unsigned)t.cx);
+                auto scatter1 = [&](const CellPt &t, float wv) {
                     unsigned long long *pb = reinterpret_cast<unsigned long long *>(
-                        reinterpret_cast<char *>(box) + (wi << 3));
+                        reinterpret_cast<char *>(box) + (t.off << 3));
                     unsigned long long *pz = pb + BOX_SZ;
                     // trilinear corner weights, (1 - f) v formed as v - f v
                     const float a = fmaf(-t.fz, wv, wv), c = t.fz * wv;
@@ -1288,14 +1316,14 @@ srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc
                     add2(pz + BOX_SY, w11);
                 };
                 if constexpr (TM == TM_SEG) {
-                    auto point = [&](const Pt &t, float wv) { scatter1(t, wv); };
+                    auto point = [&](const CellPt &t, float wv) { scatter1(t, wv); };
                     auto segment = [](int, int, float) {};
                     walk_seg<true>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, gp, g1, g2, pt,
                                    parts, klo, point, segment);
                 } else {
                     auto scatter = [&](const Pt &a, const Pt &c, float wv, int, int) {
-                        if (a.own) scatter1(a, wv);
-                        if (c.own) scatter1(c, wv);
+                        if (a.own) scatter1(cell_of(a), wv);
+                        if (c.own) scatter1(cell_of(c), wv);
                     };
                     walk_unit<true, TM, WALK_POINTS>(P, q, (size_t)b * P.nq + q, lo, hi, W,
                                                       nullptr, gp, g1, g2, klo, scatter);

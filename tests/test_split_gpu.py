@@ -1,6 +1,7 @@
 """Small grids, where G and G^T split their units over workgroups and waves: slices of one
 transducer, slices that do not divide the transducers or the windows of 128, units with fewer
-segments than parts, one-cell bricks.  Against the FP64 oracle at the gates of the other parity
+segments than parts, one-cell bricks, and transducers so near that ring segments leave a brick and
+come back (two table entries).  Against the FP64 oracle at the gates of the other parity
 tests (1e-5 in FP32, 5e-7 for G alone; 2e-3 and half a BF16 unit for BF16 storage), and bit for
 bit over the table paths for G^T."""
 import math
@@ -22,12 +23,14 @@ def _geometry(nx, ny, nz, q, dx=0.5, rs=25.0):
                           np.full(q, 4 * math.pi * rs * rs / q))
 
 
-@pytest.mark.parametrize("shape,q", [((20, 20, 20), 1), ((1, 2, 3), 3), ((21, 20, 41), 37),
-                                     ((32, 19, 40), 129), ((40, 21, 20), 300)])
-def test_small_grids_split_units(shape, q):
+@pytest.mark.parametrize("shape,q,rs", [((20, 20, 20), 1, 25.0), ((1, 2, 3), 3, 25.0),
+                                        ((21, 20, 41), 37, 25.0), ((32, 19, 40), 129, 25.0),
+                                        ((40, 21, 20), 300, 25.0), ((38, 20, 20), 24, 12.6),
+                                        ((20, 20, 20), 40, 9.2)])
+def test_small_grids_split_units(shape, q, rs):
     import torch
     from paper_1304_2017_amd.oat import Plan
-    geom = _geometry(*shape, q)
+    geom = _geometry(*shape, q, rs=rs)
     gd = geom.as_dict()
     rng = np.random.default_rng(q)
     img = rng.normal(size=geom.shape).astype(np.float32)
