@@ -256,7 +256,7 @@ struct Problem {
     // Every listed point is owned, so the kernels neither test it nor form
     // its cell per axis (BF16 G at 128 x 105 x 117 / 1024: 3.50 -> 3.32 ms;
     // at 256^3 / 2048, where the LDS binds, G 67.9 -> 67.5 and G^T 92.5 ->
-    // 91.8 ms).
+    // 90.8 ms).
     // A unit's entries are ordered by decreasing count (walk
     // order within a count), so a window of 64 has nearly equal counts.
     // Written by two passes of the bounds walk: seg_cnt[u] and
