@@ -11,9 +11,12 @@ namespace oat {
 // its (BRICK+2)^3 nodes in LDS.
 constexpr int BRICK = 20;
 constexpr int BOX = BRICK + 2;                // LDS nodes per axis
-constexpr int BOX_SY = BOX + 2;               // LDS row pitch (dwords)
-constexpr int BOX_SZ = BOX_SY * BOX + 38;     // LDS slice pitch (dwords); pitches chosen
-                                              // to spread arcs of any direction over banks
+// LDS row and slice pitches in words (4 or 8 bytes): odd, so that neither a row
+// nor a slice step keeps to few banks.  G^T at 256^3 / 2048: 87.3 ms; 24 and
+// 566: 90.8, 25 and 551: 88.7, 22 and 490: 89.8; other slice pitches with 23,
+// 510 to 538: 87.3 to 87.7.
+constexpr int BOX_SY = BOX + 1;
+constexpr int BOX_SZ = BOX_SY * BOX + 1;
 constexpr int BOX_WORDS = BOX_SZ * BOX;
 constexpr int BOX3 = BOX * BOX * BOX;          // dense box in HBM (G^T brick output)
 constexpr int WAVES = 8;                      // waves per workgroup (srt kernels)
