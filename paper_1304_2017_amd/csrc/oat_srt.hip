@@ -317,7 +317,8 @@ __device__ __forceinline__ CellPt seg_cell(const float Pl[3], int base, const Se
     const float uy = fmaf(sn, ax.B[1], fmaf(cm1, ax.A[1], Pl[1]));
     const float uz = fmaf(sn, ax.B[2], fmaf(cm1, ax.A[2], Pl[2]));
     CellPt t;
-    t.off = mad24(cvt_floor(uz), BOX_SZ * ELT, mad24(cvt_floor(uy), BOX_SY * ELT, mad24(cvt_floor(ux), ELT, base)));
+    t.off = mad24(cvt_floor(uz), BOX_SZ * ELT,
+                  mad24(cvt_floor(uy), BOX_SY * ELT, mad24(cvt_floor(ux), ELT, base)));
     t.fx = __builtin_amdgcn_fractf(ux);
     t.fy = __builtin_amdgcn_fractf(uy);
     t.fz = __builtin_amdgcn_fractf(uz);
@@ -749,6 +750,9 @@ __device__ __forceinline__ int wave_max_i(int v)
     return __builtin_amdgcn_readfirstlane(v);
 }
 
+// Minimum over the 64 lanes (all active), returned to every lane.
+__device__ __forceinline__ int wave_min_i(int v) { return -wave_max_i(-v); }
+
 // Walk the points of transducer q owned by the brick from the plan's segment
 // table: one segment per lane, 64 at a time, each lane taking its segment's
 // points one after the other (a window's segments have nearly equal counts:
@@ -756,8 +760,9 @@ __device__ __forceinline__ int wave_max_i(int v)
 // are those of walk_unit's point level (seg_ref, seg_point), and the table
 // lists owned points only.  pfn(t, w) is called for every point of an entry
 // with its weight (w g' in G^T), then sfn(np, so, w) once per window with
-// the lane's segment count (0: none), shell offset and weight.
-template <bool ADJ, int ELT, class PFn, class SFn>
+// the lane's segment count (0: none), shell offset and weight.  PAIRS: the
+// points that every lane has are taken two at a time, without a lane mask.
+template <bool ADJ, int ELT, bool PAIRS, class PFn, class SFn>
 __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, const int lo[3],
                                          const int hi[3], int *gbase, const float *gp,
                                          float gscale, float gscale2, int part, int parts,
@@ -823,7 +828,17 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
         const int nmax = wave_max_i(np);
         // dj0 + t as an FP32 counter (exact: |dj| < 2^24), one add per point
         float fdj = (float)dj0;
-        for (int t = 0; t < nmax; ++t, fdj += 1.f) {
+        int t = 0;
+        if (PAIRS) {
+            const int npair = wave_min_i(np) & ~1;
+            for (; t < npair; t += 2, fdj += 2.f) {
+                const CellPt a = seg_cell<ELT>(Pl, base, ax, rr.delta, fdj);
+                const CellPt c = seg_cell<ELT>(Pl, base, ax, rr.delta, fdj + 1.f);
+                pfn(a, w);
+                pfn(c, w);
+            }
+        }
+        for (; t < nmax; ++t, fdj += 1.f) {
             if (t < np) pfn(seg_cell<ELT>(Pl, base, ax, rr.delta, fdj), w);
         }
         sfn(np, so, w);
@@ -926,20 +941,36 @@ srt_fwd_kernel(Problem P, const void *__restrict__ img, float *__restrict__ part
 }
 
 // G on the segment table: one segment per lane (walk_seg), FWD_SEG_WAVES
-// waves per workgroup and two workgroups per CU (at most 64 VGPRs, the LDS
-// of two boxes).  Per wave, dynamic LDS holds the unit's first candidate
+// waves per workgroup.  Per wave, dynamic LDS holds the unit's first candidate
 // ring per shell (window ints) and its fixed-point shell sums (window
 // 64-bit integers).  SPLIT: the waves share units (seg_fwd_grid, parts > 0),
 // and the shell sums are per transducer of the slice.
+//
+// A point's 8 corners come from the LDS box, whose reads and the VALU are both
+// near their limits.  FP32 images on whole units: the box holds per node the
+// pair (v[x], v[x + 1] - v[x]), 8 bytes, so that a point is 4 aligned 64-bit
+// reads (8 cycles a wave at random addresses, against 15 for the two-dword
+// read of v[x] and v[x + 1]) and the x interpolation one FMA; one workgroup
+// a CU, which leaves the registers to work on two points at once.  256^3 /
+// 2048: 67.2 -> 60.4 ms (61.6 without the second point).
+// Elsewhere 4-byte words and two workgroups a CU (at most 64 VGPRs): on split
+// units, where one workgroup's staging and last units run under the other's
+// work (96^3 / 512 FP32: 1.14 ms, 1.22 with pairs), and for BF16 images, whose
+// word holds the two nodes as they are (200 x 211 x 180 / 1100: 15.3 ms, 15.9
+// with pairs).
 constexpr int FWD_SEG_WAVES = 16;
+constexpr bool fwd_seg_pairs(int img_dt, bool split) { return img_dt == 0 && !split; }
+constexpr int fwd_seg_eu(int img_dt, bool split) { return fwd_seg_pairs(img_dt, split) ? 4 : 8; }
 
 template <int IMG_DT, bool SPLIT>
-__global__ void __launch_bounds__(FWD_SEG_WAVES *WAVE) __attribute__((amdgpu_waves_per_eu(8, 8)))
+__global__ void __launch_bounds__(FWD_SEG_WAVES *WAVE)
+__attribute__((amdgpu_waves_per_eu(fwd_seg_eu(IMG_DT, SPLIT), fwd_seg_eu(IMG_DT, SPLIT))))
 srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ part,
                    int *__restrict__ klo_out, int q_per_slice, int parts)
 {
     constexpr int NW = FWD_SEG_WAVES;
-    __shared__ float box[BOX_WORDS];
+    constexpr bool PB = fwd_seg_pairs(IMG_DT, SPLIT);
+    __shared__ __align__(8) float box[BOX_WORDS * (PB ? 2 : 1)];
     __shared__ int q_next;
     __shared__ float wmax[NW];
     __shared__ int wbad[NW];
@@ -971,9 +1002,17 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
         amax = fmaxf(amax, a);
         return v;
     };
-    // FP32 images: one node per word.  BF16 images: word x holds the BF16
-    // pair (node x, node x + 1), so a point's 8 corners are 4 words (2 reads).
-    if constexpr (IMG_DT == 0) {
+    // Pairs: (node x, node x + 1 - node x).  FP32 images otherwise: one node
+    // per word.  BF16 images: word x holds the BF16 pair (node x, node x + 1),
+    // so a point's 8 corners are 4 words (2 reads).
+    if constexpr (PB) {
+        float2 *bw = reinterpret_cast<float2 *>(box);
+        for (int t = threadIdx.x; t < (BOX - 1) * BOX * BOX; t += blockDim.x) {
+            const int x = t % (BOX - 1), y = (t / (BOX - 1)) % BOX, z = t / ((BOX - 1) * BOX);
+            const float v = node(x, y, z);
+            bw[z * BOX_SZ + y * BOX_SY + x] = make_float2(v, node(x + 1, y, z) - v);
+        }
+    } else if constexpr (IMG_DT == 0) {
         for (int t = threadIdx.x; t < BOX * BOX * BOX; t += blockDim.x) {
             const int x = t % BOX, y = (t / BOX) % BOX, z = t / (BOX * BOX);
             box[z * BOX_SZ + y * BOX_SY + x] = node(x, y, z);
@@ -1054,14 +1093,30 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
         wave_sync();
         int klo = 0;
         float racc = 0.f;
-        // FP32 images: a point in the same cell as the lane's previous point
+        // FP32 nodes: a point in the same cell as the lane's previous point
         // reuses its corners without reading LDS (BF16 images, with half the
         // reads, are faster without the test).
         int prev = -1;
         float c8[8];   // loaded before any use: prev starts out unmatched
         auto point = [&](const CellPt &t, float) {
             float v000, v001, v010, v011, v100, v101, v110, v111;
-            if constexpr (IMG_DT == 0) {
+            if constexpr (PB) {
+                const float2 *pb = box_at(reinterpret_cast<float2 *>(box), t.off);
+                const float2 *pz = pb + BOX_SZ;
+                // (atomic loads so that two are not merged into one
+                // ds_read2_b64, which takes 26 cycles a wave, not 2 x 8)
+                auto ld = [](const float2 *p) {
+                    return __builtin_bit_cast(
+                        float2, __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p),
+                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT));
+                };
+                const float2 q00 = ld(pb), q01 = ld(pb + BOX_SY), q10 = ld(pz), q11 = ld(pz + BOX_SY);
+                const float c00 = fmaf(t.fx, q00.y, q00.x), c01 = fmaf(t.fx, q01.y, q01.x);
+                const float c10 = fmaf(t.fx, q10.y, q10.x), c11 = fmaf(t.fx, q11.y, q11.x);
+                const float c0 = fmaf(t.fy, c01 - c00, c00), c1 = fmaf(t.fy, c11 - c10, c10);
+                racc += fmaf(t.fz, c1 - c0, c0);
+                return;
+            } else if constexpr (IMG_DT == 0) {
                 if (t.off != prev) {
                     prev = t.off;
                     // (the plane above from a register of its own: the reads'
@@ -1104,8 +1159,9 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
             racc = 0.f;
             prev = -1;
         };
-        walk_seg<false, 4>(P, q, (size_t)b * P.nq + q, lo, hi, gbase, nullptr, 1.f, 1.f, SPLIT ? pt : 0,
-                        SPLIT ? parts : 1, klo, point, segment);
+        walk_seg<false, PB ? 8 : 4, PB>(P, q, (size_t)b * P.nq + q, lo, hi, gbase, nullptr, 1.f,
+                                        1.f, SPLIT ? pt : 0, SPLIT ? parts : 1, klo, point,
+                                        segment);
         wave_sync();
         if (SPLIT) {
             if (lane == 0) klo_s[q - qb] = klo;   // the same value from each part
@@ -1308,8 +1364,8 @@ srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc
                 if constexpr (TM == TM_SEG) {
                     auto point = [&](const CellPt &t, float wv) { scatter1(t, (wv * g1) * g2); };
                     auto segment = [](int, int, float) {};
-                    walk_seg<false, 8>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, nullptr, 1.f,
-                                    1.f, pt, parts, klo, point, segment);
+                    walk_seg<false, 8, false>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, nullptr,
+                                              1.f, 1.f, pt, parts, klo, point, segment);
                 } else {
                     auto scatter = [&](const Pt &a, const Pt &c, float wv, int, int) {
                         if (a.own) scatter1(cell_of<8>(a), (wv * g1) * g2);
@@ -1342,8 +1398,8 @@ srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc
                 if constexpr (TM == TM_SEG) {
                     auto point = [&](const CellPt &t, float wv) { scatter1(t, wv); };
                     auto segment = [](int, int, float) {};
-                    walk_seg<true, 8>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, gp, g1, g2, pt,
-                                   parts, klo, point, segment);
+                    walk_seg<true, 8, false>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, gp, g1, g2,
+                                             pt, parts, klo, point, segment);
                 } else {
                     auto scatter = [&](const Pt &a, const Pt &c, float wv, int, int) {
                         if (a.own) scatter1(cell_of<8>(a), wv);

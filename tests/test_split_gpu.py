@@ -53,3 +53,24 @@ def test_small_grids_split_units(shape, q, rs):
         assert torch.equal(other.backproject(yd), a)
         other.close()
     plan.close()
+
+
+@pytest.mark.parametrize("shape,q", [((181, 200, 163), 320), ((301, 182, 161), 259)])
+def test_whole_units_on_node_pairs(shape, q):
+    """Grids of whole units, where an FP32 image is read as node pairs and two points at a time: G
+    against the table-free walk, each within 5e-7 of the oracle, so 1e-6 apart; edge bricks are
+    partly filled and the runs of points even and odd."""
+    import torch
+    from paper_1304_2017_amd.oat import Plan
+    geom = _geometry(*shape, q, dx=0.1, rs=25.0)
+    rng = np.random.default_rng(q)
+    x = torch.from_numpy(rng.normal(size=geom.shape).astype(np.float32)).cuda()
+    plan = Plan(geom, 0)
+    assert plan.stats()["segment_table_entries"] > 0
+    g = plan.project(x, srt_only=True)
+    assert torch.equal(plan.project(x, srt_only=True), g)
+    plan.close()
+    plain = Plan(geom, 0, segment_table=0, arc_table=0)
+    check(f"G {shape}/{q}", g.cpu().numpy(),
+          plain.project(x, srt_only=True).double().cpu().numpy(), 1e-6)
+    plain.close()
