@@ -175,54 +175,62 @@ adj_gather_kernel(Problem P, const double *__restrict__ acc, int slices, void *_
 
 // FBP, Eq. (disfbp): a block takes a 16 x 16 x 8 tile of voxels, each thread
 // a column of FBP_TZ = 8 voxels along z, and loops over the transducers in
-// chunks; the transducer's data (position, weight, staged window) and the
-// x/y part of the squared distance are loaded or formed once per column.
+// chunks.  Distances are in samples (kt + tau = |r_n - r_q| sigma = r^2
+// rsqrt(r^2)), positions relative to the tile's centre, where their FP32 forms
+// lose least; a column forms the x/y part of the squared distance, and the z
+// parts, the same for every column of the tile, come from LDS.
 // For each chunk the samples a tile can touch, k in [k_lo, k_lo + win), are
 // staged in LDS per transducer (zero outside [0, K)) as pairs
-// (w p_k, w (p_{k+1} - p_k)), so each update is one 8-byte LDS read and three
-// adds and multiply-adds; coordinates are in samples, so kt + tau =
-// r^2 rsqrt(r^2) needs no scaling, and kt is taken relative to the first
-// staged sample, so its floor is the LDS index.  Bound by VALU issue (14
-// instructions an update, one of them the quarter-rate rsqrt, at 1.24 a
-// CU-cycle): 12.6 ms at 256^3 / 2048 (14.5 ms with unscaled pairs and 17
-// instructions; one branch for the column's eight voxels instead of one each:
-// 12.8 ms).  k~ is formed in FP32; when its
-// fractional part lies within the FP32 error bound of an integer, floor(k~)
-// is decided exactly as the FP64 problem statement takes it (the plan's
-// threshold table), because Eq. (disfbp) switches its forward difference at
-// integer k~.
-constexpr int FBP_LDS = 4096;   // staged samples per chunk: 32 KB, four workgroups per CU
+// (w p_k - tol w dp, w dp), dp = p_{k+1} - p_k, so each update is one 8-byte
+// LDS read and three adds and multiply-adds; kt is taken relative to the first
+// staged sample, so its floor is the LDS index.
+//
+// k~ is formed in FP32; when it lies within its error bound tol of an integer,
+// floor(k~) is decided exactly as the FP64 problem statement takes it (the
+// plan's threshold table), because Eq. (disfbp) switches its forward difference
+// at integer k~.  With e = 2^-24, R = kt + tau and h the tile's half-diagonal
+// in samples: positions 2 e (R + h), squares and sums 1.5 e R, rsqrt (1 ulp)
+// 2 e R, the rounded offset e R, the last rounding e win.  kt carries + tol, so
+// that "within tol of an integer" is one comparison of its fraction.
+//
+// Bound by VALU issue: 11 instructions an update, one of them the quarter-rate
+// rsqrt, and the FP64 decisions (6% of the wave updates): 11.1 ms at 256^3 /
+// 2048.  With positions about the grid's origin, whose looser bound sent 15% to
+// FP64, 13 instructions an update and a division a staged sample: 12.6 ms; one
+// branch for the column's eight voxels instead of one each: slower.
+constexpr int FBP_LDS = 4096;     // staged samples per chunk (32 KB) and
+constexpr int FBP_CHUNK = 128;    // transducers: 39 KB, four workgroups per CU
 
 template <int P_DT, int IMG_DT>
 __global__ void __launch_bounds__(FBP_TX *FBP_TY)
 fbp_kernel(Problem P, const void *__restrict__ pres, void *__restrict__ img, int win, int chunk)
 {
-    // per staged sample k: (w p_k, w (p_{k+1} - p_k)); per transducer: -(tau +
-    // first staged sample), 1/2 - FP64-decision tolerance
     __shared__ float2 sp[FBP_LDS];
-    __shared__ float2 sk[FBP_LDS / 8];
-    __shared__ int sk0[FBP_LDS / 8];      // first staged sample
+    // per transducer: x and y relative to the tile's centre, tol - (tau + first
+    // staged sample), 2 tol; the squared z distances of the tile's planes; the
+    // first staged sample and the bits of w
+    __shared__ float4 sq[FBP_CHUNK];
+    __shared__ float4 sz[FBP_CHUNK][FBP_TZ / 4];
+    __shared__ int2 skw[FBP_CHUNK];
+    static_assert(FBP_TZ % 4 == 0, "planes in fours");
     const int tx = threadIdx.x % FBP_TX, ty = threadIdx.x / FBP_TX;
     const int ix = blockIdx.x * FBP_TX + tx, iy = blockIdx.y * FBP_TY + ty;
     const int iz0 = blockIdx.z * FBP_TZ;
-    // positions in samples
-    const float fx = (float)ix * P.sigma, fy = (float)iy * P.sigma;
-    float fz[FBP_TZ];
-#pragma unroll
-    for (int v = 0; v < FBP_TZ; ++v) fz[v] = (float)(iz0 + v) * P.sigma;
     // tile centre and half-diagonal (grid units)
     const float cx = blockIdx.x * FBP_TX + 0.5f * (FBP_TX - 1), cy = blockIdx.y * FBP_TY + 0.5f * (FBP_TY - 1);
     const float cz = iz0 + 0.5f * (FBP_TZ - 1);
     const float hd = fbp_half_diag();
+    const double sg = P.dxd / (P.c0d * P.dtd);
+    const float fx = (float)((tx - 0.5 * (FBP_TX - 1)) * sg), fy = (float)((ty - 0.5 * (FBP_TY - 1)) * sg);
     const int K = P.nt;
-    // Distances in samples, kt + tau = |r_n - r_q| sigma.  With fr = kt - k and
-    // inv = 1/(kt + tau), the two coefficients of Eq. (disfbp) are
-    // (1 - fr) inv - 1/2 and fr inv + 1/2, so a transducer adds
-    // w inv (p_k + fr (p_{k+1} - p_k)) + w (p_{k+1} - p_k) / 2.
+    // With fr = kt - k and inv = 1/(kt + tau), the two coefficients of Eq.
+    // (disfbp) are (1 - fr) inv - 1/2 and fr inv + 1/2, so a transducer adds
+    // w inv (p_k + fr dp) + w dp / 2.
     // acc_a sums w inv (p_k + fr dp), acc_b sums w dp; the scale is applied once.
     float acc_a[FBP_TZ], acc_b[FBP_TZ];
 #pragma unroll
     for (int v = 0; v < FBP_TZ; ++v) acc_a[v] = acc_b[v] = 0.f;
+    const int j_step = (FBP_TX * FBP_TY) / win, i_step = FBP_TX * FBP_TY - j_step * win;
     for (int q0 = 0; q0 < P.nq; q0 += chunk) {
         const int nq = min(chunk, P.nq - q0);
         __syncthreads();
@@ -231,57 +239,74 @@ fbp_kernel(Problem P, const void *__restrict__ pres, void *__restrict__ img, int
             const float vx = cx - d.uqf[0], vy = cy - d.uqf[1], vz = cz - d.uqf[2];
             const float dc = sqrtf(vx * vx + vy * vy + vz * vz);
             const int k0 = fbp_first_sample(dc, P.sigma, P.tau);
-            // |FP32 kt - kt| <= 5e-7 (kt + tau) + 1e-6 (sigma and the
-            // transducer position in samples rounded to FP32, the difference,
-            // the squared norm, rsqrt to 1 ulp, tau + k0; an emulation over
-            // 4M voxel-transducer pairs at each workload reaches 0.75 of it);
-            // the tolerance is twice that at the tile's largest kt.
-            const float tol = fmaf(1e-6f, (dc + hd + 1.f) * P.sigma, 1e-5f);
-            sk[j] = make_float2(-(P.tau + (float)k0), 0.5f - tol);
-            sk0[j] = k0;
+            // the bound above (6.5 e R, taken as 4e-7 R) at the tile's largest R
+            const float tol = fmaf(4e-7f, (dc + hd + 1.f) * P.sigma, 6.2e-8f * (2.f * hd * P.sigma + (float)win));
+            sq[j] = make_float4((float)((d.uq[0] - (double)cx) * sg), (float)((d.uq[1] - (double)cy) * sg),
+                                (float)((double)tol - (P.t0d / P.dtd + (double)k0)), 2.f * tol);
+            float z2[FBP_TZ];
+#pragma unroll
+            for (int v = 0; v < FBP_TZ; ++v) {
+                const double z = ((double)(iz0 + v) - d.uq[2]) * sg;
+                z2[v] = (float)(z * z);
+            }
+#pragma unroll
+            for (int v = 0; v < FBP_TZ; v += 4)
+                sz[j][v / 4] = make_float4(z2[v], z2[v + 1], z2[v + 2], z2[v + 3]);
+            skw[j] = make_int2(k0, __float_as_int(d.fbp_w));
         }
         __syncthreads();
-        for (int t = threadIdx.x; t < nq * win; t += blockDim.x) {
-            const int j = t / win, i = t - j * win;
-            const DetRec &d = P.det[q0 + j];
-            const int k = sk0[j] + i;
+        for (int t = threadIdx.x, j = t / win, i = t - j * win; t < nq * win; t += FBP_TX * FBP_TY) {
+            const int2 kw = skw[j];
+            const int k = kw.x + i;
+            const float w = __int_as_float(kw.y);
             const size_t row = (size_t)(q0 + j) * K;
             const float p0 = k >= 0 && k < K ? load_val(pres, row + k, P_DT) : 0.f;
             const float p1 = k >= -1 && k + 1 < K ? load_val(pres, row + k + 1, P_DT) : 0.f;
-            sp[t] = make_float2(d.fbp_w * p0, d.fbp_w * (p1 - p0));
+            const float dp = w * (p1 - p0), shift = 0.5f * sq[j].w * dp;
+            // (a non-finite difference stays out of the sample itself)
+            sp[t] = make_float2(fmaf(w, p0, fabsf(dp) <= 3.4028235e38f ? -shift : 0.f), dp);
+            j += j_step, i += i_step;
+            if (i >= win) i -= win, ++j;
         }
         __syncthreads();
         for (int j = 0; j < nq; ++j) {
-            const DetRec &d = P.det[q0 + j];
-            const float vx = fx - d.us[0], vy = fy - d.us[1];
+            const float4 kc = sq[j];
+            float z2[FBP_TZ];
+#pragma unroll
+            for (int v = 0; v < FBP_TZ; v += 4) {
+                const float4 z = sz[j][v / 4];
+                z2[v] = z.x, z2[v + 1] = z.y, z2[v + 2] = z.z, z2[v + 3] = z.w;
+            }
+            const float vx = fx - kc.x, vy = fy - kc.y;
             const float rxy = fmaf(vy, vy, vx * vx);
-            const float2 kc = sk[j];
             const float2 *row = sp + j * win;
 #pragma unroll
             for (int v = 0; v < FBP_TZ; ++v) {
-                const float vz = fz[v] - d.us[2];
-                const float r2 = fmaf(vz, vz, rxy);
+                const float r2 = rxy + z2[v];
                 // r2 is hundreds of samples squared: the hardware rsqrt (1 ulp)
                 // needs no denormal scaling.
                 const float inv = __builtin_amdgcn_rsqf(r2);
-                // kt relative to the first staged sample
-                const float kt = fmaf(r2, inv, kc.x);
+                // kt + tol relative to the first staged sample
+                const float kt = fmaf(r2, inv, kc.z);
                 float fr = __builtin_amdgcn_fractf(kt);
                 int li = cvt_floor(kt);
-                // Within the tolerance of an integer m, floor(kt) of the FP64
-                // problem statement is m - 1 or m: decided by the FP64 squared
-                // distance in physical units (no contraction here) against the
-                // plan's threshold for m.  Outside m = -1 .. K both candidates
-                // select zero samples.
-                if (fabsf(fr - 0.5f) > kc.y) {
-                    const int ml = fr > 0.5f ? li + 1 : li, m = ml + sk0[j];
+                // Within tol of an integer m, floor(kt) of the FP64 problem
+                // statement is m - 1 or m: decided by the FP64 squared distance
+                // in physical units (no contraction here) against the plan's
+                // threshold for m.  Outside m = -1 .. K both candidates select
+                // zero samples.
+                if (fr < kc.w) {
+                    const int m = li + skw[j].x;
                     if (m >= -1 && m <= K) {
+                        const DetRec &d = P.det[q0 + j];
                         const double x = P.x0 + ix * P.dxd, y = P.y0 + iy * P.dxd,
                                      z = P.z0 + (iz0 + v) * P.dxd;
                         const double wx = x - d.r[0], wy = y - d.r[1], wz = z - d.r[2];
                         const double r2d = wx * wx + wy * wy + wz * wz;
-                        li = r2d >= P.fbp_thr[m + 1] ? ml : ml - 1;
-                        fr = kt - (float)li;
+                        if (!(r2d >= P.fbp_thr[m + 1])) {
+                            li -= 1;
+                            fr += 1.f;
+                        }
                     }
                 }
                 // li lies in 0 .. win - 2 (the window spans the tile's sample
@@ -339,7 +364,7 @@ hipError_t launch_fbp(const Problem &P, const void *p, int p_dtype, void *img, i
     // Samples a tile can touch per transducer: its diagonal in shells plus margins.
     const int win = fbp_window(P.sigma);
     int chunk = FBP_LDS / win;
-    if (chunk > FBP_LDS / 8) chunk = FBP_LDS / 8;
+    if (chunk > FBP_CHUNK) chunk = FBP_CHUNK;
     if (chunk < 1) return hipErrorInvalidValue;
     dim3 grid((P.nx + FBP_TX - 1) / FBP_TX, (P.ny + FBP_TY - 1) / FBP_TY, (P.nz + FBP_TZ - 1) / FBP_TZ);
     dim3 block(FBP_TX * FBP_TY);

@@ -156,7 +156,6 @@ struct alignas(16) DetRec {
     float pad;
     double r[3];       // transducer position in mm
     double pad2;
-    float us[3];       // transducer position in samples (uq sigma), rounded to FP32
     float pad3;
 };
 

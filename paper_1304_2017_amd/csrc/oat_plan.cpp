@@ -442,7 +442,6 @@ int oat_plan_create_ex(const oat_geometry *g, int device, const oat_plan_options
             D.e1[a] = (float)e1[a];
             D.e2[a] = (float)e2[a];
             D.uqf[a] = (float)D.uq[a];
-            D.us[a] = (float)(D.uq[a] * (dx / (g->c0 * g->dt)));
         }
         D.dist = (float)(d / dx);
         double area = g->det_area ? g->det_area[q] : 4.0 * M_PI * d * d / Q;
