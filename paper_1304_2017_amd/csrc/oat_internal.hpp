@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace oat {
 
 // Edge of an image brick in cells.  One workgroup owns one brick and keeps
@@ -75,9 +77,9 @@ inline int fill_slices(int nbricks, int items, int min_items, int max_slices, in
 // G on the arc-table and bounds paths (one workgroup per CU): transducers
 // per slice >= 64.
 inline int fwd_slices(int nbricks, int nq) { return brick_slices(nbricks, nq, 64); }
-// Whole-transducer slices of G on the segment table, which runs two
-// workgroups per CU (rounds of 512): up to 8 of at least 64 transducers.
-inline int seg_fwd_slices(int nbricks, int nq) { return fill_slices(nbricks, nq, 64, 8, 512); }
+// Whole-transducer slices of G on the segment table (one workgroup per CU): up
+// to 8 of at least 64 transducers.
+inline int seg_fwd_slices(int nbricks, int nq) { return fill_slices(nbricks, nq, 64, 8, 256); }
 // Whole-window slices of G^T (one workgroup per CU): up to 8 of at least 2
 // windows.
 inline int adj_slices(int nbricks, int nq) { return fill_slices(nbricks, adj_windows(nq), 2, 8, 256); }
@@ -85,20 +87,20 @@ inline int adj_slices(int nbricks, int nq) { return fill_slices(nbricks, adj_win
 // Work split of G on the segment table: `slices` workgroups per brick, each
 // with `per` transducers.  parts = 0: the slices above, one unit per wave at
 // a time.  parts > 0: every unit is taken in `parts` parts (its segment
-// windows dealt round-robin), so that a workgroup has about 64 items for its
+// windows dealt round-robin), so that a workgroup has about 96 items for its
 // 16 waves, and the parts of a unit share its shell sums in LDS (integers:
 // bit for bit the sums of one wave).
 //
 // Grids of at least 4096 workgroups keep whole units: a workgroup's staging
 // of its box (a few us) and its last, part-idle units are then small, and at
-// 256^3 / 2048 splitting costs 0.8% (68.5 against 68.0 ms).  Smaller grids
-// leave CUs idle or end in a ragged last round: they take about 1024
-// workgroups and at most 32 transducers each (16: 6% slower at 128^3 / 1024
-// BF16, 64: the same; more workgroups: 60 x 61 x 45 / 300 24% slower from
-// the staging).  32^3 / 64: 925 -> 44 us; 128 x 105 x 117 / 1024 BF16:
-// 3.82 -> 3.50 ms.
-constexpr int FWD_SPLIT_Q = 32;
-constexpr int FWD_SPLIT_WORDS = 3328;   // shell sums of a slice: 26 KB, so two boxes share a CU
+// 256^3 / 2048 splitting costs 5% (57.3 against 54.8 ms).  Smaller grids leave
+// CUs idle or end in a ragged last round: they take a workgroup for each CU,
+// up to 64 transducers each, and 96 where that still leaves 11 rounds (32: 8%
+// slower at 128 x 105 x 117 / 1024 BF16, 64 2% slower; 96 throughout: 6%
+// slower at 96^3 / 512).  Against whole units: 32^3 / 64 925 -> 39 us, 128 x
+// 105 x 117 / 1024 BF16 3.82 -> 3.11 ms.
+constexpr int FWD_SPLIT_Q = 96;
+constexpr int FWD_SPLIT_WORDS = 6656;   // shell sums of a slice: 52 KB beside the box of 87 KB
 struct FwdGrid {
     int slices, per, parts;
 };
@@ -107,9 +109,10 @@ inline FwdGrid seg_fwd_grid(int nbricks, int nq, int window)
     const int sl = seg_fwd_slices(nbricks, nq);
     if ((long long)nbricks * sl >= 4096) return FwdGrid{sl, (nq + sl - 1) / sl, 0};
     const int fit = FWD_SPLIT_WORDS / window < FWD_SPLIT_Q ? FWD_SPLIT_WORDS / window : FWD_SPLIT_Q;
-    const long long want = (long long)nbricks * nq / 1024;
+    const long long units = (long long)nbricks * nq;
+    const long long want = std::max(std::min(units / 256, 64ll), units / 2816);
     const int per = want < 1 ? 1 : (want > fit ? fit : (int)want);
-    const int parts = 64 / per;
+    const int parts = 96 / per;
     return FwdGrid{(nq + per - 1) / per, per, parts > 16 ? 16 : parts};
 }
 

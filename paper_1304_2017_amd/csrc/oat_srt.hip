@@ -300,14 +300,13 @@ __device__ __forceinline__ Pt seg_point(const float Pl[3], const int dc[3], cons
 }
 
 // A point of a segment-table entry, which the brick owns: its cell as the byte
-// offset of its node in a box of ELT-byte words (base = that of the reference
+// offset of its node in a box of 8-byte words (base = that of the reference
 // point's cell) and its position in the cell; the FP32 operations are
 // seg_point's.
 struct CellPt {
     int off;
     float fx, fy, fz;
 };
-template <int ELT>
 __device__ __forceinline__ CellPt seg_cell(const float Pl[3], int base, const SegAxes &ax, float dd,
                                            float dj)
 {
@@ -317,8 +316,7 @@ __device__ __forceinline__ CellPt seg_cell(const float Pl[3], int base, const Se
     const float uy = fmaf(sn, ax.B[1], fmaf(cm1, ax.A[1], Pl[1]));
     const float uz = fmaf(sn, ax.B[2], fmaf(cm1, ax.A[2], Pl[2]));
     CellPt t;
-    t.off = mad24(cvt_floor(uz), BOX_SZ * ELT,
-                  mad24(cvt_floor(uy), BOX_SY * ELT, mad24(cvt_floor(ux), ELT, base)));
+    t.off = mad24(cvt_floor(uz), BOX_SZ * 8, mad24(cvt_floor(uy), BOX_SY * 8, mad24(cvt_floor(ux), 8, base)));
     t.fx = __builtin_amdgcn_fractf(ux);
     t.fy = __builtin_amdgcn_fractf(uy);
     t.fz = __builtin_amdgcn_fractf(uz);
@@ -326,10 +324,9 @@ __device__ __forceinline__ CellPt seg_cell(const float Pl[3], int base, const Se
 }
 
 // A point of the other paths in the same form.
-template <int ELT>
 __device__ __forceinline__ CellPt cell_of(const Pt &t)
 {
-    return CellPt{(int)(__umul24((unsigned)t.cz, BOX_SZ) + (__umul24((unsigned)t.cy, BOX_SY) + (unsigned)t.cx)) * ELT,
+    return CellPt{(int)(__umul24((unsigned)t.cz, BOX_SZ) + (__umul24((unsigned)t.cy, BOX_SY) + (unsigned)t.cx)) * 8,
                   t.fx, t.fy, t.fz};
 }
 
@@ -762,7 +759,7 @@ __device__ __forceinline__ int wave_min_i(int v) { return -wave_max_i(-v); }
 // with its weight (w g' in G^T), then sfn(np, so, w) once per window with
 // the lane's segment count (0: none), shell offset and weight.  PAIRS: the
 // points that every lane has are taken two at a time, without a lane mask.
-template <bool ADJ, int ELT, bool PAIRS, bool AHEAD, class PFn, class SFn>
+template <bool ADJ, bool PAIRS, class PFn, class SFn>
 __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, const int lo[3],
                                          const int hi[3], int *gbase, const float *gp,
                                          float gscale, float gscale2, int part, int parts,
@@ -798,13 +795,10 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
         wave_sync();
     }
     // A window's table data are a chain of dependent loads: entry, ring record,
-    // segment reference (and in G^T the sample).  AHEAD: each is issued a
-    // window or more before its use, entries three windows ahead, rings two,
-    // the rest one (past the last entry the last one is read again).  With 4
-    // waves a SIMD this is worth 7% of G and 2 to 5% of G^T (256^3 / 2048: 60.4
-    // -> 55.9 and 87.9 -> 85.6 ms; 128 x 105 x 117 BF16 G^T 4.38 -> 4.16 ms);
-    // the 64-register kernels of 8 waves a SIMD have no room for it and take
-    // only the next window's entries early.
+    // segment reference (and in G^T the sample).  Each is issued a window or
+    // more before its use, entries three windows ahead, rings two, the rest one
+    // (past the last entry the last one is read again): 256^3 / 2048: G 60.4 ->
+    // 55.9 ms, G^T 87.9 -> 85.6; 128 x 105 x 117 BF16 G^T 4.38 -> 4.16 ms.
     auto load_entry = [&](long long c) { return P.seg[min(c + lane, s1 - 1)]; };
     auto shell_of = [](unsigned e) { return (int)(e & ((1u << SEG_SHELL_BITS) - 1u)); };
     auto index_of = [](unsigned e) {
@@ -823,30 +817,18 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
     auto load_gp = [&](unsigned e) {
         return ADJ ? gp[(size_t)q * P.nt + klo + shell_of(e)] : 0.f;
     };
-    unsigned ent_0 = load_entry(s0), ent_1 = AHEAD ? load_entry(s0 + step) : 0u,
-             ent_2 = AHEAD ? load_entry(s0 + 2 * step) : 0u;
-    RingRec ring_0, ring_1;
-    double2 ref_0;
-    float gp_0 = 0.f;
-    if (AHEAD) {
-        ring_0 = load_ring(ent_0), ring_1 = load_ring(ent_1);
-        ref_0 = load_ref(ent_0, ring_0), gp_0 = load_gp(ent_0);
-    }
+    unsigned ent_0 = load_entry(s0), ent_1 = load_entry(s0 + step),
+             ent_2 = load_entry(s0 + 2 * step);
+    RingRec ring_0 = load_ring(ent_0), ring_1 = load_ring(ent_1);
+    double2 ref_0 = load_ref(ent_0, ring_0);
+    float gp_0 = load_gp(ent_0);
     for (long long c = s0; c < s1; c += step) {
         const bool v = c + lane < s1;
         const unsigned ent = ent_0;
-        RingRec ring_2;
-        double2 ref_1;
-        float gp_1;
-        unsigned ent_n;
-        if (AHEAD) {
-            ring_2 = load_ring(ent_2), ref_1 = load_ref(ent_1, ring_1), gp_1 = load_gp(ent_1);
-            ent_n = load_entry(c + 3 * step);
-        } else {
-            const long long en = c + step + lane;
-            ent_n = en < s1 ? P.seg[en] : 0u;
-            ring_0 = P.ring[v ? ring_of(ent) : 0];
-        }
+        const RingRec ring_2 = load_ring(ent_2);
+        const double2 ref_1 = load_ref(ent_1, ring_1);
+        const float gp_1 = load_gp(ent_1);
+        const unsigned ent_n = load_entry(c + 3 * step);
         const RingRec &rr = ring_0;
         const int so = shell_of(ent), sg = index_of(ent);
         const int off = (int)((ent >> (32 - SEG_CNT_BITS - SEG_OFF_BITS)) &
@@ -854,15 +836,13 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
         const int np = v ? (int)(ent >> (32 - SEG_CNT_BITS)) + 1 : 0;
         const int jref = seg_ref_index(sg, rr.lshift, rr.nj);
         const int dj0 = (sg << rr.lshift) + off - jref;   // first point, relative to jref
-        if (!AHEAD) ref_0 = v ? load_ref(ent, rr) : make_double2(1.0, 0.0);
         float Pl[3], xa, xb;
         int dc[3];
         seg_ref(uq, e3, e1d, e2d, lo, rr.rc, rr.rs, ref_0, Pl, dc, xa, xb);
         float w = rr.w;
-        if (!AHEAD && v) gp_0 = load_gp(ent);
         if (ADJ) w = w * ((gp_0 * gscale) * gscale2);
         const SegAxes ax = seg_axes(xa, xb, e1, e2);
-        const int base = (dc[2] * BOX_SZ + dc[1] * BOX_SY + dc[0]) * ELT;
+        const int base = (dc[2] * BOX_SZ + dc[1] * BOX_SY + dc[0]) * 8;
         const int nmax = wave_max_i(np);
         // dj0 + t as an FP32 counter (exact: |dj| < 2^24), one add per point
         float fdj = (float)dj0;
@@ -870,23 +850,19 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
         if (PAIRS) {
             const int npair = wave_min_i(np) & ~1;
             for (; t < npair; t += 2, fdj += 2.f) {
-                const CellPt a = seg_cell<ELT>(Pl, base, ax, rr.delta, fdj);
-                const CellPt c = seg_cell<ELT>(Pl, base, ax, rr.delta, fdj + 1.f);
+                const CellPt a = seg_cell(Pl, base, ax, rr.delta, fdj);
+                const CellPt c = seg_cell(Pl, base, ax, rr.delta, fdj + 1.f);
                 pfn(a, w);
                 pfn(c, w);
             }
         }
         for (; t < nmax; ++t, fdj += 1.f) {
-            if (t < np) pfn(seg_cell<ELT>(Pl, base, ax, rr.delta, fdj), w);
+            if (t < np) pfn(seg_cell(Pl, base, ax, rr.delta, fdj), w);
         }
         sfn(np, so, w);
-        if (AHEAD) {
-            ent_0 = ent_1, ent_1 = ent_2, ent_2 = ent_n;
-            ring_0 = ring_1, ring_1 = ring_2;
-            ref_0 = ref_1, gp_0 = gp_1;
-        } else {
-            ent_0 = ent_n;
-        }
+        ent_0 = ent_1, ent_1 = ent_2, ent_2 = ent_n;
+        ring_0 = ring_1, ring_1 = ring_2;
+        ref_0 = ref_1, gp_0 = gp_1;
     }
 }
 
@@ -992,30 +968,25 @@ srt_fwd_kernel(Problem P, const void *__restrict__ img, float *__restrict__ part
 // and the shell sums are per transducer of the slice.
 //
 // A point's 8 corners come from the LDS box, whose reads and the VALU are both
-// near their limits.  FP32 images on whole units: the box holds per node the
-// pair (v[x], v[x + 1] - v[x]), 8 bytes, so that a point is 4 aligned 64-bit
-// reads (8 cycles a wave at random addresses, against 15 for the two-dword
-// read of v[x] and v[x + 1]) and the x interpolation one FMA; one workgroup
-// a CU, which leaves the registers to work on two points at once.  256^3 /
-// 2048: 67.2 -> 60.4 ms (61.6 without the second point).
-// Elsewhere 4-byte words and two workgroups a CU (at most 64 VGPRs): on split
-// units, where one workgroup's staging and last units run under the other's
-// work (96^3 / 512 FP32: 1.14 ms, 1.22 with pairs), and for BF16 images, whose
-// word holds the two nodes as they are (200 x 211 x 180 / 1100: 15.3 ms, 15.9
-// with pairs).
+// near their limits.  The box holds per node the pair (v[x], v[x + 1] - v[x])
+// in FP32, 8 bytes, so that a point is 4 aligned 64-bit reads (8 cycles a wave
+// at random addresses, against 15 for the two-dword read of v[x] and v[x + 1])
+// and the x interpolation one FMA.  One such workgroup a CU leaves the
+// registers to work on two points at once and to load the table ahead
+// (walk_seg).  4-byte words (BF16: both nodes in one), two workgroups a CU of
+// 64 registers: 256^3 / 2048 FP32 67.2 ms, now 54 to 56; 128 x 105 x 117 / 1024
+// BF16 3.35 ms, now 3.11; 96^3 / 512 FP32 1.12 ms, now 0.98; 32^3 / 64 43 us,
+// now 39.
 constexpr int FWD_SEG_WAVES = 16;
-constexpr bool fwd_seg_pairs(int img_dt, bool split) { return img_dt == 0 && !split; }
-constexpr int fwd_seg_eu(int img_dt, bool split) { return fwd_seg_pairs(img_dt, split) ? 4 : 8; }
 
 template <int IMG_DT, bool SPLIT>
 __global__ void __launch_bounds__(FWD_SEG_WAVES *WAVE)
-__attribute__((amdgpu_waves_per_eu(fwd_seg_eu(IMG_DT, SPLIT), fwd_seg_eu(IMG_DT, SPLIT))))
+__attribute__((amdgpu_waves_per_eu(4, 4)))
 srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ part,
                    int *__restrict__ klo_out, int q_per_slice, int parts)
 {
     constexpr int NW = FWD_SEG_WAVES;
-    constexpr bool PB = fwd_seg_pairs(IMG_DT, SPLIT);
-    __shared__ __align__(8) float box[BOX_WORDS * (PB ? 2 : 1)];
+    __shared__ float2 box[BOX_WORDS];
     __shared__ int q_next;
     __shared__ float wmax[NW];
     __shared__ int wbad[NW];
@@ -1047,28 +1018,10 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
         amax = fmaxf(amax, a);
         return v;
     };
-    // Pairs: (node x, node x + 1 - node x).  FP32 images otherwise: one node
-    // per word.  BF16 images: word x holds the BF16 pair (node x, node x + 1),
-    // so a point's 8 corners are 4 words (2 reads).
-    if constexpr (PB) {
-        float2 *bw = reinterpret_cast<float2 *>(box);
-        for (int t = threadIdx.x; t < (BOX - 1) * BOX * BOX; t += blockDim.x) {
-            const int x = t % (BOX - 1), y = (t / (BOX - 1)) % BOX, z = t / ((BOX - 1) * BOX);
-            const float v = node(x, y, z);
-            bw[z * BOX_SZ + y * BOX_SY + x] = make_float2(v, node(x + 1, y, z) - v);
-        }
-    } else if constexpr (IMG_DT == 0) {
-        for (int t = threadIdx.x; t < BOX * BOX * BOX; t += blockDim.x) {
-            const int x = t % BOX, y = (t / BOX) % BOX, z = t / (BOX * BOX);
-            box[z * BOX_SZ + y * BOX_SY + x] = node(x, y, z);
-        }
-    } else {
-        unsigned *bw = reinterpret_cast<unsigned *>(box);
-        for (int t = threadIdx.x; t < (BOX - 1) * BOX * BOX; t += blockDim.x) {
-            const int x = t % (BOX - 1), y = (t / (BOX - 1)) % BOX, z = t / ((BOX - 1) * BOX);
-            bw[z * BOX_SZ + y * BOX_SY + x] =
-                (__float_as_uint(node(x, y, z)) >> 16) | (__float_as_uint(node(x + 1, y, z)) & 0xffff0000u);
-        }
+    for (int t = threadIdx.x; t < (BOX - 1) * BOX * BOX; t += blockDim.x) {
+        const int x = t % (BOX - 1), y = (t / (BOX - 1)) % BOX, z = t / ((BOX - 1) * BOX);
+        const float v = node(x, y, z);
+        box[z * BOX_SZ + y * BOX_SY + x] = make_float2(v, node(x + 1, y, z) - v);
     }
     const int wave = threadIdx.x / WAVE;
     const int lane = lane_id();
@@ -1138,55 +1091,18 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
         wave_sync();
         int klo = 0;
         float racc = 0.f;
-        // FP32 nodes: a point in the same cell as the lane's previous point
-        // reuses its corners without reading LDS (BF16 images, with half the
-        // reads, are faster without the test).
-        int prev = -1;
-        float c8[8];   // loaded before any use: prev starts out unmatched
         auto point = [&](const CellPt &t, float) {
-            float v000, v001, v010, v011, v100, v101, v110, v111;
-            if constexpr (PB) {
-                const float2 *pb = box_at(reinterpret_cast<float2 *>(box), t.off);
-                const float2 *pz = pb + BOX_SZ;
-                // (atomic loads so that two are not merged into one
-                // ds_read2_b64, which takes 26 cycles a wave, not 2 x 8)
-                auto ld = [](const float2 *p) {
-                    return __builtin_bit_cast(
-                        float2, __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p),
-                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT));
-                };
-                const float2 q00 = ld(pb), q01 = ld(pb + BOX_SY), q10 = ld(pz), q11 = ld(pz + BOX_SY);
-                const float c00 = fmaf(t.fx, q00.y, q00.x), c01 = fmaf(t.fx, q01.y, q01.x);
-                const float c10 = fmaf(t.fx, q10.y, q10.x), c11 = fmaf(t.fx, q11.y, q11.x);
-                const float c0 = fmaf(t.fy, c01 - c00, c00), c1 = fmaf(t.fy, c11 - c10, c10);
-                racc += fmaf(t.fz, c1 - c0, c0);
-                return;
-            } else if constexpr (IMG_DT == 0) {
-                if (t.off != prev) {
-                    prev = t.off;
-                    // (the plane above from a register of its own: the reads'
-                    // offsets reach both of its rows from there)
-                    int zo = t.off + BOX_SZ * 4;
-                    asm("" : "+v"(zo));
-                    const float *pb = box_at(box, t.off), *pz = box_at(box, zo);
-                    c8[0] = pb[0], c8[1] = pb[1], c8[2] = pb[BOX_SY], c8[3] = pb[BOX_SY + 1];
-                    c8[4] = pz[0], c8[5] = pz[1], c8[6] = pz[BOX_SY], c8[7] = pz[BOX_SY + 1];
-                }
-                v000 = c8[0], v001 = c8[1], v010 = c8[2], v011 = c8[3];
-                v100 = c8[4], v101 = c8[5], v110 = c8[6], v111 = c8[7];
-            } else {
-                int zo = t.off + BOX_SZ * 4;
-                asm("" : "+v"(zo));
-                const unsigned *pb = reinterpret_cast<const unsigned *>(box_at(box, t.off));
-                const unsigned *pz = reinterpret_cast<const unsigned *>(box_at(box, zo));
-                const unsigned w00 = pb[0], w01 = pb[BOX_SY], w10 = pz[0], w11 = pz[BOX_SY];
-                v000 = __uint_as_float(w00 << 16), v001 = __uint_as_float(w00 & 0xffff0000u);
-                v010 = __uint_as_float(w01 << 16), v011 = __uint_as_float(w01 & 0xffff0000u);
-                v100 = __uint_as_float(w10 << 16), v101 = __uint_as_float(w10 & 0xffff0000u);
-                v110 = __uint_as_float(w11 << 16), v111 = __uint_as_float(w11 & 0xffff0000u);
-            }
-            const float c00 = fmaf(t.fx, v001 - v000, v000), c01 = fmaf(t.fx, v011 - v010, v010);
-            const float c10 = fmaf(t.fx, v101 - v100, v100), c11 = fmaf(t.fx, v111 - v110, v110);
+            const float2 *pb = box_at(box, t.off), *pz = pb + BOX_SZ;
+            // (atomic loads so that two are not merged into one
+            // ds_read2_b64, which takes 26 cycles a wave, not 2 x 8)
+            auto ld = [](const float2 *p) {
+                return __builtin_bit_cast(
+                    float2, __hip_atomic_load(reinterpret_cast<const unsigned long long *>(p),
+                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT));
+            };
+            const float2 q00 = ld(pb), q01 = ld(pb + BOX_SY), q10 = ld(pz), q11 = ld(pz + BOX_SY);
+            const float c00 = fmaf(t.fx, q00.y, q00.x), c01 = fmaf(t.fx, q01.y, q01.x);
+            const float c10 = fmaf(t.fx, q10.y, q10.x), c11 = fmaf(t.fx, q11.y, q11.x);
             const float c0 = fmaf(t.fy, c01 - c00, c00), c1 = fmaf(t.fy, c11 - c10, c10);
             racc += fmaf(t.fz, c1 - c0, c0);
         };
@@ -1202,11 +1118,9 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
                                                         __double_as_longlong(0x1.8p52)));
             }
             racc = 0.f;
-            prev = -1;
         };
-        walk_seg<false, PB ? 8 : 4, PB, PB>(P, q, (size_t)b * P.nq + q, lo, hi, gbase, nullptr, 1.f,
-                                        1.f, SPLIT ? pt : 0, SPLIT ? parts : 1, klo, point,
-                                        segment);
+        walk_seg<false, true>(P, q, (size_t)b * P.nq + q, lo, hi, gbase, nullptr, 1.f, 1.f,
+                              SPLIT ? pt : 0, SPLIT ? parts : 1, klo, point, segment);
         wave_sync();
         if (SPLIT) {
             if (lane == 0) klo_s[q - qb] = klo;   // the same value from each part
@@ -1409,12 +1323,12 @@ srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc
                 if constexpr (TM == TM_SEG) {
                     auto point = [&](const CellPt &t, float wv) { scatter1(t, (wv * g1) * g2); };
                     auto segment = [](int, int, float) {};
-                    walk_seg<false, 8, false, true>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, nullptr,
-                                              1.f, 1.f, pt, parts, klo, point, segment);
+                    walk_seg<false, false>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, nullptr,
+                                           1.f, 1.f, pt, parts, klo, point, segment);
                 } else {
                     auto scatter = [&](const Pt &a, const Pt &c, float wv, int, int) {
-                        if (a.own) scatter1(cell_of<8>(a), (wv * g1) * g2);
-                        if (c.own) scatter1(cell_of<8>(c), (wv * g1) * g2);
+                        if (a.own) scatter1(cell_of(a), (wv * g1) * g2);
+                        if (c.own) scatter1(cell_of(c), (wv * g1) * g2);
                     };
                     walk_unit<false, TM, WALK_POINTS>(P, q, (size_t)b * P.nq + q, lo, hi, W,
                                                        nullptr, nullptr, 1.f, 1.f, klo, scatter);
@@ -1443,12 +1357,12 @@ srt_adj_kernel(Problem P, const float *__restrict__ gp, double *__restrict__ acc
                 if constexpr (TM == TM_SEG) {
                     auto point = [&](const CellPt &t, float wv) { scatter1(t, wv); };
                     auto segment = [](int, int, float) {};
-                    walk_seg<true, 8, false, true>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, gp, g1, g2,
-                                             pt, parts, klo, point, segment);
+                    walk_seg<true, false>(P, q, (size_t)b * P.nq + q, lo, hi, W.gbase, gp, g1, g2,
+                                          pt, parts, klo, point, segment);
                 } else {
                     auto scatter = [&](const Pt &a, const Pt &c, float wv, int, int) {
-                        if (a.own) scatter1(cell_of<8>(a), wv);
-                        if (c.own) scatter1(cell_of<8>(c), wv);
+                        if (a.own) scatter1(cell_of(a), wv);
+                        if (c.own) scatter1(cell_of(c), wv);
                     };
                     walk_unit<true, TM, WALK_POINTS>(P, q, (size_t)b * P.nq + q, lo, hi, W,
                                                       nullptr, gp, g1, g2, klo, scatter);
