@@ -779,6 +779,9 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
     const long long s0 = P.seg_off[unit] + part * WAVE, s1 = P.seg_off[unit + 1];
     const int step = parts * WAVE;
     if (s0 >= s1) return;
+    auto load_entry = [&](long long c) { return P.seg[min(c + lane, s1 - 1)]; };
+    unsigned ent_0 = load_entry(s0), ent_1 = load_entry(s0 + step),
+             ent_2 = load_entry(s0 + 2 * step);
     // Each shell's first candidate ring, as the bounds walk found it when
     // the table was built (the same FP32 operations).
     {
@@ -799,7 +802,6 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
     // more before its use, entries three windows ahead, rings two, the rest one
     // (past the last entry the last one is read again): 256^3 / 2048: G 60.4 ->
     // 55.9 ms, G^T 87.9 -> 85.6; 128 x 105 x 117 BF16 G^T 4.38 -> 4.16 ms.
-    auto load_entry = [&](long long c) { return P.seg[min(c + lane, s1 - 1)]; };
     auto shell_of = [](unsigned e) { return (int)(e & ((1u << SEG_SHELL_BITS) - 1u)); };
     auto index_of = [](unsigned e) {
         return (int)((e >> (SEG_SHELL_BITS + SEG_RING_BITS)) & ((1u << SEG_INDEX_BITS) - 1u));
@@ -817,8 +819,6 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
     auto load_gp = [&](unsigned e) {
         return ADJ ? gp[(size_t)q * P.nt + klo + shell_of(e)] : 0.f;
     };
-    unsigned ent_0 = load_entry(s0), ent_1 = load_entry(s0 + step),
-             ent_2 = load_entry(s0 + 2 * step);
     RingRec ring_0 = load_ring(ent_0), ring_1 = load_ring(ent_1);
     double2 ref_0 = load_ref(ent_0, ring_0);
     float gp_0 = load_gp(ent_0);
@@ -1003,25 +1003,41 @@ srt_fwd_seg_kernel(Problem P, const void *__restrict__ img, float *__restrict__ 
     // the fixed-point scale of the shell sums below
     float amax = 0.f;
     int abad = 0;
-    auto node = [&](int x, int y, int z) {
-        const int gx = lo[0] + x, gy = lo[1] + y, gz = lo[2] + z;
-        float v = 0.f;
-        if (gx >= 0 && gx < P.nx && gy >= 0 && gy < P.ny && gz >= 0 && gz < P.nz) {
-            const size_t n = ((size_t)gz * P.ny + gy) * P.nx + gx;
-            if (IMG_DT == 0)
-                v = ((const float *)img)[n];
-            else
-                v = __uint_as_float(((unsigned)((const unsigned short *)img)[n]) << 16);
-        }
+    auto load = [&](int x, int y, int z) {   // (any node of the grid where it lies outside)
+        const int gx = min(max(lo[0] + x, 0), P.nx - 1), gy = min(max(lo[1] + y, 0), P.ny - 1),
+                  gz = min(max(lo[2] + z, 0), P.nz - 1);
+        const size_t n = ((size_t)gz * P.ny + gy) * P.nx + gx;
+        if (IMG_DT == 0) return ((const float *)img)[n];
+        return __uint_as_float(((unsigned)((const unsigned short *)img)[n]) << 16);
+    };
+    auto node = [&](int x, int y, int z, float v) {   // zero outside the grid
+        const bool in = (unsigned)(lo[0] + x) < (unsigned)P.nx && (unsigned)(lo[1] + y) < (unsigned)P.ny &&
+                        (unsigned)(lo[2] + z) < (unsigned)P.nz;
+        v = in ? v : 0.f;
         const float a = fabsf(v);
         abad |= !(a <= 3.4028235e38f);
         amax = fmaxf(amax, a);
         return v;
     };
-    for (int t = threadIdx.x; t < (BOX - 1) * BOX * BOX; t += blockDim.x) {
-        const int x = t % (BOX - 1), y = (t / (BOX - 1)) % BOX, z = t / ((BOX - 1) * BOX);
-        const float v = node(x, y, z);
-        box[z * BOX_SZ + y * BOX_SY + x] = make_float2(v, node(x + 1, y, z) - v);
+    // (the loads of STAGE nodes are issued together; one at a time G takes 1%
+    // longer on split units)
+    constexpr int NODES = (BOX - 1) * BOX * BOX, STAGE = 5;
+    for (int t0 = threadIdx.x; t0 < NODES; t0 += STAGE * NW * WAVE) {
+        float va[STAGE], vb[STAGE];
+#pragma unroll
+        for (int k = 0; k < STAGE; ++k) {
+            const int t = min(t0 + k * NW * WAVE, NODES - 1);
+            const int x = t % (BOX - 1), y = (t / (BOX - 1)) % BOX, z = t / ((BOX - 1) * BOX);
+            va[k] = load(x, y, z);
+            vb[k] = load(x + 1, y, z);
+        }
+#pragma unroll
+        for (int k = 0; k < STAGE; ++k) {
+            const int t = min(t0 + k * NW * WAVE, NODES - 1);
+            const int x = t % (BOX - 1), y = (t / (BOX - 1)) % BOX, z = t / ((BOX - 1) * BOX);
+            const float v = node(x, y, z, va[k]);
+            box[z * BOX_SZ + y * BOX_SY + x] = make_float2(v, node(x + 1, y, z, vb[k]) - v);
+        }
     }
     const int wave = threadIdx.x / WAVE;
     const int lane = lane_id();
