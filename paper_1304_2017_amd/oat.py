@@ -35,7 +35,9 @@ EXPORTED = ("oat_plan_create", "oat_plan_create_ex", "oat_plan_destroy", "oat_pr
             # include/oat_cnn.h
             "oat_conv3d_forward", "oat_conv3d_backward_weight_workspace",
             "oat_conv3d_backward_weight", "oat_adam_step", "oat_mse_workspace", "oat_mse",
-            "oat_net_workspace", "oat_net_forward", "oat_net_backward")
+            "oat_net_workspace", "oat_net_forward", "oat_net_backward",
+            # include/oat_recon.h
+            "oat_recon_workspace", "oat_dot", "oat_tv", "oat_tv_curvature")
 
 
 class OatError(RuntimeError):
@@ -131,6 +133,14 @@ def lib():
         L.oat_net_forward.restype = ci
         L.oat_net_backward.argtypes = [vp] * 4 + [ci] * 3 + [vp] * 9 + [sz, vp]
         L.oat_net_backward.restype = ci
+        L.oat_recon_workspace.argtypes = []
+        L.oat_recon_workspace.restype = sz
+        L.oat_dot.argtypes = [vp, vp, ctypes.c_int64, vp, vp, vp]
+        L.oat_dot.restype = ci
+        L.oat_tv.argtypes = [vp, ci, ci, ci, ctypes.c_float, vp, vp, vp, vp, vp]
+        L.oat_tv.restype = ci
+        L.oat_tv_curvature.argtypes = [vp, vp, ci, ci, ci, vp, vp, vp]
+        L.oat_tv_curvature.restype = ci
         _lib = L
     return _lib
 

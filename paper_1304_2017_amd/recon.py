@@ -29,12 +29,15 @@ of Sec. IV.A.
 """
 from __future__ import annotations
 
+import ctypes
 import os
 import time
 from dataclasses import dataclass, field
 from typing import Callable, List, Optional
 
 import torch
+
+from . import oat
 
 
 class Project(torch.autograd.Function):
@@ -94,8 +97,65 @@ def smoothness_normal(a: torch.Tensor) -> torch.Tensor:
     return out
 
 
+def _fused(*tensors) -> bool:
+    """The tensors are what the library's vector kernels take: plain FP32 on one GPU, dense and
+    not empty, fewer than 2^31 elements, and outside autograd."""
+    t0 = tensors[0]
+    return t0.is_cuda and all(
+        type(t) is torch.Tensor and t.dtype == torch.float32 and t.device == t0.device
+        and t.is_contiguous() and 0 < t.numel() < 2 ** 31 and not t.requires_grad
+        for t in tensors)
+
+
+class _Sums:
+    """FP64 scalars of one step, computed by the library's vector kernels into one device array
+    and read back together."""
+
+    def __init__(self, device, count: int):
+        L = oat.lib()
+        self.lib, self.device, self.used = L, device, 0
+        self.out = torch.empty(count, device=device, dtype=torch.float64)
+        self.work = torch.empty(L.oat_recon_workspace() // 8, device=device, dtype=torch.float64)
+
+    def _call(self, fn, *args):
+        ptrs = [ctypes.c_void_p(x.data_ptr()) if isinstance(x, torch.Tensor) else x for x in args]
+        out = ctypes.c_void_p(self.out.data_ptr() + 8 * self.used)
+        self.used += 1
+        with torch.cuda.device(self.device):
+            stream = torch.cuda.current_stream(self.device).cuda_stream
+            oat._check(fn(*ptrs, out, ctypes.c_void_p(self.work.data_ptr()),
+                          ctypes.c_void_p(stream)))
+
+    def dot(self, a, b):
+        self._call(self.lib.oat_dot, a, b, a.numel())
+
+    def tv(self, a, eps):
+        nz, ny, nx = a.shape
+        grad, w = torch.empty_like(a), torch.empty_like(a)
+        self._call(self.lib.oat_tv, a, nx, ny, nz, float(eps * eps), grad, w)
+        return grad, w
+
+    def curvature(self, d, w):
+        nz, ny, nx = d.shape
+        self._call(self.lib.oat_tv_curvature, d, w, nx, ny, nz)
+
+    def read(self) -> List[float]:
+        return self.out[:self.used].tolist()
+
+
+def _dots(*pairs) -> List[float]:
+    """Inner products, accumulated in FP64."""
+    if all(a.shape == b.shape and _fused(a, b) for a, b in pairs) \
+            and len({a.device for a, _ in pairs}) == 1:
+        s = _Sums(pairs[0][0].device, len(pairs))
+        for a, b in pairs:
+            s.dot(a, b)
+        return s.read()
+    return [float(torch.dot(a.reshape(-1).double(), b.reshape(-1).double())) for a, b in pairs]
+
+
 def _dot(a: torch.Tensor, b: torch.Tensor) -> float:
-    return float(torch.dot(a.reshape(-1).double(), b.reshape(-1).double()))
+    return _dots((a, b))[0]
 
 
 def rmse(a: torch.Tensor, ref) -> float:
@@ -235,6 +295,33 @@ def tv_eps(a: torch.Tensor, eps: float):
     return float(s.double().sum()), grad, w
 
 
+def _tv_sums(a: torch.Tensor, eps: float, *pairs):
+    """`tv_eps` of the iterate a and, read back with it, the inner products of `pairs`:
+    (TV, gradient, weights, inner products)."""
+    if a.dim() == 3 and all(x.shape == y.shape and _fused(a, x, y) for x, y in pairs or ((a, a),)):
+        s = _Sums(a.device, 1 + len(pairs))
+        grad, w = s.tv(a, eps)
+        for x, y in pairs:
+            s.dot(x, y)
+        tv, *dots = s.read()
+        return tv, grad, w, dots
+    tv, grad, w = tv_eps(a, eps)
+    return tv, grad, w, _dots(*pairs) if pairs else []
+
+
+def _step_sums(Hd, d, g, w):
+    """||H d||^2, <g, d> and the TV curvature sum w |grad d|^2 along d."""
+    if d.dim() == 3 and d.shape == g.shape == w.shape and _fused(d, g, w, Hd):
+        s = _Sums(d.device, 3)
+        s.dot(Hd, Hd)
+        s.dot(g, d)
+        s.curvature(d, w)
+        return s.read()
+    dx, dy, dz = forward_diff(d)
+    curv = float((w.double() * (dx * dx + dy * dy + dz * dz).double()).sum())
+    return [*_dots((Hd, Hd), (g, d)), curv]
+
+
 def _pls_tv_steps(plan, u: torch.Tensor, mu: float, eps: float, iters: int, storage,
                   state: Optional[dict] = None):
     """The PLS-TV recursion; yields (k, a, g, d, r, gg, ||u - H a||^2, TV_eps(a))
@@ -250,34 +337,32 @@ def _pls_tv_steps(plan, u: torch.Tensor, mu: float, eps: float, iters: int, stor
         k0 = 0
         a = torch.zeros(plan.image_shape, device=u.device, dtype=torch.float32)
         r = u.clone()                                # u - H a
-        tv, tg, w = tv_eps(a, eps)
-        g = -2.0 * HT(r) + mu * tg
+        tv, tg, w, (rr,) = _tv_sums(a, eps, (r, r))
+        g = torch.add(mu * tg, HT(r), alpha=-2.0)
         d = -g
         gg = _dot(g, g)
-        yield 0, a, g, d, r, gg, _dot(r, r), tv
+        yield 0, a, g, d, r, gg, rr, tv
     else:
         k0, a, r, g, d, gg = state["k"], state["a"], state["r"], state["g"], state["d"], state["gg"]
-        tv, tg, w = tv_eps(a, eps)
+        tv, tg, w, _ = _tv_sums(a, eps)
     for k in range(k0, iters):
         Hd = H(d)
-        dx, dy, dz = forward_diff(d)
-        curv = float((w.double() * (dx * dx + dy * dy + dz * dz).double()).sum())
-        den = 2.0 * _dot(Hd, Hd) + mu * curv
-        slope = _dot(g, d)
+        hh, slope, curv = _step_sums(Hd, d, g, w)
+        den = 2.0 * hh + mu * curv
         if den <= 0.0 or slope >= 0.0:
             return
         t = -slope / den
-        a = a + t * d
-        r = r - t * Hd
-        tv, tg, w = tv_eps(a, eps)
-        g_new = -2.0 * HT(r) + mu * tg
-        gg_new = _dot(g_new, g_new)
-        beta = max(0.0, (gg_new - _dot(g_new, g)) / gg) if gg > 0 else 0.0
-        d = -g_new + beta * d
+        a = torch.add(a, d, alpha=t)
+        r = torch.add(r, Hd, alpha=-t)
+        tv, tg, w, (rr,) = _tv_sums(a, eps, (r, r))
+        g_new = torch.add(mu * tg, HT(r), alpha=-2.0)
+        gg_new, gn_g = _dots((g_new, g_new), (g_new, g))
+        beta = max(0.0, (gg_new - gn_g) / gg) if gg > 0 else 0.0
+        d = torch.add(-g_new, d, alpha=beta)
         if _dot(g_new, d) >= 0.0:
             d = -g_new
         g, gg = g_new, gg_new
-        yield k + 1, a, g, d, r, gg, _dot(r, r), tv
+        yield k + 1, a, g, d, r, gg, rr, tv
 
 
 def pls_tv(plan, u: torch.Tensor, mu: float, eps: float, iters: int = 20,
@@ -307,7 +392,7 @@ def pls_tv(plan, u: torch.Tensor, mu: float, eps: float, iters: int = 20,
         if track:
             res.residuals.append(rn ** 0.5 / unorm)
             res.objective.append(rn + mu * tv)
-            res.times.append(time.perf_counter() - t0)   # rn is an FP64 dot: the device is synced
+            res.times.append(time.perf_counter() - t0)   # the step ended with an FP64 dot read back
         if observe is not None:                       # not counted in the times
             t_obs = time.perf_counter()
             observe(k, a)
