@@ -159,7 +159,6 @@ struct alignas(16) DetRec {
     float pad;
     double r[3];       // transducer position in mm
     double pad2;
-    float pad3;
 };
 
 // Per-shell record: shell k holds rings [ring_base, ring_base + n_rings).

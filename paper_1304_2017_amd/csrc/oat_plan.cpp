@@ -451,7 +451,6 @@ int oat_plan_create_ex(const oat_geometry *g, int device, const oat_plan_options
         D.r[1] = r[1];
         D.r[2] = r[2];
         D.pad2 = 0.0;
-        D.pad3 = 0.f;
     }
 
     // Quadrature tables in FP64 (Appendix; bands of arc length dx from the pole).
