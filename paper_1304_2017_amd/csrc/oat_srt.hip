@@ -236,23 +236,27 @@ struct BuildLds {
 
 // Reference point of a ring segment.  cs = (cos, sin) in FP64 of the
 // segment's reference azimuth (Problem::segref).  The point, formed in FP64,
-// is split into an integer cell relative to the box (clamped; clamped
-// offsets only occur for points far outside the box) and an FP32 fraction
-// Pl; (xa, xb) = rs (cos, sin) are its in-plane coordinates.
+// is split into an integer cell relative to the box and an FP32 fraction Pl;
+// (xa, xb) = rs (cos, sin) are its in-plane coordinates.  CLAMP: the offsets
+// are clamped, which only binds for points far outside the box (never for a
+// table entry's).
+template <bool CLAMP>
 __device__ __forceinline__ void seg_ref(const double uq[3], const double e3[3],
                                         const double e1d[3], const double e2d[3],
                                         const int lo[3], double rc, double rs, double2 cs,
                                         float Pl[3], int dc[3], float &xa, float &xb)
 {
+    const double pxa = rs * cs.x, pxb = rs * cs.y;
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const double pa = fma(rc, e3[a], uq[a]) + rs * fma(cs.x, e1d[a], cs.y * e2d[a]);
+        const double pa = fma(pxb, e2d[a], fma(pxa, e1d[a], fma(rc, e3[a], uq[a])));
         const double ph = floor(pa);
         Pl[a] = (float)(pa - ph);
-        dc[a] = min(max((int)ph - lo[a], -512), 511);
+        dc[a] = (int)ph - lo[a];
+        if (CLAMP) dc[a] = min(max(dc[a], -512), 511);
     }
-    xa = (float)(rs * cs.x);
-    xb = (float)(rs * cs.y);
+    xa = (float)pxa;
+    xb = (float)pxb;
 }
 
 // Point j of a segment, dj = j - jref, relative to the segment's reference
@@ -364,8 +368,8 @@ __device__ __forceinline__ void segment_points(const Problem &P, SegLds &W, Buil
     const int jref = seg_ref_index(sg, ls2, nj2);
     float Pl[3], xa, xb;
     int dc[3];
-    seg_ref(uq, e3, e1d, e2d, lo, rc2, rs2, v2 ? P.segref[sref2 + sg] : make_double2(1.0, 0.0),
-            Pl, dc, xa, xb);
+    seg_ref<true>(uq, e3, e1d, e2d, lo, rc2, rs2,
+                  v2 ? P.segref[sref2 + sg] : make_double2(1.0, 0.0), Pl, dc, xa, xb);
     const int np = v2 ? npts : 0;
     // jb - jref in [-16, 16], npts <= 32, shell index < 4096 (n_t <= 4096)
     const int meta = (jb - jref + 64) | (np << 7) | (k2 << 13);
@@ -734,22 +738,6 @@ struct SegWave {
     int gbase[WMAX];
 };
 
-// Maximum over the 64 lanes (all active), returned to every lane.
-__device__ __forceinline__ int wave_max_i(int v)
-{
-    v = max(v, dpp_i<0xB1, 0xF>(v));    // quad_perm [1,0,3,2]
-    v = max(v, dpp_i<0x4E, 0xF>(v));    // quad_perm [2,3,0,1]
-    v = max(v, dpp_i<0x141, 0xF>(v));   // row_half_mirror
-    v = max(v, dpp_i<0x140, 0xF>(v));   // row_mirror: every lane holds its row maximum
-    v = max(v, __builtin_amdgcn_readlane(v, 16));
-    v = max(v, __builtin_amdgcn_readlane(v, 32));
-    v = max(v, __builtin_amdgcn_readlane(v, 48));
-    return __builtin_amdgcn_readfirstlane(v);
-}
-
-// Minimum over the 64 lanes (all active), returned to every lane.
-__device__ __forceinline__ int wave_min_i(int v) { return -wave_max_i(-v); }
-
 // Walk the points of transducer q owned by the brick from the plan's segment
 // table: one segment per lane, 64 at a time, each lane taking its segment's
 // points one after the other (a window's segments have nearly equal counts:
@@ -776,12 +764,20 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
     unit_shells(P, uq, lo, hi, klo, khi);
     klo_out = klo;
     const int lane = lane_id();
-    const long long s0 = P.seg_off[unit] + part * WAVE, s1 = P.seg_off[unit + 1];
-    const int step = parts * WAVE;
-    if (s0 >= s1) return;
-    auto load_entry = [&](long long c) { return P.seg[min(c + lane, s1 - 1)]; };
-    unsigned ent_0 = load_entry(s0), ent_1 = load_entry(s0 + step),
-             ent_2 = load_entry(s0 + 2 * step);
+    // (uniform: kept in scalar registers; a unit has fewer than 2^26 entries, the
+    // shells, rings, segments and runs of one)
+    const long long first = P.seg_off[unit];
+    const int n = __builtin_amdgcn_readfirstlane((int)(P.seg_off[unit + 1] - first));
+    const char *seg = reinterpret_cast<const char *>(
+        P.seg + (((long long)__builtin_amdgcn_readfirstlane((int)(first >> 32)) << 32) |
+                 (unsigned)__builtin_amdgcn_readfirstlane((int)first)));
+    const int s0 = part * WAVE, step = parts * WAVE;
+    if (s0 >= n) return;
+    auto load_entry = [&](int c) {
+        return *reinterpret_cast<const unsigned *>(seg + (unsigned)min(c + lane, n - 1) * 4u);
+    };
+    unsigned e_0 = load_entry(s0), e_1 = load_entry(s0 + step), e_2 = load_entry(s0 + 2 * step),
+             e_3 = load_entry(s0 + 3 * step);
     // Each shell's first candidate ring, as the bounds walk found it when
     // the table was built (the same FP32 operations).
     {
@@ -799,9 +795,14 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
     }
     // A window's table data are a chain of dependent loads: entry, ring record,
     // segment reference (and in G^T the sample).  Each is issued a window or
-    // more before its use, entries three windows ahead, rings two, the rest one
-    // (past the last entry the last one is read again): 256^3 / 2048: G 60.4 ->
-    // 55.9 ms, G^T 87.9 -> 85.6; 128 x 105 x 117 BF16 G^T 4.38 -> 4.16 ms.
+    // more before its use, entries two to four windows ahead, rings two, the
+    // rest one (past the last entry the last one is read again): 256^3 / 2048: G
+    // 60.4 -> 55.9 ms, G^T 87.9 -> 85.6; 128 x 105 x 117 BF16 G^T 4.38 -> 4.16.
+    // Two windows per loop pass, so that no ring or reference is moved from one
+    // window's registers to the next's, and a window's largest and smallest
+    // counts from its first and last lane, since its entries are sorted: with
+    // the reference point in 11 FP64 operations (17) a window's set-up took 40
+    // instructions fewer, and G 54.2 -> 51.2 ms, G^T 83.6 -> 82.0.
     auto shell_of = [](unsigned e) { return (int)(e & ((1u << SEG_SHELL_BITS) - 1u)); };
     auto index_of = [](unsigned e) {
         return (int)((e >> (SEG_SHELL_BITS + SEG_RING_BITS)) & ((1u << SEG_INDEX_BITS) - 1u));
@@ -819,17 +820,14 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
     auto load_gp = [&](unsigned e) {
         return ADJ ? gp[(size_t)q * P.nt + klo + shell_of(e)] : 0.f;
     };
-    RingRec ring_0 = load_ring(ent_0), ring_1 = load_ring(ent_1);
-    double2 ref_0 = load_ref(ent_0, ring_0);
-    float gp_0 = load_gp(ent_0);
-    for (long long c = s0; c < s1; c += step) {
-        const bool v = c + lane < s1;
-        const unsigned ent = ent_0;
-        const RingRec ring_2 = load_ring(ent_2);
-        const double2 ref_1 = load_ref(ent_1, ring_1);
-        const float gp_1 = load_gp(ent_1);
-        const unsigned ent_n = load_entry(c + 3 * step);
-        const RingRec &rr = ring_0;
+    RingRec ring_a = load_ring(e_0), ring_b = load_ring(e_1);
+    double2 ref_a = load_ref(e_0, ring_a), ref_b;
+    float gp_a = load_gp(e_0), gp_b;
+    // The window from entry c on (entries ent, rings rr, references ref, samples
+    // gv); its ring registers take window c + 2's rings (entries e_n) as soon as
+    // they are read.
+    auto window = [&](int c, unsigned ent, RingRec &rr, double2 ref, float gv, unsigned e_n) {
+        const bool v = lane < n - c;
         const int so = shell_of(ent), sg = index_of(ent);
         const int off = (int)((ent >> (32 - SEG_CNT_BITS - SEG_OFF_BITS)) &
                               ((1u << SEG_OFF_BITS) - 1u));
@@ -838,31 +836,46 @@ __device__ __forceinline__ void walk_seg(const Problem &P, int q, size_t unit, c
         const int dj0 = (sg << rr.lshift) + off - jref;   // first point, relative to jref
         float Pl[3], xa, xb;
         int dc[3];
-        seg_ref(uq, e3, e1d, e2d, lo, rr.rc, rr.rs, ref_0, Pl, dc, xa, xb);
+        seg_ref<false>(uq, e3, e1d, e2d, lo, rr.rc, rr.rs, ref, Pl, dc, xa, xb);
         float w = rr.w;
-        if (ADJ) w = w * ((gp_0 * gscale) * gscale2);
+        const float dd = rr.delta;
+        if (ADJ) w = w * ((gv * gscale) * gscale2);
         const SegAxes ax = seg_axes(xa, xb, e1, e2);
         const int base = (dc[2] * BOX_SZ + dc[1] * BOX_SY + dc[0]) * 8;
-        const int nmax = wave_max_i(np);
+        rr = load_ring(e_n);
+        // (sorted by decreasing count)
+        const int nmax = __builtin_amdgcn_readfirstlane(np);
         // dj0 + t as an FP32 counter (exact: |dj| < 2^24), one add per point
         float fdj = (float)dj0;
         int t = 0;
         if (PAIRS) {
-            const int npair = wave_min_i(np) & ~1;
+            const int npair = __builtin_amdgcn_readlane(np, WAVE - 1) & ~1;
             for (; t < npair; t += 2, fdj += 2.f) {
-                const CellPt a = seg_cell(Pl, base, ax, rr.delta, fdj);
-                const CellPt c = seg_cell(Pl, base, ax, rr.delta, fdj + 1.f);
+                const CellPt a = seg_cell(Pl, base, ax, dd, fdj);
+                const CellPt b = seg_cell(Pl, base, ax, dd, fdj + 1.f);
                 pfn(a, w);
-                pfn(c, w);
+                pfn(b, w);
             }
         }
         for (; t < nmax; ++t, fdj += 1.f) {
-            if (t < np) pfn(seg_cell(Pl, base, ax, rr.delta, fdj), w);
+            if (t < np) pfn(seg_cell(Pl, base, ax, dd, fdj), w);
         }
         sfn(np, so, w);
-        ent_0 = ent_1, ent_1 = ent_2, ent_2 = ent_n;
-        ring_0 = ring_1, ring_1 = ring_2;
-        ref_0 = ref_1, gp_0 = gp_1;
+    };
+    for (int c = s0;;) {
+        ref_b = load_ref(e_1, ring_b);
+        gp_b = load_gp(e_1);
+        const unsigned e_4 = load_entry(c + 4 * step);
+        window(c, e_0, ring_a, ref_a, gp_a, e_2);
+        c += step;
+        if (c >= n) break;
+        ref_a = load_ref(e_2, ring_a);
+        gp_a = load_gp(e_2);
+        const unsigned e_5 = load_entry(c + 4 * step);
+        window(c, e_1, ring_b, ref_b, gp_b, e_3);
+        c += step;
+        if (c >= n) break;
+        e_0 = e_2, e_1 = e_3, e_2 = e_4, e_3 = e_5;
     }
 }
 
@@ -974,9 +987,9 @@ srt_fwd_kernel(Problem P, const void *__restrict__ img, float *__restrict__ part
 // and the x interpolation one FMA.  One such workgroup a CU leaves the
 // registers to work on two points at once and to load the table ahead
 // (walk_seg).  4-byte words (BF16: both nodes in one), two workgroups a CU of
-// 64 registers: 256^3 / 2048 FP32 67.2 ms, now 54 to 56; 128 x 105 x 117 / 1024
-// BF16 3.35 ms, now 3.11; 96^3 / 512 FP32 1.12 ms, now 0.98; 32^3 / 64 43 us,
-// now 39.
+// 64 registers: 256^3 / 2048 FP32 67.2 ms, now 51.2; 128 x 105 x 117 / 1024
+// BF16 3.35 ms, now 2.91; 96^3 / 512 FP32 1.12 ms, now 0.92; 32^3 / 64 43 us,
+// now 36.
 constexpr int FWD_SEG_WAVES = 16;
 
 template <int IMG_DT, bool SPLIT>
