@@ -303,7 +303,7 @@ def pls_tv_learned(plan, u: torch.Tensor, model: Preconditioner, mu: float, eps:
 
     a = torch.zeros(plan.image_shape, device=u.device, dtype=torch.float32)
     r = u.clone()
-    tv, tg, w = recon.tv_eps(a, eps)
+    tv, tg, w, _ = recon._tv_sums(a, eps)
     g = -2.0 * HT(r) + mu * tg
     s = -g
     z = net(s)
@@ -320,16 +320,14 @@ def pls_tv_learned(plan, u: torch.Tensor, model: Preconditioner, mu: float, eps:
     for _ in range(iters):
         res.directions.append((kind, cos))
         Hd = H(d)
-        dx, dy, dz = recon.forward_diff(d)
-        curv = float((w.double() * (dx * dx + dy * dy + dz * dz).double()).sum())
-        den = 2.0 * recon._dot(Hd, Hd) + mu * curv
-        slope = recon._dot(g, d)
+        hh, slope, curv = recon._step_sums(Hd, d, g, w)
+        den = 2.0 * hh + mu * curv
         if den <= 0.0 or slope >= 0.0:
             break
         t = -slope / den
         a = a + t * d
         r = r - t * Hd
-        tv, tg, w = recon.tv_eps(a, eps)
+        tv, tg, w, (rn,) = recon._tv_sums(a, eps, (r, r))
         g = -2.0 * HT(r) + mu * tg
         s_new = -g
         ss_new = recon._dot(s_new, s_new)
@@ -348,7 +346,6 @@ def pls_tv_learned(plan, u: torch.Tensor, model: Preconditioner, mu: float, eps:
             kind, d, cos = _direction(cands + [("learned", z_new)], s_new, switch)
             zs = recon._dot(z_new, s_new)
         s = s_new
-        rn = recon._dot(r, r)
         res.residuals.append(rn ** 0.5 / unorm)
         res.objective.append(rn + mu * tv)
         res.times.append(time.perf_counter() - t0)   # after FP64 dots: the device is synced

@@ -338,7 +338,7 @@ def _pls_tv_steps(plan, u: torch.Tensor, mu: float, eps: float, iters: int, stor
         a = torch.zeros(plan.image_shape, device=u.device, dtype=torch.float32)
         r = u.clone()                                # u - H a
         tv, tg, w, (rr,) = _tv_sums(a, eps, (r, r))
-        g = torch.add(mu * tg, HT(r), alpha=-2.0)
+        g = -2.0 * HT(r) + mu * tg
         d = -g
         gg = _dot(g, g)
         yield 0, a, g, d, r, gg, rr, tv
@@ -352,13 +352,13 @@ def _pls_tv_steps(plan, u: torch.Tensor, mu: float, eps: float, iters: int, stor
         if den <= 0.0 or slope >= 0.0:
             return
         t = -slope / den
-        a = torch.add(a, d, alpha=t)
-        r = torch.add(r, Hd, alpha=-t)
+        a = a + t * d
+        r = r - t * Hd
         tv, tg, w, (rr,) = _tv_sums(a, eps, (r, r))
-        g_new = torch.add(mu * tg, HT(r), alpha=-2.0)
+        g_new = -2.0 * HT(r) + mu * tg
         gg_new, gn_g = _dots((g_new, g_new), (g_new, g))
         beta = max(0.0, (gg_new - gn_g) / gg) if gg > 0 else 0.0
-        d = torch.add(-g_new, d, alpha=beta)
+        d = -g_new + beta * d
         if _dot(g_new, d) >= 0.0:
             d = -g_new
         g, gg = g_new, gg_new
