@@ -206,15 +206,16 @@ adj_gather_kernel(Problem P, const double *__restrict__ acc, int slices, void *_
 // 2 e R, the rounded offset e R, the last rounding e win.  kt carries + tol, so
 // that "within tol of an integer" is one comparison of its fraction.
 //
-// Bound by VALU issue: 11 instructions an update, one of them the quarter-rate
-// rsqrt, and the FP64 decisions (6% of the wave updates): 11.1 ms at 256^3 /
-// 2048.  With positions about the grid's origin, whose looser bound sent 15% to
+// Bound by VALU issue: 10 instructions an update, one of them the quarter-rate
+// rsqrt, and the FP64 decisions (6% of the wave updates): 10.3 ms at 256^3 /
+// 2048.  HELD leaves out the clamp of the LDS index where the host has shown
+// that it cannot bind (11.0 ms with it).  With positions about the grid's origin, whose looser bound sent 15% to
 // FP64, 13 instructions an update and a division a staged sample: 12.6 ms; one
 // branch for the column's eight voxels instead of one each: slower.
 constexpr int FBP_LDS = 4096;     // staged samples per chunk (32 KB) and
 constexpr int FBP_CHUNK = 128;    // transducers: 39 KB, four workgroups per CU
 
-template <int P_DT, int IMG_DT>
+template <int P_DT, int IMG_DT, bool HELD>
 __global__ void __launch_bounds__(FBP_TX *FBP_TY)
 fbp_kernel(Problem P, const void *__restrict__ pres, void *__restrict__ img, int win, int chunk)
 {
@@ -322,11 +323,11 @@ fbp_kernel(Problem P, const void *__restrict__ pres, void *__restrict__ img, int
                         }
                     }
                 }
-                // li lies in 0 .. win - 2 (the window spans the tile's sample
-                // range with margins; tests/host/fbp_window_check.cpp checks
-                // it over every workload geometry); the unsigned minimum only
-                // keeps the reads inside the row.
-                const float2 s = row[min((unsigned)li, (unsigned)(win - 2))];
+                // li lies in 0 .. win - 2 (fbp_window_holds;
+                // tests/host/fbp_window_check.cpp checks it over every workload
+                // geometry).  Where FP32 distances are too coarse for the proof,
+                // the unsigned minimum keeps the reads inside the row.
+                const float2 s = row[HELD ? (unsigned)li : min((unsigned)li, (unsigned)(win - 2))];
                 acc_a[v] = fmaf(inv, fmaf(fr, s.y, s.x), acc_a[v]);
                 acc_b[v] += s.y;
             }
@@ -381,14 +382,17 @@ hipError_t launch_fbp(const Problem &P, const void *p, int p_dtype, void *img, i
     if (chunk < 1) return hipErrorInvalidValue;
     dim3 grid((P.nx + FBP_TX - 1) / FBP_TX, (P.ny + FBP_TY - 1) / FBP_TY, (P.nz + FBP_TZ - 1) / FBP_TZ);
     dim3 block(FBP_TX * FBP_TY);
+    auto launch = [&](auto held, auto clamped) {
+        hipLaunchKernelGGL(P.fbp_held ? held : clamped, grid, block, 0, s, P, p, img, win, chunk);
+    };
     if (p_dtype == 0 && img_dtype == 0)
-        hipLaunchKernelGGL((fbp_kernel<0, 0>), grid, block, 0, s, P, p, img, win, chunk);
+        launch(fbp_kernel<0, 0, true>, fbp_kernel<0, 0, false>);
     else if (p_dtype == 0)
-        hipLaunchKernelGGL((fbp_kernel<0, 1>), grid, block, 0, s, P, p, img, win, chunk);
+        launch(fbp_kernel<0, 1, true>, fbp_kernel<0, 1, false>);
     else if (img_dtype == 0)
-        hipLaunchKernelGGL((fbp_kernel<1, 0>), grid, block, 0, s, P, p, img, win, chunk);
+        launch(fbp_kernel<1, 0, true>, fbp_kernel<1, 0, false>);
     else
-        hipLaunchKernelGGL((fbp_kernel<1, 1>), grid, block, 0, s, P, p, img, win, chunk);
+        launch(fbp_kernel<1, 1, true>, fbp_kernel<1, 1, false>);
     return hipGetLastError();
 }
 

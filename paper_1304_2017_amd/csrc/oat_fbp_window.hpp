@@ -38,4 +38,19 @@ __host__ __device__ inline int fbp_first_sample(float dc, float sigma, float tau
     return (int)floorf(fmaf(dc - fbp_half_diag(), sigma, -tau)) - 2;
 }
 
+// Whether the indices of every voxel stay inside the staged windows without a
+// clamp, for transducers and voxels within `reach` grid units of each other per
+// axis.  With e = 2^-24, the FP32 argument of fbp_first_sample's floor is off by
+// at most 16 e ((reach + 36) sigma + |tau|) samples: the position and the
+// difference 3.5, the norm 6.1, dc - half 1.7, sigma 1.7, the product 1.7 times
+// e reach sigma, half 36 e sigma, tau and the product 2 e |tau|.  If that is at
+// most 1/2, a voxel's position relative to the first sample, between dc - half
+// and dc + half exactly, lies in [1.5, 2 half sigma + 3.5], and with the
+// kernel's + 2 tol (at most 0.8 then) and its step down by one sample the index
+// lies in 0 .. ceil(2 half sigma) + 4 = window - 2.
+__host__ inline bool fbp_window_holds(double reach, double sigma, double tau)
+{
+    return 16.0 / 16777216.0 * ((reach + 36.0) * sigma + (tau < 0.0 ? -tau : tau)) <= 0.5;
+}
+
 }  // namespace oat

@@ -249,6 +249,7 @@ struct Problem {
     // of a transducer sum to 1); point-like transducers: one node r_q, 1.
     const double4 *sph_pts;
     int sph_ns;
+    int fbp_held;          // fbp_window_holds: FBP's indices need no clamp
     double sph_rf;         // half diagonal of the faces (mm; 0 point-like)
     // Segment table (null when the plan has none): the segments of unit u
     // that hold points owned by the brick are entries seg_off[u] ..

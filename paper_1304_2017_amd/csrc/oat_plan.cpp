@@ -13,6 +13,7 @@
 #include "oat.h"
 #include "oat_internal.hpp"
 #include "oat_fbp_floor.hpp"
+#include "oat_fbp_window.hpp"
 #include "oat_geom.hpp"
 
 using namespace oat;
@@ -567,6 +568,11 @@ int oat_plan_create_ex(const oat_geometry *g, int device, const oat_plan_options
     P.t0 = (float)g->t0;
     P.dt = (float)g->dt;
     P.d_coef = (float)(g->gamma / (4.0 * M_PI * g->c0 * g->c0) / (2.0 * g->dt));
+    double reach = 0.0;   // grid units between a transducer and a voxel of a tile, per axis
+    for (const DetRec &d : det)
+        for (int a = 0; a < 3; ++a) reach = std::max(reach, std::fabs(d.uq[a]));
+    reach += std::max(g->nx, std::max(g->ny, g->nz)) + 16;
+    P.fbp_held = fbp_window_holds(reach, g->dx / (g->c0 * g->dt), g->t0 / g->dt) ? 1 : 0;
     P.fbp_scale = (float)(-1.0 / (M_PI * g->gamma * g->c0 * g->dt));
     P.sigma = (float)(dx / (g->c0 * g->dt));
     P.tau = (float)(g->t0 / g->dt);
