@@ -124,12 +124,11 @@ inline FwdGrid seg_fwd_grid(int nbricks, int nq, int window)
 // one box.
 //
 // Grids of at least 2048 workgroups keep whole windows (8 rounds and a short
-// tail).  Smaller ones halve the window down to 32 transducers until they
-// have 2048 (1024: 3% slower at 117 x 128 x 99 / 1000 BF16, 4096: 4%; 16
-// transducers: 6% slower on a 96^3 / 512 reconstruction), and on to single
-// transducers until every CU has a workgroup.  32^3 / 64: 910 -> 96 us;
-// 117 x 128 x 99 / 1000 BF16: 5.30 -> 4.60 ms; 90 x 120 x 200 / 360 ring
-// views: 6.35 -> 3.57 ms.
+// tail; from 1024 on: 3% slower at 117 x 128 x 99 / 1000 BF16).  Smaller ones take
+// half windows (quarters: 4% slower at 96^3 / 512, the same elsewhere), and go
+// on to single transducers until every CU has a workgroup.  32^3 / 64: 910 ->
+// 57 us; 117 x 128 x 99 / 1000 BF16: 5.30 -> 3.99 ms; 96^3 / 512: 1.88 -> 1.26 ms;
+// 90 x 120 x 200 / 360 ring views: 6.35 -> 3.28 ms.
 struct AdjGrid {
     int slices, per, parts;
 };
@@ -139,7 +138,7 @@ inline AdjGrid adj_grid(int nbricks, int nq)
     if ((long long)nbricks * sl >= 2048) return AdjGrid{sl, wps * ADJ_WINDOW, 1};
     int per = ADJ_WINDOW;
     auto grid = [&]() { return (long long)nbricks * ((nq + per - 1) / per); };
-    while (per > 32 && grid() < 2048) per /= 2;
+    while (per > 64 && grid() < 2048) per /= 2;
     while (per > 1 && grid() < 256) per /= 2;
     const int parts = per >= 64 ? 1 : (64 / per > 16 ? 16 : 64 / per);
     return AdjGrid{(nq + per - 1) / per, per, parts};
