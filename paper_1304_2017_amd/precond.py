@@ -132,18 +132,21 @@ class Preconditioner:
     def parameters(self) -> List[torch.Tensor]:
         return self.w + self.b
 
-    def _check_parameters(self):
-        shapes = [(self.CH, 1, 27), (self.CH, self.CH, 27), (1, self.CH, 27)]
-        for w, b, sh in zip(self.w, self.b, shapes):
-            if tuple(w.shape) != sh or w.dtype != torch.float32:
-                raise ValueError(f"weight must be float32 {list(sh)}, got {w.dtype} {tuple(w.shape)}")
-            if tuple(b.shape) != sh[:1] or b.dtype != torch.float32:
-                raise ValueError(f"bias must be float32 {list(sh[:1])}")
+    def _one_pass(self) -> bool:
+        """The parameters are what the whole-network calls are written for: FP32, 16 channels.
+        Others go layer by layer, which checks each layer's own."""
+        shapes = [(16, 1, 27), (16, 16, 27), (1, 16, 27)]
+        return len(self.w) == 3 and len(self.b) == 3 and all(
+            w.dtype == torch.float32 and tuple(w.shape) == sh and b is not None
+            and b.dtype == torch.float32 and tuple(b.shape) == sh[:1]
+            for w, b, sh in zip(self.w, self.b, shapes))
 
     def forward(self, x: torch.Tensor, keep: bool = False) -> torch.Tensor:
         """x: [D, H, W] -> z, same shape, in the storage dtype."""
-        if self.storage == torch.bfloat16:
-            return self._forward_bf16(x, keep)
+        if self.storage == torch.bfloat16 and self._one_pass():
+            d, h, w = x.shape
+            if oat.lib().oat_net_workspace(d, h, w, 0):
+                return self._forward_bf16(x, keep)
         x1 = x.to(self.storage).contiguous()[None]
         a1 = conv3d(x1, self.w[0], self.b[0], relu=True)
         a2 = conv3d(a1, self.w[1], self.b[1], relu=True)
@@ -155,9 +158,9 @@ class Preconditioner:
 
     def backward(self, dz: torch.Tensor):
         """Parameter gradients for dloss/dz (the last forward had keep=True)."""
-        if self.storage == torch.bfloat16:
-            return self._backward_bf16(dz)
         x1, a1, a2 = self._cache
+        if x1.dim() == 3:                             # kept by _forward_bf16
+            return self._backward_bf16(dz)
         d3 = dz.to(self.storage).contiguous()[None]
         dw3, db3 = conv3d_weight_grad(a2, d3)
         d2 = conv3d(d3, flip_transpose(self.w[2]), None, mask=a2)     # through relu(a2)
@@ -169,11 +172,10 @@ class Preconditioner:
     def _forward_bf16(self, x: torch.Tensor, keep: bool) -> torch.Tensor:
         """The layers in one library call; a1 and a2 are channel-last."""
         d, h, w = x.shape
-        self._check_parameters()
         L = oat.lib()
         x1 = x if x.dtype == torch.float32 and not keep else x.to(self.storage)
         x1 = x1.contiguous()
-        a1, a2 = (torch.empty((d, h, w, self.CH), device=x.device, dtype=self.storage)
+        a1, a2 = (torch.empty((d, h, w, 16), device=x.device, dtype=self.storage)
                   for _ in range(2))
         z = torch.empty((d, h, w), device=x.device, dtype=self.storage)
         ws = L.oat_net_workspace(d, h, w, 0)
@@ -190,7 +192,8 @@ class Preconditioner:
         d, h, w = x1.shape
         if tuple(dz.shape) != (d, h, w):
             raise ValueError(f"dz must have shape {(d, h, w)}, got {tuple(dz.shape)}")
-        self._check_parameters()
+        if not self._one_pass():
+            raise ValueError("the parameters are no longer those of the kept forward pass")
         L = oat.lib()
         dzc = dz.to(self.storage).contiguous()
         ws = L.oat_net_workspace(d, h, w, 1)
