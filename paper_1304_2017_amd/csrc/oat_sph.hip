@@ -379,56 +379,96 @@ __device__ __forceinline__ void sph_dist(double r2, double &d, double &rd)
 }
 
 // --- H_sph -----------------------------------------------------------------
-// hdr: number of listed voxels, bits of the largest |value|.
-__global__ void sph_list_init_kernel(int *hdr)
-{
-    if (threadIdx.x < 2) hdr[threadIdx.x] = 0;
-}
+// Voxels per block of the list, and values per thread of one.
+constexpr int SPH_LIST = 8 * SPH_THREADS;
 
-// The non-zero voxels n0 .. n1 - 1 as (ix, iy, iz, value bits), in any order.
-__global__ void __launch_bounds__(SPH_THREADS)
-sph_list_kernel(Problem P, const void *__restrict__ img, int img_dt, long long n0, long long n1,
-                int *__restrict__ hdr, int4 *__restrict__ list)
+// A thread's values of the block's voxels n0 .. n1 - 1; returns the block's
+// count of non-zero ones, and in wcnt each wave's.
+__device__ __forceinline__ int sph_block_values(const void *__restrict__ img, int img_dt, long long n0,
+                                                long long n1, float v[SPH_LIST / SPH_THREADS], int *wcnt)
 {
-    constexpr int PER = 8, NW = SPH_THREADS / 64;
-    __shared__ int wcnt[NW], base;
-    __shared__ unsigned wmax[NW];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const long long b0 = n0 + (long long)blockIdx.x * SPH_THREADS * PER;
-    float v[PER];
+    const int wave = threadIdx.x >> 6;
     int cnt = 0;
-    unsigned m = 0;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        const long long n = b0 + i * SPH_THREADS + threadIdx.x;
+    for (int i = 0; i < SPH_LIST / SPH_THREADS; ++i) {
+        const long long n = n0 + (long long)blockIdx.x * SPH_LIST + i * SPH_THREADS + threadIdx.x;
         v[i] = n < n1 ? load_val(img, (size_t)n, img_dt) : 0.f;
         cnt += __popcll(__ballot(v[i] != 0.f));
-        m = max(m, __float_as_uint(v[i]) & 0x7fffffffu);
     }
+    if ((threadIdx.x & 63) == 0) wcnt[wave] = cnt;
+    __syncthreads();
+    cnt = 0;
+    for (int w = 0; w < SPH_THREADS / 64; ++w) cnt += wcnt[w];
+    return cnt;
+}
+
+// blk[block] = (non-zero voxels, bits of the largest |value|) of the blocks of
+// the voxels n0 .. n1 - 1.
+__global__ void __launch_bounds__(SPH_THREADS)
+sph_count_kernel(const void *__restrict__ img, int img_dt, long long n0, long long n1,
+                 int2 *__restrict__ blk)
+{
+    __shared__ int wcnt[SPH_THREADS / 64];
+    __shared__ unsigned wmax[SPH_THREADS / 64];
+    float v[SPH_LIST / SPH_THREADS];
+    const int cnt = sph_block_values(img, img_dt, n0, n1, v, wcnt);
+    unsigned m = 0;
+#pragma unroll
+    for (int i = 0; i < SPH_LIST / SPH_THREADS; ++i) m = max(m, __float_as_uint(v[i]) & 0x7fffffffu);
     for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
-    if (lane == 0) {
-        wcnt[wave] = cnt;
-        wmax[wave] = m;
-    }
+    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) {
-        int tot = 0;
-        unsigned mm = 0;
-        for (int w = 0; w < NW; ++w) {
-            tot += wcnt[w];
-            mm = max(mm, wmax[w]);
-        }
-        base = tot ? atomicAdd(hdr, tot) : 0;
-        if (tot) atomicMax((unsigned *)hdr + 1, mm);
+        for (int w = 1; w < SPH_THREADS / 64; ++w) m = max(m, wmax[w]);
+        blk[blockIdx.x] = make_int2(cnt, (int)m);
     }
-    __syncthreads();
-    int pos = base;
+}
+
+// The non-zero voxels n0 .. n1 - 1 as (ix, iy, iz, value bits), block by block,
+// each block's in a fixed order: parts of the list, and their sums, are the
+// same on every call.  hdr: their number, bits of the largest |value|.
+__global__ void __launch_bounds__(SPH_THREADS)
+sph_list_kernel(Problem P, const void *__restrict__ img, int img_dt, long long n0, long long n1,
+                const int2 *__restrict__ blk, int *__restrict__ hdr, int4 *__restrict__ list)
+{
+    constexpr int NW = SPH_THREADS / 64;
+    __shared__ int wcnt[NW], wsum[NW];
+    __shared__ unsigned wmax[NW];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // the blocks before this one (the last block looks at all of them)
+    const int upto = blockIdx.x + 1 < gridDim.x ? blockIdx.x : gridDim.x;
+    int before = 0;
+    unsigned m = 0;
+    for (int i = threadIdx.x; i < upto; i += SPH_THREADS) {
+        const int2 c = blk[i];
+        before += i < (int)blockIdx.x ? c.x : 0;
+        m = max(m, (unsigned)c.y);
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        before += __shfl_xor(before, o);
+        m = max(m, (unsigned)__shfl_xor((int)m, o));
+    }
+    if (lane == 0) {
+        wsum[wave] = before;
+        wmax[wave] = m;
+    }
+    float v[SPH_LIST / SPH_THREADS];
+    const int cnt = sph_block_values(img, img_dt, n0, n1, v, wcnt);
+    int pos = 0;
+    for (int w = 0; w < NW; ++w) {
+        pos += wsum[w];
+        m = max(m, wmax[w]);
+    }
+    if (blockIdx.x + 1 == gridDim.x && threadIdx.x == 0) {
+        hdr[0] = pos + cnt;
+        hdr[1] = (int)m;
+    }
     for (int w = 0; w < wave; ++w) pos += wcnt[w];
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
+    for (int i = 0; i < SPH_LIST / SPH_THREADS; ++i) {
         const uint64_t bal = __ballot(v[i] != 0.f);
         if (v[i] != 0.f) {
-            const long long n = b0 + i * SPH_THREADS + threadIdx.x;
+            const long long n = n0 + (long long)blockIdx.x * SPH_LIST + i * SPH_THREADS + threadIdx.x;
             const long long xy = (long long)P.nx * P.ny;
             const int iz = (int)(n / xy), r = (int)(n - iz * xy), iy = r / P.nx;
             list[pos + __popcll(bal & ((1ull << lane) - 1ull))] =
@@ -450,7 +490,7 @@ __device__ __forceinline__ int sph_parts(long long n, int parts, int fixed)
 // (blockIdx.y of sph_parts): M[part][q][i][m] = sum over the (voxel, face
 // node) terms in interval i of w t^m, w = value x node weight / (2 pi d),
 // added to the earlier contents if `add`.  The LDS sums are 64-bit integers,
-// so they do not depend on the order of the list: every |w t^m| is below
+// so they do not depend on the order of a part's terms: every |w t^m| is below
 // 2^k / S with k + log2(terms) <= 62, k <= 50 (adding 1.5 2^52 rounds a term
 // to an integer in the low bits).  A value that is not finite makes the
 // moments NaN.
@@ -907,12 +947,18 @@ static bool sph_adj_fast(const Problem &P, int n_f, double f_min, double df, Sph
     return B.n_want * n_f * 18 + terms * 40 < terms * (4.0 * n_f + 100);
 }
 
+// The list's header (256 bytes) and its blocks' counts.
+static size_t sph_list_bytes(long long N)
+{
+    return 256 + (sizeof(int2) * (size_t)((std::min(N, SPH_PASS) + SPH_LIST - 1) / SPH_LIST) + 255) / 256 * 256;
+}
+
 size_t sph_workspace_bytes(const Problem &P, int n_f, double f_min, double df)
 {
     SphBand B;
     if (!sph_fwd_fast(P, n_f, f_min, df, B)) return sizeof(double2) * (size_t)SPH_CHUNKS * P.nq * n_f;
     const long long N = (long long)P.nx * P.ny * P.nz;
-    return 256 + sizeof(int4) * (size_t)std::min(N, SPH_PASS) +
+    return sph_list_bytes(N) + sizeof(int4) * (size_t)std::min(N, SPH_PASS) +
            sizeof(double) * SPH_M * (size_t)sph_moment_parts(P) * P.nq * B.n;
 }
 
@@ -923,14 +969,16 @@ hipError_t launch_sph_project(const Problem &P, const void *img, int img_dt, flo
     SphBand B;
     if (sph_fwd_fast(P, n_f, f_min, df, B)) {
         int *hdr = (int *)part;
-        int4 *list = (int4 *)((char *)part + 256);
+        int2 *blk = (int2 *)((char *)part + 256);
+        int4 *list = (int4 *)((char *)part + sph_list_bytes(N));
         double *M = (double *)(list + std::min(N, SPH_PASS));
         const int parts = sph_moment_parts(P);
         for (long long n0 = 0; n0 < N; n0 += SPH_PASS) {
             const long long n1 = std::min(N, n0 + SPH_PASS);
-            hipLaunchKernelGGL(sph_list_init_kernel, dim3(1), dim3(64), 0, s, hdr);
-            hipLaunchKernelGGL(sph_list_kernel, dim3((unsigned)((n1 - n0 + 8 * SPH_THREADS - 1) / (8 * SPH_THREADS))),
-                               dim3(SPH_THREADS), 0, s, P, img, img_dt, n0, n1, hdr, list);
+            const dim3 blocks((unsigned)((n1 - n0 + SPH_LIST - 1) / SPH_LIST)), threads(SPH_THREADS);
+            hipLaunchKernelGGL(sph_count_kernel, blocks, threads, 0, s, img, img_dt, n0, n1, blk);
+            hipLaunchKernelGGL(sph_list_kernel, blocks, threads, 0, s, P, img, img_dt, n0, n1, blk, hdr,
+                               list);
             hipLaunchKernelGGL(sph_moment_kernel, dim3(P.nq, parts), dim3(SPH_MTHREADS),
                                sizeof(unsigned long long) * SPH_MROW * B.n, s, P, B, list, hdr, M,
                                n0 > 0 ? 1 : 0, N > SPH_PASS ? 1 : 0);
