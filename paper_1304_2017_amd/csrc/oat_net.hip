@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <cmath>
 #include <string>
+#include <type_traits>
 
 #include "oat.h"
 #include "oat_cnn.h"
@@ -57,10 +58,24 @@ __device__ __forceinline__ unsigned split_term(float w, int s)
     unsigned b = f_bf(w);
     for (int i = 0; i < s; ++i) {
         const float r = w - bf_f(b);
-        w = fabsf(w) <= 3.4e38f ? r : 0.f;   // a non-finite weight has no remainder
+        w = fabsf(r) <= 3.4028235e38f ? r : 0.f;   // no remainder of a first term that is not finite
         b = f_bf(w);
     }
     return b;
+}
+
+// Infinities in a product with a split weight's terms, or with the zeros in
+// unused slots, give NaN where the product with the weight itself is an
+// infinity.  So where values or weights are large enough for that, or not
+// finite, the product with the first terms alone is formed too and stands for
+// the results that it does not leave finite.
+constexpr float LARGE_VALUE = 0x1p90f, LARGE_WEIGHT = 0x1p30f;
+constexpr unsigned LARGE_BITS = 0x6c80;   // LARGE_VALUE as BF16
+__device__ __forceinline__ f32x4 first_if_not_finite(f32x4 first, f32x4 all)
+{
+#pragma unroll
+    for (int r = 0; r < 4; ++r) all[r] = fabsf(first[r]) <= 3.4028235e38f ? all[r] : first[r];
+    return all;
 }
 
 // One-channel input value as FP32, then BF16 bits (FP32 inputs are rounded).
@@ -72,7 +87,8 @@ __device__ __forceinline__ unsigned in_bits(const void *x, size_t i, int dt)
 // ---------------------------------------------------------------------------
 // 16 -> 16: weight fragments.  The taps of a row dy come as 5 k-blocks of two
 // taps: (dz, dx = 0 | dx = 1) for dz = 0, 1, 2, then dx = 2 of dz = 0 | 1 and of
-// dz = 2 | nothing.  k slot 8 (g & 1) + j of tap half g >> 1 is channel
+// dz = 2 twice, with half the weight each (exact; a zero weight would turn an
+// infinity into NaN).  k slot 8 (g & 1) + j of tap half g >> 1 is channel
 // 8 (g & 1) + j.  frag[dy * 5 + f][lane], row (output channel) lane % 16.
 // ---------------------------------------------------------------------------
 constexpr int NFRAG = 15;
@@ -84,7 +100,7 @@ __device__ __forceinline__ void block_tap(int f, int half, int &dz, int &dx)
         dx = half;
     } else {
         dz = f == 3 ? half : 2;
-        dx = (f == 4 && half) ? -1 : 2;   // -1: no tap
+        dx = 2;
     }
 }
 
@@ -97,14 +113,12 @@ __device__ void write_fragments(const float *__restrict__ w, int flip, u32x4 *__
         int dz, dx;
         block_tap(f, g >> 1, dz, dx);
         u32x4 v = {0u, 0u, 0u, 0u};
-        if (dx >= 0) {
-            const int t = 9 * dz + 3 * dy + dx;
+        const int t = 9 * dz + 3 * dy + dx;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int ci = 8 * (g & 1) + j;
-                const float a = flip ? w[(ci * 16 + co) * 27 + 26 - t] : w[(co * 16 + ci) * 27 + t];
-                v[j >> 1] |= f_bf(a) << (16 * (j & 1));
-            }
+        for (int j = 0; j < 8; ++j) {
+            const int ci = 8 * (g & 1) + j;
+            const float a = flip ? w[(ci * 16 + co) * 27 + 26 - t] : w[(co * 16 + ci) * 27 + t];
+            v[j >> 1] |= f_bf(f == 4 ? 0.5f * a : a) << (16 * (j & 1));
         }
         frag[e] = v;
     }
@@ -158,8 +172,12 @@ net_c1_kernel(const void *__restrict__ x, int xdt, int D, int H, int W, const fl
 {
     constexpr int C1HZ = C1Z + 2;
     __shared__ u16 xs[C1HZ * C1HY * C1P];
+    __shared__ int wave_large[C1_THREADS / 64];
+    static_assert(C1_THREADS / 64 == 4, "wave_large");
     const int x0 = blockIdx.x * C1X, y0 = blockIdx.y * C1Y, z0 = blockIdx.z * C1Z;
     const size_t plane = (size_t)H * W;
+    unsigned top = 0;   // the largest |value| of this thread's, as bits
+    bool large = false;
     for (int r = threadIdx.x >> 5; r < C1HZ * C1HY; r += C1_THREADS / 32) {
         const int gy = y0 - 1 + r % C1HY, gz = z0 - 1 + r / C1HY;
         const bool in = gy >= 0 && gy < H && gz >= 0 && gz < D;
@@ -167,7 +185,9 @@ net_c1_kernel(const void *__restrict__ x, int xdt, int D, int H, int W, const fl
 #pragma unroll
         for (int xx = threadIdx.x & 31; xx < C1X + 2; xx += 32) {
             const int gx = x0 - 1 + xx;
-            xs[r * C1P + xx] = (in && gx >= 0 && gx < W) ? (u16)in_bits(x, row + gx, xdt) : (u16)0;
+            const unsigned v = (in && gx >= 0 && gx < W) ? in_bits(x, row + gx, xdt) : 0u;
+            xs[r * C1P + xx] = (u16)v;
+            top = max(top, v & 0x7fffu);
         }
     }
     const int wave = wave_index(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
@@ -181,6 +201,7 @@ net_c1_kernel(const void *__restrict__ x, int xdt, int D, int H, int W, const fl
         off[j] = ((tt / 9) * C1HY + (tt / 3) % 3) * C1P + tt % 3 + col;
         if (t < 27) {
             const float f = w[col * 27 + (flip ? 26 - t : t)];
+            large |= !(fabsf(f) < LARGE_WEIGHT);
 #pragma unroll
             for (int s = 0; s < 3; ++s) a[s][j >> 1] |= split_term(f, s) << (16 * (j & 1));
         }
@@ -188,25 +209,38 @@ net_c1_kernel(const void *__restrict__ x, int xdt, int D, int H, int W, const fl
     f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
     if (bias) b4 = *reinterpret_cast<const f32x4 *>(bias + 4 * g);
     if (frag && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) write_fragments(w16, flip, frag);
+    const uint64_t lanes = __ballot(large || top >= LARGE_BITS);
+    if (lane == 0) wave_large[wave] = lanes != 0;
     __syncthreads();
+    large = wave_large[0] | wave_large[1] | wave_large[2] | wave_large[3];
     const unsigned vo = (unsigned)col * 16 + 4 * g;   // the lane's offset in a group's row
-    for (int lz = wave; lz < C1Z && z0 + lz < D; lz += C1_THREADS / 64) {
+    // group k of the plane's 16 groups of 16 voxels along x
+    auto group = [&](int lz, int k, auto with_large) {
         const u16 *__restrict__ xz = xs + lz * C1HY * C1P;
-        // 16 groups of 16 voxels along x
+        const int ly = k >> 1, lx = (k & 1) * 16;
+        u32x4 v;
 #pragma unroll
-        for (int k = 0; k < 2 * C1Y; ++k) {
-            const int ly = k >> 1, lx = (k & 1) * 16;
-            u32x4 v;
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                v[j] = (unsigned)xz[ly * C1P + lx + off[2 * j]] |
-                       ((unsigned)xz[ly * C1P + lx + off[2 * j + 1]] << 16);
-            f32x4 acc = mfma(a[2], v, b4);
-            acc = mfma(a[1], v, acc);
-            acc = mfma(a[0], v, acc);
-            const size_t row = ((z0 + lz) * plane + (size_t)(y0 + ly) * W + x0 + lx) * 16;
-            if (y0 + ly < H && x0 + lx + col < W) store4(y + row, vo, acc, relu, mask ? mask + row : nullptr);
+        for (int j = 0; j < 4; ++j)
+            v[j] = (unsigned)xz[ly * C1P + lx + off[2 * j]] |
+                   ((unsigned)xz[ly * C1P + lx + off[2 * j + 1]] << 16);
+        f32x4 acc = mfma(a[2], v, b4);
+        acc = mfma(a[1], v, acc);
+        acc = mfma(a[0], v, acc);
+        if (decltype(with_large)::value) {
+            if (g == 3) v = u32x4{v[0], v[1] & 0xffffu, 0u, 0u};   // (slots past tap 26)
+            acc = first_if_not_finite(mfma(a[0], v, b4), acc);
         }
+        const size_t row = ((z0 + lz) * plane + (size_t)(y0 + ly) * W + x0 + lx) * 16;
+        if (y0 + ly < H && x0 + lx + col < W) store4(y + row, vo, acc, relu, mask ? mask + row : nullptr);
+    };
+    if (__builtin_amdgcn_readfirstlane(large)) {
+        for (int i = wave; i < C1Z * 2 * C1Y; i += C1_THREADS / 64)
+            if (z0 + i / (2 * C1Y) < D) group(i / (2 * C1Y), i % (2 * C1Y), std::true_type());
+        return;
+    }
+    for (int lz = wave; lz < C1Z && z0 + lz < D; lz += C1_THREADS / 64) {
+#pragma unroll
+        for (int k = 0; k < 2 * C1Y; ++k) group(lz, k, std::false_type());
     }
 }
 
@@ -333,6 +367,7 @@ net_c3_kernel(const u16 *__restrict__ a, const void *__restrict__ x, int xdt, in
     const int wave = wave_index(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     // weights: [tap tile][terms 1 and 2 | term 3]
     u32x4 wt[2][2];
+    bool large_w = false;
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
@@ -341,9 +376,11 @@ net_c3_kernel(const u16 *__restrict__ a, const void *__restrict__ x, int xdt, in
             const int t = 16 * m + col;
             if (t < 27 && (p == 0 || g < 2))
 #pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    wt[m][p][j >> 1] |= split_term(w[(8 * (g & 1) + j) * 27 + t], p == 0 ? g >> 1 : 2)
-                                        << (16 * (j & 1));
+                for (int j = 0; j < 8; ++j) {
+                    const float f = w[(8 * (g & 1) + j) * 27 + t];
+                    large_w |= !(fabsf(f) < LARGE_WEIGHT);
+                    wt[m][p][j >> 1] |= split_term(f, p == 0 ? g >> 1 : 2) << (16 * (j & 1));
+                }
         }
     // this wave's halo voxels: groups wave, wave + 8, ...
     int idx[C3GW];        // offset in the plane, -1 outside the volume
@@ -367,8 +404,17 @@ net_c3_kernel(const u16 *__restrict__ a, const void *__restrict__ x, int xdt, in
                 v[k] = *reinterpret_cast<const u32x4 *>(a + (zi * plane + idx[k]) * 16 + (g & 1) * 8);
         }
     };
+    auto put = [&](int grp, f32x4 r0, f32x4 r1) {
+        float *dst = ys + grp * 16 + col;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            dst[(4 * g + r) * C3P] = r0[r];
+            if (16 + 4 * g + r < 27) dst[(16 + 4 * g + r) * C3P] = r1[r];
+        }
+    };
     load(z0 - 1);
     for (int zi = z0 - 1; zi <= z1; ++zi) {
+        bool large = large_w;
 #pragma unroll
         for (int k = 0; k < C3GW; ++k) {
             const int grp = wave + k * C3_WAVES;
@@ -378,11 +424,21 @@ net_c3_kernel(const u16 *__restrict__ a, const void *__restrict__ x, int xdt, in
             r1 = mfma(wt[1][1], v[k], r1);
             r0 = mfma(wt[0][0], v[k], r0);
             r1 = mfma(wt[1][0], v[k], r1);
-            float *dst = ys + grp * 16 + col;
+            large |= !(fabsf(r0[0]) < LARGE_VALUE);   // (a value that large makes every row so)
+            put(grp, r0, r1);
+        }
+        if (__any(large)) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                dst[(4 * g + r) * C3P] = r0[r];
-                if (16 + 4 * g + r < 27) dst[(16 + 4 * g + r) * C3P] = r1[r];
+            for (int k = 0; k < C3GW; ++k) {
+                const int grp = wave + k * C3_WAVES;
+                if (grp >= C3G) break;
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+                const u32x4 first = g < 2 ? v[k] : u32x4{0u, 0u, 0u, 0u};
+                f32x4 r0 = mfma(wt[0][0], v[k], mfma(wt[0][1], v[k], zero));
+                f32x4 r1 = mfma(wt[1][0], v[k], mfma(wt[1][1], v[k], zero));
+                r0 = first_if_not_finite(mfma(wt[0][0], first, zero), r0);
+                r1 = first_if_not_finite(mfma(wt[1][0], first, zero), r1);
+                put(grp, r0, r1);
             }
         }
         if (zi < z1) load(zi + 1);   // in flight while the sums run
@@ -529,6 +585,27 @@ net_wgrad16_kernel(const u16 *__restrict__ x, const u16 *__restrict__ dy, int D,
     }
 }
 
+// sum_v s[v][ch] t[v + tap] over a workgroup's tiles, both voxels inside the
+// volume; ends at the first NaN.
+__device__ __attribute__((noinline)) float pair_sum(const u16 *__restrict__ sv, const u16 *__restrict__ tv,
+                                                    int D, int H, int W, int tx, int ty, int tiles, int ch,
+                                                    int tap)
+{
+    float sum = 0.f;
+    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+        int x0, y0, z0;
+        tile_origin(tile, tx, ty, x0, y0, z0);
+        for (int v = 0; v < GV && sum == sum; ++v) {
+            const int gx = x0 + v % GX, gy = y0 + v / GX % GY, gz = z0 + v / (GX * GY);
+            const int px = gx + tap % 3 - 1, py = gy + tap / 3 % 3 - 1, pz = gz + tap / 9 - 1;
+            if (gx < W && gy < H && gz < D && px >= 0 && px < W && py >= 0 && py < H && pz >= 0 && pz < D)
+                sum = fmaf(bf_f(sv[(((size_t)gz * H + gy) * W + gx) * 16 + ch]),
+                           bf_f(tv[((size_t)pz * H + py) * W + px]), sum);
+        }
+    }
+    return sum;
+}
+
 // One-channel layers: P[ch][tap] = sum_v s[v][ch] t[v + tap].  C1: s = dy, t = x
 // (with the bias, sum_v s[v][ch], as tap 27); C3: s = x, t = dy and tap 26 - tap
 // (with the bias, sum_v t[v]).  A: rows = taps, from three copies of t's tile
@@ -620,7 +697,10 @@ net_wgrad1_kernel(const u16 *__restrict__ sv, const u16 *__restrict__ tv, int D,
     for (int i = threadIdx.x; i < 512; i += G_THREADS) {
         const int r = i & 3, l = (i >> 2) & 63, m = i >> 8;
         const int t = 16 * m + 4 * (l >> 4) + r, ch = l & 15;
-        const float v = (red[0][m][l][r] + red[1][m][l][r]) + (red[2][m][l][r] + red[3][m][l][r]);
+        float v = (red[0][m][l][r] + red[1][m][l][r]) + (red[2][m][l][r] + red[3][m][l][r]);
+        // an infinite activation times the zeros around t is no part of C3's sum
+        if (C3 && t < 27 && !(fabsf(v) <= 3.4028235e38f))
+            v = pair_sum(sv, tv, D, H, W, tx, ty, tiles, ch, t);
         if (t < 27)
             dst[ch * 27 + (C3 ? 26 - t : t)] = v;
         else if (!C3 && t == 27)
