@@ -112,6 +112,7 @@ inline FwdGrid seg_fwd_grid(int nbricks, int nq, int window)
     const long long units = (long long)nbricks * nq;
     const long long want = std::max(std::min(units / 256, 64ll), units / 2816);
     const int per = want < 1 ? 1 : (want > fit ? fit : (int)want);
+    if ((nq + per - 1) / per > 65535) return FwdGrid{sl, (nq + sl - 1) / sl, 0};   // a grid's limit in y
     const int parts = 96 / per;
     return FwdGrid{(nq + per - 1) / per, per, parts > 16 ? 16 : parts};
 }
@@ -126,9 +127,12 @@ inline FwdGrid seg_fwd_grid(int nbricks, int nq, int window)
 // Grids of at least 2048 workgroups keep whole windows (8 rounds and a short
 // tail; from 1024 on: 3% slower at 117 x 128 x 99 / 1000 BF16).  Smaller ones take
 // half windows (quarters: 4% slower at 96^3 / 512, the same elsewhere), and go
-// on to single transducers until every CU has a workgroup.  32^3 / 64: 910 ->
-// 57 us; 117 x 128 x 99 / 1000 BF16: 5.30 -> 3.99 ms; 96^3 / 512: 1.88 -> 1.26 ms;
-// 90 x 120 x 200 / 360 ring views: 6.35 -> 3.28 ms.
+// on to single transducers until every CU has a workgroup; where many
+// transducers would make more than 8192 workgroups (each has brick sums of 85 KB:
+// 0.7 GB) they take several windows (a limit of 4096 workgroups: 1.5% slower at
+// 96^3 / 8192 and 117 x 128 x 99 / 4096).  32^3 / 64: 910 -> 57 us; 117 x 128 x
+// 99 / 1000 BF16: 5.30 -> 3.99 ms; 96^3 / 512: 1.88 -> 1.26 ms; 90 x 120 x 200 /
+// 360 ring views: 6.35 -> 3.28 ms.
 struct AdjGrid {
     int slices, per, parts;
 };
@@ -136,7 +140,9 @@ inline AdjGrid adj_grid(int nbricks, int nq)
 {
     const int sl = adj_slices(nbricks, nq), nwin = adj_windows(nq), wps = (nwin + sl - 1) / sl;
     if ((long long)nbricks * sl >= 2048) return AdjGrid{sl, wps * ADJ_WINDOW, 1};
-    int per = ADJ_WINDOW;
+    int many = (int)(((long long)nbricks * nwin + 8191) / 8192);
+    while ((long long)nbricks * ((nwin + many - 1) / many) > 8192) ++many;
+    int per = many * ADJ_WINDOW;
     auto grid = [&]() { return (long long)nbricks * ((nq + per - 1) / per); };
     while (per > 64 && grid() < 2048) per /= 2;
     while (per > 1 && grid() < 256) per /= 2;
