@@ -61,6 +61,7 @@ constexpr int SPH_P = 8;         // polynomial coefficients per interval (adjoin
 constexpr int SPH_M = 6;         // moments per interval (forward)
 constexpr int SPH_MROW = 7;      // 64-bit words per interval of moments in LDS (odd: spreads banks)
 constexpr int SPH_MTHREADS = 1024;
+constexpr int SPH_RUN = 1 << 20;         // terms summed in integers at a time
 constexpr int SPH_TX = 16, SPH_TZ = 8;   // voxel tile of the table adjoint: 16 x 16 x 8
 constexpr int SPH_TVOX = SPH_TX * SPH_TX * SPH_TZ;
 constexpr int SPH_STAGE = 40960;         // bytes of staged polynomials: 4 workgroups per CU
@@ -490,10 +491,13 @@ __device__ __forceinline__ int sph_parts(long long n, int parts, int fixed)
 // (blockIdx.y of sph_parts): M[part][q][i][m] = sum over the (voxel, face
 // node) terms in interval i of w t^m, w = value x node weight / (2 pi d),
 // added to the earlier contents if `add`.  The LDS sums are 64-bit integers,
-// so they do not depend on the order of a part's terms: every |w t^m| is below
+// so they do not depend on the order of a run's terms: every |w t^m| is below
 // 2^k / S with k + log2(terms) <= 62, k <= 50 (adding 1.5 2^52 rounds a term
-// to an integer in the low bits).  A value that is not finite makes the
-// moments NaN.
+// to an integer in the low bits).  A run is at most SPH_RUN terms, so k >= 42
+// whatever the image: the runs are added in FP64, and the roundings of N terms
+// together stay near sqrt(N) 2^-43 of the largest, 3e-9 of the output for 2^30
+// terms of which one is large (all of them in one run: 1e-5).  A value that
+// is not finite makes the moments NaN.
 // Bound by the LDS atomics, SPH_M a term at about 12 cycles per wave (two
 // thirds of it bank conflicts of random intervals).
 __global__ void __launch_bounds__(SPH_MTHREADS)
@@ -507,9 +511,8 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
     const int parts = sph_parts((long long)total * NS, gridDim.y, fixed);
     if ((int)blockIdx.y >= parts) return;
     const int len = (total + parts - 1) / parts;
-    const int i1 = min(total, (int)(blockIdx.y + 1) * len);
-    for (int j = threadIdx.x; j < B.n * SPH_MROW; j += SPH_MTHREADS) mom[j] = 0ull;
-    __syncthreads();
+    const int i0 = (int)blockIdx.y * len, i1 = min(total, i0 + len);
+    const int run = min(max(len, 1), SPH_RUN / NS);
     const int first = sph_first(P, B, q);
     const bool bad = amax >= 0x7f800000u;
     // |w| <= |value| / (2 pi d), d >= the transducer's distance - reach
@@ -517,43 +520,48 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
     const double dmin = sqrt(fma(z, z, fma(y, y, x * x))) - B.reach;
     int e = 0;
     (void)frexp((double)__uint_as_float(amax) / (6.283185307179586 * dmin), &e);
-    int kb = 62 - (32 - __clz(max(len, 1) - 1)) - (32 - __clz(NS));
-    kb = min(kb, 50) - e;
+    const int kb = min(62 - (32 - __clz(run * NS - 1)), 50) - e;
     const double S = ldexp(1.0, kb);
     const double unscale = bad ? __longlong_as_double(0x7ff8000000000000ll) : ldexp(1.0, -kb);
     const double ws = S / 6.283185307179586;
-    for (int idx = (int)blockIdx.y * len + threadIdx.x; idx < i1; idx += SPH_MTHREADS) {
-        const int4 en = list[idx];
-        const double vx = fma((double)en.x, P.dxd, P.x0), vy = fma((double)en.y, P.dxd, P.y0),
-                     vz = fma((double)en.z, P.dxd, P.z0);
-        const double av = (double)__uint_as_float((unsigned)en.w) * ws;
-        for (int fs = 0; fs < NS; ++fs) {
-            const double4 fp = P.sph_pts[(size_t)q * NS + fs];
-            const double dx = vx - fp.x, dy = vy - fp.y, dz = vz - fp.z;
-            double d, rd;
-            sph_dist(fma(dz, dz, fma(dy, dy, dx * dx)), d, rd);
-            const double sp = d * B.inv, k = rint(sp), t = sp - k;
-            // (in range by the triangle inequality; the minimum keeps the
-            // LDS access inside the rows whatever the values are)
-            const unsigned i = min((unsigned)((int)k - first), (unsigned)(B.n - 1));
-            unsigned long long *row = mom + i * SPH_MROW;
-            double v = av * (fp.w * rd);
+    double *dst = M + ((size_t)blockIdx.y * P.nq + q) * B.n * SPH_M;
+    for (int r0 = i0; r0 == i0 || r0 < i1; r0 += run) {
+        const int r1 = min(i1, r0 + run);
+        for (int j = threadIdx.x; j < B.n * SPH_MROW; j += SPH_MTHREADS) mom[j] = 0ull;
+        __syncthreads();
+        for (int idx = r0 + threadIdx.x; idx < r1; idx += SPH_MTHREADS) {
+            const int4 en = list[idx];
+            const double vx = fma((double)en.x, P.dxd, P.x0), vy = fma((double)en.y, P.dxd, P.y0),
+                         vz = fma((double)en.z, P.dxd, P.z0);
+            const double av = (double)__uint_as_float((unsigned)en.w) * ws;
+            for (int fs = 0; fs < NS; ++fs) {
+                const double4 fp = P.sph_pts[(size_t)q * NS + fs];
+                const double dx = vx - fp.x, dy = vy - fp.y, dz = vz - fp.z;
+                double d, rd;
+                sph_dist(fma(dz, dz, fma(dy, dy, dx * dx)), d, rd);
+                const double sp = d * B.inv, k = rint(sp), t = sp - k;
+                // (in range by the triangle inequality; the minimum keeps the
+                // LDS access inside the rows whatever the values are)
+                const unsigned i = min((unsigned)((int)k - first), (unsigned)(B.n - 1));
+                unsigned long long *row = mom + i * SPH_MROW;
+                double v = av * (fp.w * rd);
 #pragma unroll
-            for (int m = 0; m < SPH_M; ++m) {
-                // the magic constant's low word is zero: one 32-bit subtract
-                const long long bits = __double_as_longlong(v + 0x1.8p52);
-                const unsigned hi = (unsigned)(bits >> 32) - 0x43380000u;
-                atomicAdd(row + m, ((unsigned long long)hi << 32) | (unsigned)bits);
-                v *= t;
+                for (int m = 0; m < SPH_M; ++m) {
+                    // the magic constant's low word is zero: one 32-bit subtract
+                    const long long bits = __double_as_longlong(v + 0x1.8p52);
+                    const unsigned hi = (unsigned)(bits >> 32) - 0x43380000u;
+                    atomicAdd(row + m, ((unsigned long long)hi << 32) | (unsigned)bits);
+                    v *= t;
+                }
             }
         }
-    }
-    __syncthreads();
-    double *dst = M + ((size_t)blockIdx.y * P.nq + q) * B.n * SPH_M;
-    for (int j = threadIdx.x; j < B.n * SPH_M; j += SPH_MTHREADS) {
-        const int i = j / SPH_M;
-        const double v = (double)(long long)mom[i * (SPH_MROW - SPH_M) + j] * unscale;
-        dst[j] = add ? dst[j] + v : v;
+        __syncthreads();
+        for (int j = threadIdx.x; j < B.n * SPH_M; j += SPH_MTHREADS) {
+            const int i = j / SPH_M;
+            const double v = (double)(long long)mom[i * (SPH_MROW - SPH_M) + j] * unscale;
+            dst[j] = add || r0 > i0 ? dst[j] + v : v;
+        }
+        __syncthreads();
     }
 }
 
