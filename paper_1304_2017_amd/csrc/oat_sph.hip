@@ -12,9 +12,9 @@
 // moments per interval and transforms those; H_sph^T tabulates each
 // transducer's function as FP32 polynomials and evaluates one per (voxel,
 // transducer).  The polynomials' errors, as a share of a term, stay below
-// 4e-8 rms over the band (H_sph, degree 5; about 1e-8 of the output, whose
-// rounding to FP32 is 2.5e-8) and 7e-9 (H_sph^T, degree 7, whose tables are
-// rounded to FP32).  Measured at 64^3 / 2048 transducers / 256
+// 4e-8 rms over the band (H_sph, degree 5; 1 to 2e-8 of the output, whose
+// rounding to FP32 is 2.5e-8; degree 7 where the plain sums have no other error
+// than that) and 7e-9 (H_sph^T, degree 7, whose tables are rounded to FP32).  Measured at 64^3 / 2048 transducers / 256
 // frequencies against the plain sums: H_sph of an iterate 29.0 -> 1.55 ms, of
 // a phantom (4.7% of its voxels set) 1.29 -> 0.30 ms, H_sph^T 18.2 -> 0.76 ms.
 //
@@ -58,8 +58,10 @@ constexpr int SPH_ANCHOR = 16;   // frequencies per Horner block (adjoint)
 constexpr int SPH_VQ = 4096;     // staged u p0* values per adjoint tile (32 KB: 4 groups per CU)
 constexpr int SPH_NV = 2;        // consecutive voxels per adjoint thread
 constexpr int SPH_P = 8;         // polynomial coefficients per interval (adjoint)
-constexpr int SPH_M = 6;         // moments per interval (forward)
-constexpr int SPH_MROW = 7;      // 64-bit words per interval of moments in LDS (odd: spreads banks)
+constexpr int SPH_M = 6;         // moments per interval (forward): 6, or
+constexpr int SPH_M8 = 8;        // 8 where the plain sums have no error but rounding
+// 64-bit words per interval of moments in LDS (odd: spreads banks)
+constexpr int sph_mrow(int m) { return m + 1; }
 constexpr int SPH_MTHREADS = 1024;
 constexpr int SPH_RUN = 1 << 20;         // terms summed in integers at a time
 constexpr int SPH_TX = 16, SPH_TZ = 8;   // voxel tile of the table adjoint: 16 x 16 x 8
@@ -370,13 +372,17 @@ __device__ __forceinline__ void sph_basis(const SphBand &B, double f, double a[N
 }
 
 // Distance d and its reciprocal from the squared distance: the FP32
-// reciprocal square root with one FP64 Newton step (relative error ~1e-14).
+// reciprocal square root and one FP64 step, the series of (1 - 2 e)^(-1/2),
+// e < 2e-7, to e^2 (FULL: to the last places of FP64) or to e (1e-14, where the
+// position in the interval is rounded to FP32 next; FULL there: 784 us for 755 at
+// 64^3 / 2048 / 256).
+template <bool FULL>
 __device__ __forceinline__ void sph_dist(double r2, double &d, double &rd)
 {
     const double y = (double)__builtin_amdgcn_rsqf((float)r2);
-    const double p = r2 * y, e = fma(-p, 0.5 * y, 0.5);
-    d = fma(p, e, p);
-    rd = fma(y, e, y);
+    const double p = r2 * y, e = fma(-p, 0.5 * y, 0.5), c = FULL ? fma(1.5 * e, e, e) : e;
+    d = fma(p, c, p);
+    rd = fma(y, c, y);
 }
 
 // --- H_sph -----------------------------------------------------------------
@@ -498,13 +504,15 @@ __device__ __forceinline__ int sph_parts(long long n, int parts, int fixed)
 // together stay near sqrt(N) 2^-43 of the largest, 3e-9 of the output for 2^30
 // terms of which one is large (all of them in one run: 1e-5).  A value that
 // is not finite makes the moments NaN.
-// Bound by the LDS atomics, SPH_M a term at about 12 cycles per wave (two
+// Bound by the LDS atomics, NM a term at about 12 cycles per wave (two
 // thirds of it bank conflicts of random intervals).
+template <int NM>
 __global__ void __launch_bounds__(SPH_MTHREADS)
 sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int *__restrict__ hdr,
                   double *__restrict__ M, int add, int fixed)
 {
-    extern __shared__ unsigned long long mom[];   // [n][SPH_MROW]
+    constexpr int MROW = sph_mrow(NM);
+    extern __shared__ unsigned long long mom[];   // [n][MROW]
     const int q = blockIdx.x, NS = P.sph_ns;
     const int total = hdr[0];
     const unsigned amax = (unsigned)hdr[1];
@@ -524,10 +532,10 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
     const double S = ldexp(1.0, kb);
     const double unscale = bad ? __longlong_as_double(0x7ff8000000000000ll) : ldexp(1.0, -kb);
     const double ws = S / 6.283185307179586;
-    double *dst = M + ((size_t)blockIdx.y * P.nq + q) * B.n * SPH_M;
+    double *dst = M + ((size_t)blockIdx.y * P.nq + q) * B.n * NM;
     for (int r0 = i0; r0 == i0 || r0 < i1; r0 += run) {
         const int r1 = min(i1, r0 + run);
-        for (int j = threadIdx.x; j < B.n * SPH_MROW; j += SPH_MTHREADS) mom[j] = 0ull;
+        for (int j = threadIdx.x; j < B.n * MROW; j += SPH_MTHREADS) mom[j] = 0ull;
         __syncthreads();
         for (int idx = r0 + threadIdx.x; idx < r1; idx += SPH_MTHREADS) {
             const int4 en = list[idx];
@@ -538,15 +546,15 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
                 const double4 fp = P.sph_pts[(size_t)q * NS + fs];
                 const double dx = vx - fp.x, dy = vy - fp.y, dz = vz - fp.z;
                 double d, rd;
-                sph_dist(fma(dz, dz, fma(dy, dy, dx * dx)), d, rd);
+                sph_dist<true>(fma(dz, dz, fma(dy, dy, dx * dx)), d, rd);
                 const double sp = d * B.inv, k = rint(sp), t = sp - k;
                 // (in range by the triangle inequality; the minimum keeps the
                 // LDS access inside the rows whatever the values are)
                 const unsigned i = min((unsigned)((int)k - first), (unsigned)(B.n - 1));
-                unsigned long long *row = mom + i * SPH_MROW;
+                unsigned long long *row = mom + i * MROW;
                 double v = av * (fp.w * rd);
 #pragma unroll
-                for (int m = 0; m < SPH_M; ++m) {
+                for (int m = 0; m < NM; ++m) {
                     // the magic constant's low word is zero: one 32-bit subtract
                     const long long bits = __double_as_longlong(v + 0x1.8p52);
                     const unsigned hi = (unsigned)(bits >> 32) - 0x43380000u;
@@ -556,9 +564,9 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
             }
         }
         __syncthreads();
-        for (int j = threadIdx.x; j < B.n * SPH_M; j += SPH_MTHREADS) {
-            const int i = j / SPH_M;
-            const double v = (double)(long long)mom[i * (SPH_MROW - SPH_M) + j] * unscale;
+        for (int j = threadIdx.x; j < B.n * NM; j += SPH_MTHREADS) {
+            const int i = j / NM;
+            const double v = (double)(long long)mom[i * (MROW - NM) + j] * unscale;
             dst[j] = add || r0 > i0 ? dst[j] + v : v;
         }
         __syncthreads();
@@ -573,7 +581,7 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
 // one accurate phase.  The waves split the intervals evenly and are added in
 // wave order.  Bound by FP64 VALU issue: 10 operations per (interval,
 // frequency).
-template <int LF>
+template <int NM, int LF>
 __global__ void __launch_bounds__(LF == 1 ? 1024 : 256)
 sph_synth_kernel(Problem P, SphBand B, const double *__restrict__ M, const int *__restrict__ hdr,
                  int max_parts, int fixed, int n_f, double f_min, double df, float2 *__restrict__ u)
@@ -586,29 +594,34 @@ sph_synth_kernel(Problem P, SphBand B, const double *__restrict__ M, const int *
     const double tau = B.step / P.c0d;   // us per interval
     const int share = (B.n + NW - 1) / NW, ia = min(B.n, wave * share), ib = min(B.n, ia + share);
     const int first = sph_first(P, B, q);
-    double a[LF][SPH_M], zc[LF], zs[LF], tr[LF], ti[LF];
+    double a[LF][NM], zc[LF], zs[LF], tr[LF], ti[LF];
 #pragma unroll
     for (int v = 0; v < LF; ++v) {
         const double f = f_min + df * (double)min(lb + v * 64 + lane, n_f - 1);
-        sph_basis<SPH_M>(B, f, a[v]);
+        sph_basis<NM>(B, f, a[v]);
         sincos_turns_d(frac_turn(f * tau), zc[v], zs[v]);
         tr[v] = ti[v] = 0.0;
     }
     for (int c = 0; c < parts; ++c) {
-        const double *__restrict__ row = M + (((size_t)c * P.nq + q) * B.n + ib) * SPH_M;
+        const double *__restrict__ row = M + (((size_t)c * P.nq + q) * B.n + ib) * NM;
         double sr[LF], si[LF];
 #pragma unroll
         for (int v = 0; v < LF; ++v) sr[v] = si[v] = 0.0;
 #pragma unroll 2
         for (int i = ib; i > ia; --i) {
-            row -= SPH_M;
+            row -= NM;
 #pragma unroll
             for (int v = 0; v < LF; ++v) {
                 // S <- (even - j odd) + S (zc - j zs)
-                const double r = fma(sr[v], zc[v], fma(si[v], zs[v], a[v][0] * row[0]));
-                const double m = fma(si[v], zc[v], fma(-sr[v], zs[v], -(a[v][1] * row[1])));
-                sr[v] = fma(a[v][4], row[4], fma(a[v][2], row[2], r));
-                si[v] = fma(-a[v][5], row[5], fma(-a[v][3], row[3], m));
+                double r = fma(sr[v], zc[v], fma(si[v], zs[v], a[v][0] * row[0]));
+                double m = fma(si[v], zc[v], fma(-sr[v], zs[v], -(a[v][1] * row[1])));
+#pragma unroll
+                for (int k = 2; k < NM; k += 2) {
+                    r = fma(a[v][k], row[k], r);
+                    m = fma(-a[v][k + 1], row[k + 1], m);
+                }
+                sr[v] = r;
+                si[v] = m;
             }
         }
 #pragma unroll
@@ -782,7 +795,7 @@ sph_eval_kernel(Problem P, SphBand B, SphBatch bt, const float4 *__restrict__ ta
                 for (int v = 0; v < SPH_TZ; ++v) {
                     const double vz = fma((double)v, dz, vz0);
                     double sp, rd;
-                    sph_dist(fma(vz, vz, rxy), sp, rd);
+                    sph_dist<false>(fma(vz, vz, rxy), sp, rd);
                     const double k = rint(sp);
                     const float t = (float)(sp - k);
                     // (in range by the choice of w; the minimum keeps the
@@ -925,33 +938,50 @@ static double sph_fwd_phase(int n_f, double f_min, double df)
     return 0.4 * std::pow(1.0 / (13.0 * m), 1.0 / 12.0);
 }
 
-// H_sph: six moments an interval, half-phases up to 0.4 (two workgroups' LDS
-// per CU at 64^3 and (0, 5] MHz).  Eight moments at 0.5 took 2.13 ms, six at 0.3
-// 1.96 ms (one workgroup per CU), at 0.33 1.58, at 0.45 1.55.  The moment path is taken when a
-// transducer's moments fit the LDS and its work is less, in VALU operations:
-// about 60 a (voxel, node) term and 12 per (interval, frequency), against 6
-// per frequency of whole blocks of SPH_FB, and 40, of the dense sum.  (The
-// images' zero voxels are skipped on both paths.)
-static bool sph_fwd_fast(const Problem &P, int n_f, double f_min, double df, SphBand &B)
+// Moments per interval of H_sph.  Six, at half-phases up to 0.4 (two workgroups'
+// LDS per CU at 64^3 and (0, 5] MHz; 0.3: 1.96 ms (one workgroup per CU), 0.33:
+// 1.58, 0.4: 1.55, 0.45: 1.55; eight at 0.5: 2.13): their error, 1 to 2e-8 of the
+// output, is below that of the plain sums, whose runs of SPH_FB frequencies
+// start from FP32 exponentials (together with the outputs' rounding of 2.5e-8, 3
+// to 5e-8 against 7 to 11e-8).  A single run that starts at or near the frequency
+// 0 starts exactly, and leaves the plain sums nothing but that rounding: eight
+// moments at 0.5 add as little (40 x 37 x 33 voxels, 16 frequencies from 0 to 4.7
+// MHz: 2.54e-8 either way, six moments 3.30e-8).
+static int sph_moments(const SphBand &B, const Problem &P, int n_f, double f_min)
+{
+    return n_f <= SPH_FB && f_min * B.reach < 0.25 * P.c0d ? SPH_M8 : SPH_M;
+}
+
+// The moment path is taken when a transducer's moments fit the LDS and its work
+// is less, in VALU operations: about 10 per moment of a (voxel, node) term and 2
+// per moment, interval and frequency, against 6 per frequency of whole blocks of
+// SPH_FB, and 40, of the dense sum.  (The images' zero voxels are skipped on both
+// paths.)
+static bool sph_fwd_fast(const Problem &P, int n_f, double f_min, double df, SphBand &B, int &nm)
 {
     B = sph_band(P, n_f, f_min, df, SPH_M, sph_fwd_phase(n_f, f_min, df));
+    nm = sph_moments(B, P, n_f, f_min);
+    if (nm == SPH_M8) B = sph_band(P, n_f, f_min, df, SPH_M8, 0.5);
     const double terms = (double)P.nx * P.ny * P.nz * P.sph_ns;
-    if (B.n_want * SPH_MROW * 8 > 150e3) return false;
+    if (B.n_want * sph_mrow(nm) * 8 > 150e3) return false;
     const double parts = std::max(1.0, std::min((double)sph_moment_parts(P), terms / 16384));
     const int blocks = (n_f + SPH_FB - 1) / SPH_FB;
-    return terms * 60 + B.n_want * n_f * 12 * parts < terms * (6.0 * SPH_FB * blocks + 40);
+    return terms * 10 * nm + B.n_want * n_f * 2 * nm * parts < terms * (6.0 * SPH_FB * blocks + 40);
 }
 
 // H_sph^T: interval half-phases up to 0.65 (error 6e-9 of a term, below the
 // FP32 rounding of the tables).  The table path is taken where its work is
 // less, in VALU operations: 18 per (interval, frequency) and 40 a (voxel,
 // node) term, against 4 per frequency and 100 of the dense sum (14 x 12 x 18
-// voxels, 80 transducers, 20 frequencies: 32 against 35 us).
+// voxels, 80 transducers, 20 frequencies: 32 against 35 us).  A single frequency
+// takes the plain sums, which hold nothing but u p0* in FP32 (40 x 37 x 33 voxels, 3
+// MHz: 3.7e-8 of the output, the tables 5.0e-8; from two frequencies on Horner's
+// FP32 steps make theirs the larger error).
 static bool sph_adj_fast(const Problem &P, int n_f, double f_min, double df, SphBand &B)
 {
     B = sph_band(P, n_f, f_min, df, SPH_P, 0.65);
     const double terms = (double)P.nx * P.ny * P.nz * P.sph_ns;
-    if (B.w > 3072 || B.n_want * 32 > 8e6) return false;
+    if (n_f == 1 || B.w > 3072 || B.n_want * 32 > 8e6) return false;
     return B.n_want * n_f * 18 + terms * 40 < terms * (4.0 * n_f + 100);
 }
 
@@ -964,10 +994,48 @@ static size_t sph_list_bytes(long long N)
 size_t sph_workspace_bytes(const Problem &P, int n_f, double f_min, double df)
 {
     SphBand B;
-    if (!sph_fwd_fast(P, n_f, f_min, df, B)) return sizeof(double2) * (size_t)SPH_CHUNKS * P.nq * n_f;
+    int nm;
+    if (!sph_fwd_fast(P, n_f, f_min, df, B, nm))
+        return sizeof(double2) * (size_t)SPH_CHUNKS * P.nq * n_f;
     const long long N = (long long)P.nx * P.ny * P.nz;
     return sph_list_bytes(N) + sizeof(int4) * (size_t)std::min(N, SPH_PASS) +
-           sizeof(double) * SPH_M * (size_t)sph_moment_parts(P) * P.nq * B.n;
+           sizeof(double) * nm * (size_t)sph_moment_parts(P) * P.nq * B.n;
+}
+
+template <int NM>
+static hipError_t launch_sph_moments(const Problem &P, const SphBand &B, const void *img, int img_dt,
+                                     float2 *u, int n_f, double f_min, double df, char *work,
+                                     hipStream_t s)
+{
+    const long long N = (long long)P.nx * P.ny * P.nz;
+    int *hdr = (int *)work;
+    int2 *blk = (int2 *)(work + 256);
+    int4 *list = (int4 *)(work + sph_list_bytes(N));
+    double *M = (double *)(list + std::min(N, SPH_PASS));
+    const int parts = sph_moment_parts(P), fixed = N > SPH_PASS ? 1 : 0;
+    for (long long n0 = 0; n0 < N; n0 += SPH_PASS) {
+        const long long n1 = std::min(N, n0 + SPH_PASS);
+        const dim3 blocks((unsigned)((n1 - n0 + SPH_LIST - 1) / SPH_LIST)), threads(SPH_THREADS);
+        hipLaunchKernelGGL(sph_count_kernel, blocks, threads, 0, s, img, img_dt, n0, n1, blk);
+        hipLaunchKernelGGL(sph_list_kernel, blocks, threads, 0, s, P, img, img_dt, n0, n1, blk, hdr, list);
+        hipLaunchKernelGGL(sph_moment_kernel<NM>, dim3(P.nq, parts), dim3(SPH_MTHREADS),
+                           sizeof(unsigned long long) * sph_mrow(NM) * B.n, s, P, B, list, hdr, M,
+                           n0 > 0 ? 1 : 0, fixed);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    auto synth = [&](auto kernel, int lf, int nw) {
+        hipLaunchKernelGGL(kernel, dim3(P.nq, (n_f + 64 * lf - 1) / (64 * lf)), dim3(64 * nw),
+                           sizeof(double2) * (size_t)(64 * lf * nw), s, P, B, M, hdr, parts, fixed, n_f,
+                           f_min, df, u);
+    };
+    // Frequencies share the loads of the moments where enough waves are
+    // left without it; few blocks split the intervals over more waves.
+    const long long blocks = (long long)P.nq * ((n_f + 63) / 64);
+    if (NM == SPH_M && blocks >= 2048 && n_f > 128) synth(sph_synth_kernel<SPH_M, 4>, 4, 4);
+    else if (NM == SPH_M && blocks >= 2048 && n_f > 64) synth(sph_synth_kernel<SPH_M, 2>, 2, 4);
+    else synth(sph_synth_kernel<NM, 1>, 1, blocks >= 1024 ? 4 : (blocks >= 512 ? 8 : 16));
+    return hipGetLastError();
 }
 
 hipError_t launch_sph_project(const Problem &P, const void *img, int img_dt, float2 *u, int n_f,
@@ -975,37 +1043,10 @@ hipError_t launch_sph_project(const Problem &P, const void *img, int img_dt, flo
 {
     const long long N = (long long)P.nx * P.ny * P.nz;
     SphBand B;
-    if (sph_fwd_fast(P, n_f, f_min, df, B)) {
-        int *hdr = (int *)part;
-        int2 *blk = (int2 *)((char *)part + 256);
-        int4 *list = (int4 *)((char *)part + sph_list_bytes(N));
-        double *M = (double *)(list + std::min(N, SPH_PASS));
-        const int parts = sph_moment_parts(P);
-        for (long long n0 = 0; n0 < N; n0 += SPH_PASS) {
-            const long long n1 = std::min(N, n0 + SPH_PASS);
-            const dim3 blocks((unsigned)((n1 - n0 + SPH_LIST - 1) / SPH_LIST)), threads(SPH_THREADS);
-            hipLaunchKernelGGL(sph_count_kernel, blocks, threads, 0, s, img, img_dt, n0, n1, blk);
-            hipLaunchKernelGGL(sph_list_kernel, blocks, threads, 0, s, P, img, img_dt, n0, n1, blk, hdr,
-                               list);
-            hipLaunchKernelGGL(sph_moment_kernel, dim3(P.nq, parts), dim3(SPH_MTHREADS),
-                               sizeof(unsigned long long) * SPH_MROW * B.n, s, P, B, list, hdr, M,
-                               n0 > 0 ? 1 : 0, N > SPH_PASS ? 1 : 0);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        auto synth = [&](auto kernel, int lf, int nw) {
-            hipLaunchKernelGGL(kernel, dim3(P.nq, (n_f + 64 * lf - 1) / (64 * lf)), dim3(64 * nw),
-                               sizeof(double2) * (size_t)(64 * lf * nw), s, P, B, M, hdr, parts,
-                               N > SPH_PASS ? 1 : 0, n_f, f_min, df, u);
-        };
-        // Frequencies share the loads of the moments where enough waves are
-        // left without it; few blocks split the intervals over more waves.
-        const long long blocks = (long long)P.nq * ((n_f + 63) / 64);
-        if (blocks >= 2048 && n_f > 128) synth(sph_synth_kernel<4>, 4, 4);
-        else if (blocks >= 2048 && n_f > 64) synth(sph_synth_kernel<2>, 2, 4);
-        else synth(sph_synth_kernel<1>, 1, blocks >= 1024 ? 4 : (blocks >= 512 ? 8 : 16));
-        return hipGetLastError();
-    }
+    int nm;
+    if (sph_fwd_fast(P, n_f, f_min, df, B, nm))
+        return (nm == SPH_M8 ? launch_sph_moments<SPH_M8> : launch_sph_moments<SPH_M>)(
+            P, B, img, img_dt, u, n_f, f_min, df, (char *)part, s);
     // n_f <= SPH_THREADS * SPH_FB (checked by the caller): a transducer's
     // frequency blocks fit one workgroup.
     const int LB = (n_f + SPH_FB - 1) / SPH_FB;
