@@ -68,6 +68,7 @@ constexpr int SPH_TX = 16, SPH_TZ = 8;   // voxel tile of the table adjoint: 16 
 constexpr int SPH_TVOX = SPH_TX * SPH_TX * SPH_TZ;
 constexpr int SPH_STAGE = 40960;         // bytes of staged polynomials: 4 workgroups per CU
 constexpr long long SPH_PASS = 1ll << 24;   // voxels listed per forward pass (16 bytes each)
+constexpr size_t SPH_MOMENTS = size_t(1) << 30;   // bytes of moments held at a time (forward)
 
 __device__ __forceinline__ double frac_turn(double x) { return x - floor(x); }
 
@@ -493,8 +494,8 @@ __device__ __forceinline__ int sph_parts(long long n, int parts, int fixed)
     return fixed ? parts : (int)max(1ll, min((long long)parts, n >> 14));
 }
 
-// Moments of one transducer (blockIdx.x) over a part of the listed voxels
-// (blockIdx.y of sph_parts): M[part][q][i][m] = sum over the (voxel, face
+// Moments of one transducer (q = q0 + blockIdx.x) over a part of the listed
+// voxels (blockIdx.y of sph_parts): M[part][q - q0][i][m] = sum over the (voxel, face
 // node) terms in interval i of w t^m, w = value x node weight / (2 pi d),
 // added to the earlier contents if `add`.  The LDS sums are 64-bit integers,
 // so they do not depend on the order of a run's terms: every |w t^m| is below
@@ -509,11 +510,11 @@ __device__ __forceinline__ int sph_parts(long long n, int parts, int fixed)
 template <int NM>
 __global__ void __launch_bounds__(SPH_MTHREADS)
 sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int *__restrict__ hdr,
-                  double *__restrict__ M, int add, int fixed)
+                  int q0, double *__restrict__ M, int add, int fixed)
 {
     constexpr int MROW = sph_mrow(NM);
     extern __shared__ unsigned long long mom[];   // [n][MROW]
-    const int q = blockIdx.x, NS = P.sph_ns;
+    const int q = q0 + (int)blockIdx.x, NS = P.sph_ns;
     const int total = hdr[0];
     const unsigned amax = (unsigned)hdr[1];
     const int parts = sph_parts((long long)total * NS, gridDim.y, fixed);
@@ -532,7 +533,7 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
     const double S = ldexp(1.0, kb);
     const double unscale = bad ? __longlong_as_double(0x7ff8000000000000ll) : ldexp(1.0, -kb);
     const double ws = S / 6.283185307179586;
-    double *dst = M + ((size_t)blockIdx.y * P.nq + q) * B.n * NM;
+    double *dst = M + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * B.n * NM;
     for (int r0 = i0; r0 == i0 || r0 < i1; r0 += run) {
         const int r1 = min(i1, r0 + run);
         for (int j = threadIdx.x; j < B.n * MROW; j += SPH_MTHREADS) mom[j] = 0ull;
@@ -584,10 +585,11 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
 template <int NM, int LF>
 __global__ void __launch_bounds__(LF == 1 ? 1024 : 256)
 sph_synth_kernel(Problem P, SphBand B, const double *__restrict__ M, const int *__restrict__ hdr,
-                 int max_parts, int fixed, int n_f, double f_min, double df, float2 *__restrict__ u)
+                 int q0, int max_parts, int fixed, int n_f, double f_min, double df,
+                 float2 *__restrict__ u)
 {
     extern __shared__ double2 red[];   // [waves][LF * 64]
-    const int q = blockIdx.x, NW = blockDim.x >> 6;
+    const int q = q0 + (int)blockIdx.x, NW = blockDim.x >> 6;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const int lb = blockIdx.y * 64 * LF;
     const int parts = sph_parts((long long)hdr[0] * P.sph_ns, max_parts, fixed);
@@ -603,7 +605,7 @@ sph_synth_kernel(Problem P, SphBand B, const double *__restrict__ M, const int *
         tr[v] = ti[v] = 0.0;
     }
     for (int c = 0; c < parts; ++c) {
-        const double *__restrict__ row = M + (((size_t)c * P.nq + q) * B.n + ib) * NM;
+        const double *__restrict__ row = M + (((size_t)c * gridDim.x + blockIdx.x) * B.n + ib) * NM;
         double sr[LF], si[LF];
 #pragma unroll
         for (int v = 0; v < LF; ++v) sr[v] = si[v] = 0.0;
@@ -991,6 +993,15 @@ static size_t sph_list_bytes(long long N)
     return 256 + (sizeof(int2) * (size_t)((std::min(N, SPH_PASS) + SPH_LIST - 1) / SPH_LIST) + 255) / 256 * 256;
 }
 
+// Transducers whose moments are held at a time, and the moments' bytes.
+static int sph_moment_batch(const Problem &P, const SphBand &B, int nm, size_t &bytes)
+{
+    const size_t row = sizeof(double) * nm * (size_t)sph_moment_parts(P) * B.n;
+    const int qb = (int)std::max<size_t>(1, std::min<size_t>(SPH_MOMENTS / row, (size_t)P.nq));
+    bytes = row * qb;
+    return qb;
+}
+
 size_t sph_workspace_bytes(const Problem &P, int n_f, double f_min, double df)
 {
     SphBand B;
@@ -998,8 +1009,9 @@ size_t sph_workspace_bytes(const Problem &P, int n_f, double f_min, double df)
     if (!sph_fwd_fast(P, n_f, f_min, df, B, nm))
         return sizeof(double2) * (size_t)SPH_CHUNKS * P.nq * n_f;
     const long long N = (long long)P.nx * P.ny * P.nz;
-    return sph_list_bytes(N) + sizeof(int4) * (size_t)std::min(N, SPH_PASS) +
-           sizeof(double) * nm * (size_t)sph_moment_parts(P) * P.nq * B.n;
+    size_t moments;
+    (void)sph_moment_batch(P, B, nm, moments);
+    return sph_list_bytes(N) + sizeof(int4) * (size_t)std::min(N, SPH_PASS) + moments;
 }
 
 template <int NM>
@@ -1013,28 +1025,36 @@ static hipError_t launch_sph_moments(const Problem &P, const SphBand &B, const v
     int4 *list = (int4 *)(work + sph_list_bytes(N));
     double *M = (double *)(list + std::min(N, SPH_PASS));
     const int parts = sph_moment_parts(P), fixed = N > SPH_PASS ? 1 : 0;
-    for (long long n0 = 0; n0 < N; n0 += SPH_PASS) {
-        const long long n1 = std::min(N, n0 + SPH_PASS);
-        const dim3 blocks((unsigned)((n1 - n0 + SPH_LIST - 1) / SPH_LIST)), threads(SPH_THREADS);
-        hipLaunchKernelGGL(sph_count_kernel, blocks, threads, 0, s, img, img_dt, n0, n1, blk);
-        hipLaunchKernelGGL(sph_list_kernel, blocks, threads, 0, s, P, img, img_dt, n0, n1, blk, hdr, list);
-        hipLaunchKernelGGL(sph_moment_kernel<NM>, dim3(P.nq, parts), dim3(SPH_MTHREADS),
-                           sizeof(unsigned long long) * sph_mrow(NM) * B.n, s, P, B, list, hdr, M,
-                           n0 > 0 ? 1 : 0, fixed);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    size_t bytes;
+    const int qb = sph_moment_batch(P, B, NM, bytes);
+    for (int q0 = 0; q0 < P.nq; q0 += qb) {
+        const int nq = std::min(qb, P.nq - q0);
+        for (long long n0 = 0; n0 < N; n0 += SPH_PASS) {
+            const long long n1 = std::min(N, n0 + SPH_PASS);
+            if (fixed || q0 == 0) {   // one pass: its list serves every batch of transducers
+                const dim3 blocks((unsigned)((n1 - n0 + SPH_LIST - 1) / SPH_LIST)), threads(SPH_THREADS);
+                hipLaunchKernelGGL(sph_count_kernel, blocks, threads, 0, s, img, img_dt, n0, n1, blk);
+                hipLaunchKernelGGL(sph_list_kernel, blocks, threads, 0, s, P, img, img_dt, n0, n1, blk, hdr,
+                                   list);
+            }
+            hipLaunchKernelGGL(sph_moment_kernel<NM>, dim3(nq, parts), dim3(SPH_MTHREADS),
+                               sizeof(unsigned long long) * sph_mrow(NM) * B.n, s, P, B, list, hdr, q0, M,
+                               n0 > 0 ? 1 : 0, fixed);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        auto synth = [&](auto kernel, int lf, int nw) {
+            hipLaunchKernelGGL(kernel, dim3(nq, (n_f + 64 * lf - 1) / (64 * lf)), dim3(64 * nw),
+                               sizeof(double2) * (size_t)(64 * lf * nw), s, P, B, M, hdr, q0, parts, fixed,
+                               n_f, f_min, df, u);
+        };
+        // Frequencies share the loads of the moments where enough waves are
+        // left without it; few blocks split the intervals over more waves.
+        const long long blocks = (long long)nq * ((n_f + 63) / 64);
+        if (NM == SPH_M && blocks >= 2048 && n_f > 128) synth(sph_synth_kernel<SPH_M, 4>, 4, 4);
+        else if (NM == SPH_M && blocks >= 2048 && n_f > 64) synth(sph_synth_kernel<SPH_M, 2>, 2, 4);
+        else synth(sph_synth_kernel<NM, 1>, 1, blocks >= 1024 ? 4 : (blocks >= 512 ? 8 : 16));
     }
-    auto synth = [&](auto kernel, int lf, int nw) {
-        hipLaunchKernelGGL(kernel, dim3(P.nq, (n_f + 64 * lf - 1) / (64 * lf)), dim3(64 * nw),
-                           sizeof(double2) * (size_t)(64 * lf * nw), s, P, B, M, hdr, parts, fixed, n_f,
-                           f_min, df, u);
-    };
-    // Frequencies share the loads of the moments where enough waves are
-    // left without it; few blocks split the intervals over more waves.
-    const long long blocks = (long long)P.nq * ((n_f + 63) / 64);
-    if (NM == SPH_M && blocks >= 2048 && n_f > 128) synth(sph_synth_kernel<SPH_M, 4>, 4, 4);
-    else if (NM == SPH_M && blocks >= 2048 && n_f > 64) synth(sph_synth_kernel<SPH_M, 2>, 2, 4);
-    else synth(sph_synth_kernel<NM, 1>, 1, blocks >= 1024 ? 4 : (blocks >= 512 ? 8 : 16));
     return hipGetLastError();
 }
 
