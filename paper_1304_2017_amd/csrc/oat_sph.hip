@@ -63,6 +63,11 @@ constexpr int SPH_M8 = 8;        // 8 where the plain sums have no error but rou
 // 64-bit words per interval of moments in LDS (odd: spreads banks)
 constexpr int sph_mrow(int m) { return m + 1; }
 constexpr int SPH_MTHREADS = 1024;
+// Terms up to which half the threads take a transducer's: more workgroups at once
+// hide the clearing and storing of the moments, which such calls consist of (a 5%
+// phantom of 28^3 / 2048, 32 frequencies: 78 -> 72 us; every voxel set: 198 -> 202,
+// at 64^3 1573 -> 1653).
+constexpr int SPH_FEW = 24576;
 constexpr int SPH_RUN = 1 << 20;         // terms summed in integers at a time
 constexpr int SPH_TX = 16, SPH_TZ = 8;   // voxel tile of the table adjoint: 16 x 16 x 8
 constexpr int SPH_TVOX = SPH_TX * SPH_TX * SPH_TZ;
@@ -486,6 +491,63 @@ sph_list_kernel(Problem P, const void *__restrict__ img, int img_dt, long long n
     }
 }
 
+// The same list and header of at most SPH_ONE voxels from one workgroup: one
+// launch for two, which at such sizes are 4 us each of a call of 20 to 100 (up to
+// 32768 voxels this way: 10 us longer at 32^3).
+constexpr int SPH_ONE = 8192, SPH_ONE_THREADS = 1024;
+__global__ void __launch_bounds__(SPH_ONE_THREADS)
+sph_list_one_kernel(Problem P, const void *__restrict__ img, int img_dt, int N, int *__restrict__ hdr,
+                    int4 *__restrict__ list)
+{
+    constexpr int PER = 8, NW = SPH_ONE_THREADS / 64;
+    __shared__ int wcnt[2][NW];
+    __shared__ unsigned wmax[NW];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int base = 0, buf = 0;
+    unsigned m = 0;
+    for (int b0 = 0; b0 < N; b0 += PER * SPH_ONE_THREADS, buf ^= 1) {
+        float v[PER];
+        int cnt = 0;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int n = b0 + i * SPH_ONE_THREADS + threadIdx.x;
+            v[i] = n < N ? load_val(img, (size_t)n, img_dt) : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            cnt += __popcll(__ballot(v[i] != 0.f));
+            m = max(m, __float_as_uint(v[i]) & 0x7fffffffu);
+        }
+        if (lane == 0) wcnt[buf][wave] = cnt;
+        __syncthreads();
+        int pos = base;
+        for (int w = 0; w < NW; ++w) {
+            const int c = wcnt[buf][w];
+            pos += w < wave ? c : 0;
+            base += c;
+        }
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const uint64_t bal = __ballot(v[i] != 0.f);
+            if (v[i] != 0.f) {
+                const int n = b0 + i * SPH_ONE_THREADS + threadIdx.x;
+                const int row = n / P.nx, iz = row / P.ny;
+                list[pos + __popcll(bal & ((1ull << lane) - 1ull))] =
+                    make_int4(n - row * P.nx, row - iz * P.ny, iz, (int)__float_as_uint(v[i]));
+            }
+            pos += __popcll(bal);
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
+    if (lane == 0) wmax[wave] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < NW; ++w) m = max(m, wmax[w]);
+        hdr[0] = base;
+        hdr[1] = (int)m;
+    }
+}
+
 // Parts in use of the `parts` that a call provides for the moments of n
 // listed terms: enough to fill the device, not more than the terms are worth
 // (every part costs sph_synth_kernel another pass over the intervals).
@@ -536,9 +598,9 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
     double *dst = M + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * B.n * NM;
     for (int r0 = i0; r0 == i0 || r0 < i1; r0 += run) {
         const int r1 = min(i1, r0 + run);
-        for (int j = threadIdx.x; j < B.n * MROW; j += SPH_MTHREADS) mom[j] = 0ull;
+        for (int j = threadIdx.x; j < B.n * MROW; j += (int)blockDim.x) mom[j] = 0ull;
         __syncthreads();
-        for (int idx = r0 + threadIdx.x; idx < r1; idx += SPH_MTHREADS) {
+        for (int idx = r0 + threadIdx.x; idx < r1; idx += (int)blockDim.x) {
             const int4 en = list[idx];
             const double vx = fma((double)en.x, P.dxd, P.x0), vy = fma((double)en.y, P.dxd, P.y0),
                          vz = fma((double)en.z, P.dxd, P.z0);
@@ -565,7 +627,7 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
             }
         }
         __syncthreads();
-        for (int j = threadIdx.x; j < B.n * NM; j += SPH_MTHREADS) {
+        for (int j = threadIdx.x; j < B.n * NM; j += (int)blockDim.x) {
             const int i = j / NM;
             const double v = (double)(long long)mom[i * (MROW - NM) + j] * unscale;
             dst[j] = add || r0 > i0 ? dst[j] + v : v;
@@ -580,21 +642,27 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
 // through the scalar cache (LF frequencies share a load); the sum over a
 // wave's intervals is Horner's rule in exp(-j 2 pi f step / c0), FP64, times
 // one accurate phase.  The waves split the intervals evenly and are added in
-// wave order.  Bound by FP64 VALU issue: 10 operations per (interval,
+// wave order.  SUB > 1 (at most 64 / SUB frequencies): a wave's lanes are SUB
+// such shares, so that none is idle (a 5% phantom of 12^3 / 2048, 16 frequencies:
+// the call 47 -> 31 us).  Bound by FP64 VALU issue: 10 operations per (interval,
 // frequency).
-template <int NM, int LF>
+template <int NM, int LF, int SUB>
 __global__ void __launch_bounds__(LF == 1 ? 1024 : 256)
 sph_synth_kernel(Problem P, SphBand B, const double *__restrict__ M, const int *__restrict__ hdr,
                  int q0, int max_parts, int fixed, int n_f, double f_min, double df,
                  float2 *__restrict__ u)
 {
-    extern __shared__ double2 red[];   // [waves][LF * 64]
-    const int q = q0 + (int)blockIdx.x, NW = blockDim.x >> 6;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    static_assert(SUB == 1 || LF == 1, "shares of a wave have one frequency a lane");
+    constexpr int F = 64 / SUB;
+    extern __shared__ double2 red[];   // [shares][LF * F]
+    const int q = q0 + (int)blockIdx.x, NS = (blockDim.x >> 6) * SUB;
+    const int lane = threadIdx.x & (F - 1);
+    // (uniform with one share a wave: the moments' loads are scalar)
+    const int sh = SUB > 1 ? (int)threadIdx.x / F : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lb = blockIdx.y * 64 * LF;
     const int parts = sph_parts((long long)hdr[0] * P.sph_ns, max_parts, fixed);
     const double tau = B.step / P.c0d;   // us per interval
-    const int share = (B.n + NW - 1) / NW, ia = min(B.n, wave * share), ib = min(B.n, ia + share);
+    const int share = (B.n + NS - 1) / NS, ia = min(B.n, sh * share), ib = min(B.n, ia + share);
     const int first = sph_first(P, B, q);
     double a[LF][NM], zc[LF], zs[LF], tr[LF], ti[LF];
 #pragma unroll
@@ -634,18 +702,18 @@ sph_synth_kernel(Problem P, SphBand B, const double *__restrict__ M, const int *
     }
 #pragma unroll
     for (int v = 0; v < LF; ++v) {
-        // times exp(-j theta) of the wave's first interval
+        // times exp(-j theta) of the share's first interval
         const double f = f_min + df * (double)min(lb + v * 64 + lane, n_f - 1);
         double c, s;
         sincos_turns_d(frac_turn(f * tau * (double)(first + ia)), c, s);
-        red[(wave * LF + v) * 64 + lane] = make_double2(fma(tr[v], c, ti[v] * s), fma(ti[v], c, -(tr[v] * s)));
+        red[(sh * LF + v) * F + lane] = make_double2(fma(tr[v], c, ti[v] * s), fma(ti[v], c, -(tr[v] * s)));
     }
     __syncthreads();
-    for (int t = threadIdx.x; t < 64 * LF && lb + t < n_f; t += blockDim.x) {
+    for (int t = threadIdx.x; t < F * LF && lb + t < n_f; t += blockDim.x) {
         double2 r = red[t];
-        for (int w = 1; w < NW; ++w) {
-            r.x += red[w * LF * 64 + t].x;
-            r.y += red[w * LF * 64 + t].y;
+        for (int w = 1; w < NS; ++w) {
+            r.x += red[w * LF * F + t].x;
+            r.y += red[w * LF * F + t].y;
         }
         const double2 p0 = sph_p0(P, f_min + df * (double)(lb + t));
         u[(size_t)q * n_f + lb + t] = make_float2((float)(p0.x * r.x - p0.y * r.y),
@@ -1027,17 +1095,22 @@ static hipError_t launch_sph_moments(const Problem &P, const SphBand &B, const v
     const int parts = sph_moment_parts(P), fixed = N > SPH_PASS ? 1 : 0;
     size_t bytes;
     const int qb = sph_moment_batch(P, B, NM, bytes);
+    const int threads_m = N * P.sph_ns <= SPH_FEW ? SPH_MTHREADS / 2 : SPH_MTHREADS;
     for (int q0 = 0; q0 < P.nq; q0 += qb) {
         const int nq = std::min(qb, P.nq - q0);
         for (long long n0 = 0; n0 < N; n0 += SPH_PASS) {
             const long long n1 = std::min(N, n0 + SPH_PASS);
-            if (fixed || q0 == 0) {   // one pass: its list serves every batch of transducers
+            // (one pass: its list serves every batch of transducers)
+            if (N <= SPH_ONE && q0 == 0) {
+                hipLaunchKernelGGL(sph_list_one_kernel, dim3(1), dim3(SPH_ONE_THREADS), 0, s, P, img, img_dt,
+                                   (int)N, hdr, list);
+            } else if (fixed || q0 == 0) {
                 const dim3 blocks((unsigned)((n1 - n0 + SPH_LIST - 1) / SPH_LIST)), threads(SPH_THREADS);
                 hipLaunchKernelGGL(sph_count_kernel, blocks, threads, 0, s, img, img_dt, n0, n1, blk);
                 hipLaunchKernelGGL(sph_list_kernel, blocks, threads, 0, s, P, img, img_dt, n0, n1, blk, hdr,
                                    list);
             }
-            hipLaunchKernelGGL(sph_moment_kernel<NM>, dim3(nq, parts), dim3(SPH_MTHREADS),
+            hipLaunchKernelGGL(sph_moment_kernel<NM>, dim3(nq, parts), dim3(threads_m),
                                sizeof(unsigned long long) * sph_mrow(NM) * B.n, s, P, B, list, hdr, q0, M,
                                n0 > 0 ? 1 : 0, fixed);
             const hipError_t e = hipGetLastError();
@@ -1051,9 +1124,12 @@ static hipError_t launch_sph_moments(const Problem &P, const SphBand &B, const v
         // Frequencies share the loads of the moments where enough waves are
         // left without it; few blocks split the intervals over more waves.
         const long long blocks = (long long)nq * ((n_f + 63) / 64);
-        if (NM == SPH_M && blocks >= 2048 && n_f > 128) synth(sph_synth_kernel<SPH_M, 4>, 4, 4);
-        else if (NM == SPH_M && blocks >= 2048 && n_f > 64) synth(sph_synth_kernel<SPH_M, 2>, 2, 4);
-        else synth(sph_synth_kernel<NM, 1>, 1, blocks >= 1024 ? 4 : (blocks >= 512 ? 8 : 16));
+        const int nw = blocks >= 1024 ? 4 : (blocks >= 512 ? 8 : 16);
+        if (n_f <= 16) synth(sph_synth_kernel<NM, 1, 4>, 1, nw);
+        else if (n_f <= 32) synth(sph_synth_kernel<NM, 1, 2>, 1, nw);
+        else if (blocks >= 2048 && n_f > 128) synth(sph_synth_kernel<SPH_M, 4, 1>, 4, 4);
+        else if (blocks >= 2048 && n_f > 64) synth(sph_synth_kernel<SPH_M, 2, 1>, 2, 4);
+        else synth(sph_synth_kernel<SPH_M, 1, 1>, 1, nw);
     }
     return hipGetLastError();
 }
