@@ -268,7 +268,7 @@ int oat_plan_set_aperture(oat_plan *plan, double width, double height, int m);
  * oat_sph_backproject, which may grow the plan's workspace; this variant
  * calls no hipMalloc, hipFree or allocating library routine and never waits
  * for the device.  Its tables and partial sums go to a fixed 64 MiB scratch
- * array in device memory, one per GPU (resolved at the first oat_plan_create
+ * array in device memory, one per GPU (allocated at the first oat_plan_create
  * on that GPU and held until the process ends); the transducers' tables are
  * taken in batches that fit it, and a need that does not is rejected with
  * OAT_ERR_ARG (no image this library accepts has one).  Every value is

@@ -327,9 +327,10 @@ hipError_t launch_sph_backproject(const Problem &P, const float2 *u, int n_f, do
 // path's partial sums are at most 1024 tiles of 2048 doubles (16 MiB) and
 // its basis 256 KiB, and its table batches are sized to the rest.
 constexpr size_t SPH_SCRATCH_BYTES = size_t(64) << 20;
-// Device address of the fixed scratch on `device`, which must be current.
-// Resolved by hipGetSymbolAddress on the first call for that device, cached
-// afterwards (thread-safe).
+// Device address of the fixed scratch on `device`, which must be current:
+// allocated by the first call for that device (a static array of this size
+// cost the first plan of a process 24 ms for its zeros) and held until the
+// process ends; thread-safe.
 hipError_t sph_scratch_address(int device, double **out);
 
 }  // namespace oat

@@ -595,13 +595,13 @@ int oat_plan_create_ex(const oat_geometry *g, int device, const oat_plan_options
         return fail_hip(e, "hipSetDevice");
     }
     {
-        // Resolve this device's fixed scratch (oat_sph_backproject_noalloc)
-        // while the device is current; later plans reuse the cached address.
+        // This device's fixed scratch (oat_sph_backproject_noalloc), allocated
+        // while the device is current; later plans reuse it.
         double *scr = nullptr;
         if ((e = sph_scratch_address(device, &scr)) != hipSuccess) {
             delete plan;
             (void)hipSetDevice(prev);
-            return fail_hip(e, "oat_plan_create: hipGetSymbolAddress(scratch)");
+            return fail_hip(e, "oat_plan_create: hipMalloc(scratch)");
         }
     }
     auto alloc = [&](void **p, size_t bytes, const char *what) -> hipError_t {

@@ -913,24 +913,18 @@ sph_eval_sum_kernel(Problem P, SphBand B, const double *__restrict__ part, int s
               (float)(s * (B.inv * 0.15915494309189535)));
 }
 
-// Device scratch of oat_sph_backproject_noalloc: the adjoint's FP64 slice
-// partial images.  Each GPU the library runs on holds its own copy until the
-// process ends.  In host code this name is only a stand-in for the symbol:
-// kernels and copies get the address that sph_scratch_address resolved.
-static __device__ __align__(256) double scratch[SPH_SCRATCH_BYTES / sizeof(double)];
-
 }  // namespace
 
 hipError_t sph_scratch_address(int device, double **out)
 {
     static std::mutex mu;
-    static std::vector<double *> addr;   // per device ordinal; null until resolved
+    static std::vector<double *> addr;   // per device ordinal; null until allocated
     std::lock_guard<std::mutex> lock(mu);
     if (device < 0) return hipErrorInvalidDevice;
     if ((size_t)device >= addr.size()) addr.resize((size_t)device + 1, nullptr);
     if (!addr[(size_t)device]) {
         double *p = nullptr;
-        const hipError_t e = hipGetSymbolAddress((void **)&p, HIP_SYMBOL(scratch));
+        const hipError_t e = hipMalloc((void **)&p, SPH_SCRATCH_BYTES);
         if (e != hipSuccess) return e;
         addr[(size_t)device] = p;
     }
