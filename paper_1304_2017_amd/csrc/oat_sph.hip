@@ -722,18 +722,23 @@ sph_synth_kernel(Problem P, SphBand B, const double *__restrict__ M, const int *
 }
 
 // --- H_sph^T ---------------------------------------------------------------
-// ab[l][m] = a_m(f_l) beta_l with p0(f_l) = j beta_l.
+// ab[m] = a_m(f) beta with p0(f) = j beta.
+__device__ __forceinline__ void sph_adj_basis(const Problem &P, const SphBand &B, double f,
+                                              double *__restrict__ ab)
+{
+    const double beta = sph_p0(P, f).y;
+    double a[SPH_P];
+    sph_basis<SPH_P>(B, f, a);
+#pragma unroll
+    for (int m = 0; m < SPH_P; ++m) ab[m] = a[m] * beta;
+}
+
 __global__ void __launch_bounds__(64)
 sph_adj_basis_kernel(Problem P, SphBand B, int n_f, double f_min, double df,
                      double *__restrict__ ab)
 {
     const int l = blockIdx.x * 64 + threadIdx.x;
-    if (l >= n_f) return;
-    const double f = f_min + df * (double)l, beta = sph_p0(P, f).y;
-    double a[SPH_P];
-    sph_basis<SPH_P>(B, f, a);
-#pragma unroll
-    for (int m = 0; m < SPH_P; ++m) ab[(size_t)l * SPH_P + m] = a[m] * beta;
+    if (l < n_f) sph_adj_basis(P, B, f_min + df * (double)l, ab + (size_t)l * SPH_P);
 }
 
 // Transducers of a table batch: the offsets b0 .. b1 - 1 of every slice of
@@ -745,32 +750,47 @@ struct SphBatch {
 // Interval polynomials of F_q(d) = Re sum_l u[q][l] conj(p0(f_l))
 // exp(+j 2 pi f_l d / c0) of the batch's transducers: table[row][i] holds the
 // coefficients of t^0 .. t^7 (two float4).
-// A lane takes two intervals (they share the scalar loads of the row of u and
-// of the basis), a workgroup one transducer; FP64 up to the final rounding.
+// A lane takes two intervals (they share the loads of the row of u and of the
+// basis), a workgroup one transducer; FP64 up to the final rounding.  Small grids,
+// bound by latency: OWN forms the basis in the workgroup, a launch less, and SH
+// groups of threads share the frequencies, their sums added in order (20^3 voxels,
+// 16 transducers, 200 frequencies: 15 us, 45 for the two launches).
 constexpr int SPH_TTHREADS = 128;
-__global__ void __launch_bounds__(SPH_TTHREADS)
+template <int SH, bool OWN>
+__global__ void __launch_bounds__(SPH_TTHREADS *SH)
 sph_table_kernel(Problem P, SphBand B, SphBatch bt, const float2 *__restrict__ u,
                  const double *__restrict__ ab, int n_f, double f_min, double df,
                  float4 *__restrict__ table)
 {
+    extern __shared__ double tl[];   // OWN: basis [n_f][SPH_P]; SH > 1: sums [SH - 1][2 SPH_P][threads]
     const int per = bt.b1 - bt.b0, slice = blockIdx.y / per, off = bt.b0 + blockIdx.y % per;
     const int q = slice * bt.qps + off;
-    const int i0 = blockIdx.x * 2 * SPH_TTHREADS + threadIdx.x;
-    if (off >= bt.qps || q >= P.nq) return;
+    const int lane = threadIdx.x % SPH_TTHREADS;
+    const int sh = SH > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / SPH_TTHREADS) : 0;
+    const int i0 = blockIdx.x * 2 * SPH_TTHREADS + lane;
+    if (off >= bt.qps || q >= P.nq) return;   // (the whole workgroup)
+    if (OWN) {
+        for (int l = threadIdx.x; l < n_f; l += SPH_TTHREADS * SH)
+            sph_adj_basis(P, B, f_min + df * (double)l, tl + l * SPH_P);
+        __syncthreads();
+    }
+    const int share = (n_f + SH - 1) / SH, la = sh * share, lb = min(n_f, la + share);
     double zc[2], zs[2], c[2], s[2], k[2][SPH_P];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const double tau = B.step / P.c0d * (double)(sph_first(P, B, q) + i0 + h * SPH_TTHREADS);
         sincos_turns_d(frac_turn(df * tau), zc[h], zs[h]);
-        sincos_turns_d(frac_turn(f_min * tau), c[h], s[h]);
+        sincos_turns_d(frac_turn((f_min + df * (double)la) * tau), c[h], s[h]);
 #pragma unroll
         for (int m = 0; m < SPH_P; ++m) k[h][m] = 0.0;
     }
     const float2 *__restrict__ row = u + (size_t)q * n_f;
 #pragma unroll 2
-    for (int l = 0; l < n_f; ++l) {
+    for (int l = la; l < lb; ++l) {
         const double ux = (double)row[l].x, uy = (double)row[l].y;
-        const double *__restrict__ a = ab + (size_t)l * SPH_P;
+        double a[SPH_P];
+#pragma unroll
+        for (int m = 0; m < SPH_P; ++m) a[m] = OWN ? tl[l * SPH_P + m] : ab[(size_t)l * SPH_P + m];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             // u conj(p0) exp(j theta) = beta (A - j D); times cos(y t) +
@@ -785,6 +805,23 @@ sph_table_kernel(Problem P, SphBand B, SphBatch bt, const float2 *__restrict__ u
             s[h] = fma(c[h], zs[h], s[h] * zc[h]);
             c[h] = nc;
         }
+    }
+    if (SH > 1) {
+        __syncthreads();   // the basis is read
+        double *part = tl + (size_t)(sh - 1) * 2 * SPH_P * SPH_TTHREADS + lane;
+        if (sh > 0)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int m = 0; m < SPH_P; ++m) part[(h * SPH_P + m) * SPH_TTHREADS] = k[h][m];
+        __syncthreads();
+        if (sh > 0) return;
+        for (int w = 0; w < SH - 1; ++w)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int m = 0; m < SPH_P; ++m)
+                    k[h][m] += tl[((size_t)(w * 2 + h) * SPH_P + m) * SPH_TTHREADS + lane];
     }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -1020,27 +1057,43 @@ static int sph_moments(const SphBand &B, const Problem &P, int n_f, double f_min
 // is less, in VALU operations: about 10 per moment of a (voxel, node) term and 2
 // per moment, interval and frequency, against 6 per frequency of whole blocks of
 // SPH_FB, and 40, of the dense sum.  (The images' zero voxels are skipped on both
-// paths.)
+// paths.)  A few terms take the plain sums' two launches (1 voxel: 12 us, 17 with
+// the moments').
 static bool sph_fwd_fast(const Problem &P, int n_f, double f_min, double df, SphBand &B, int &nm)
 {
     B = sph_band(P, n_f, f_min, df, SPH_M, sph_fwd_phase(n_f, f_min, df));
     nm = sph_moments(B, P, n_f, f_min);
     if (nm == SPH_M8) B = sph_band(P, n_f, f_min, df, SPH_M8, 0.5);
     const double terms = (double)P.nx * P.ny * P.nz * P.sph_ns;
-    if (B.n_want * sph_mrow(nm) * 8 > 150e3) return false;
+    if (terms < 32 || B.n_want * sph_mrow(nm) * 8 > 150e3) return false;
     const double parts = std::max(1.0, std::min((double)sph_moment_parts(P), terms / 16384));
     const int blocks = (n_f + SPH_FB - 1) / SPH_FB;
     return terms * 10 * nm + B.n_want * n_f * 2 * nm * parts < terms * (6.0 * SPH_FB * blocks + 40);
 }
 
+// Transducer slices of the dense adjoint: a grid of fewer than 1024
+// workgroups (a small image) takes the transducers in up to 4 slices along
+// grid y, so the device holds more waves; their FP64 partial images are then
+// added in slice order.
+static int sph_adj_slices(const Problem &P)
+{
+    const long long N = (long long)P.nx * P.ny * P.nz;
+    const long long blocks = ((N + SPH_NV - 1) / SPH_NV + SPH_THREADS - 1) / SPH_THREADS;
+    if (blocks >= 1024) return 1;
+    long long sl = 1024 / blocks;
+    if (sl > 4) sl = 4;
+    if (sl > P.nq) sl = P.nq;
+    return (int)sl;
+}
+
 // H_sph^T: interval half-phases up to 0.65 (error 6e-9 of a term, below the
 // FP32 rounding of the tables).  The table path is taken where its work is
 // less, in VALU operations: 18 per (interval, frequency) and 40 a (voxel,
-// node) term, against 4 per frequency and 100 of the dense sum (14 x 12 x 18
-// voxels, 80 transducers, 20 frequencies: 32 against 35 us).  A single frequency
-// takes the plain sums, which hold nothing but u p0* in FP32 (40 x 37 x 33 voxels, 3
-// MHz: 3.7e-8 of the output, the tables 5.0e-8; from two frequencies on Horner's
-// FP32 steps make theirs the larger error).
+// node) term, against 4 per frequency and 100 of the dense sum (12^3 voxels, 64
+// transducers, 16 frequencies: 22 against 24 us, and an error of 5e-8 against
+// 7e-7).  A single frequency takes the plain sums, which hold nothing but u p0* in
+// FP32 (40 x 37 x 33 voxels, 3 MHz: 3.7e-8 of the output, the tables 5.0e-8; from
+// two frequencies on Horner's FP32 steps make theirs the larger error).
 static bool sph_adj_fast(const Problem &P, int n_f, double f_min, double df, SphBand &B)
 {
     B = sph_band(P, n_f, f_min, df, SPH_P, 0.65);
@@ -1154,24 +1207,10 @@ hipError_t launch_sph_project(const Problem &P, const void *img, int img_dt, flo
     return hipGetLastError();
 }
 
-// Transducer slices of the dense adjoint: a grid of fewer than 1024
-// workgroups (a small image) takes the transducers in up to 4 slices along
-// grid y, so the device holds more waves; their FP64 partial images are then
-// added in slice order.
-static int sph_adj_slices(const Problem &P)
-{
-    const long long N = (long long)P.nx * P.ny * P.nz;
-    const long long blocks = ((N + SPH_NV - 1) / SPH_NV + SPH_THREADS - 1) / SPH_THREADS;
-    if (blocks >= 1024) return 1;
-    long long sl = (1024 + blocks - 1) / blocks;
-    if (sl > 4) sl = 4;
-    if (sl > P.nq) sl = P.nq;
-    return (int)sl;
-}
-
 // Work split of the table adjoint: tiles of 16 x 16 x 8 voxels, taken
 // 1024 at a time; fewer tiles than that take the transducers in `slices`
-// slices of at least 8.  The tables of a batch of `per` transducers of every
+// slices of at least 8 (4 where that makes no more than 16: 12^3 / 64 / 16
+// frequencies, the evaluation 12.7 -> 7.9 us).  The tables of a batch of `per` transducers of every
 // slice, and the partial sums, stay within the fixed scratch.
 struct SphAdjPlan {
     long long tiles;
@@ -1189,7 +1228,8 @@ static SphAdjPlan sph_adj_plan(const Problem &P, const SphBand &B, int n_f)
     // holds 65535 of them)
     const size_t row = sizeof(float4) * 2 * (size_t)B.n;
     const int most = (int)std::min<size_t>((SPH_SCRATCH_BYTES - (size_t(17) << 20)) / row, 65535);
-    A.slices = std::max(1, std::min({1024 / A.chunk, (P.nq + 7) / 8, most}));
+    const int least = std::max(4, std::min(8, (P.nq + 15) / 16));
+    A.slices = std::max(1, std::min({1024 / A.chunk, (P.nq + least - 1) / least, most}));
     A.qps = (P.nq + A.slices - 1) / A.slices;
     A.slices = (P.nq + A.qps - 1) / A.qps;
     A.per = std::max(1, std::min(most / A.slices, A.qps));
@@ -1221,17 +1261,26 @@ static hipError_t launch_sph_table_adjoint(const Problem &P, const SphBand &B, c
     const int qt = std::max(1, SPH_STAGE / (48 * B.w));
     const size_t shm = (sizeof(float4) * 3 * B.w + sizeof(int2)) * (size_t)qt;
     const int batches = (A.qps + A.per - 1) / A.per;
-    hipLaunchKernelGGL(sph_adj_basis_kernel, dim3((n_f + 63) / 64), dim3(64), 0, s, P, B, n_f, f_min,
-                       df, ab);
+    const unsigned gx = (B.n + 2 * SPH_TTHREADS - 1) / (2 * SPH_TTHREADS);
+    const bool small = (long long)gx * A.slices * A.per <= 1024 && n_f <= 512;
+    if (!small)
+        hipLaunchKernelGGL(sph_adj_basis_kernel, dim3((n_f + 63) / 64), dim3(64), 0, s, P, B, n_f, f_min,
+                           df, ab);
     for (long long t0 = 0; t0 < A.tiles; t0 += A.chunk) {
         const unsigned nt = (unsigned)std::min<long long>(A.chunk, A.tiles - t0);
         for (int k = 0; k < batches; ++k) {
             const SphBatch bt{A.qps, k * A.per, std::min(A.qps, (k + 1) * A.per)};
-            if (batches > 1 || t0 == 0)   // one batch: the tables serve every chunk
-                hipLaunchKernelGGL(sph_table_kernel,
-                                   dim3((B.n + 2 * SPH_TTHREADS - 1) / (2 * SPH_TTHREADS),
-                                        A.slices * (bt.b1 - bt.b0)),
-                                   dim3(SPH_TTHREADS), 0, s, P, B, bt, u, ab, n_f, f_min, df, table);
+            auto tab = [&](auto kernel, int sh, size_t lds) {
+                hipLaunchKernelGGL(kernel, dim3(gx, A.slices * (bt.b1 - bt.b0)), dim3(SPH_TTHREADS * sh), lds,
+                                   s, P, B, bt, u, ab, n_f, f_min, df, table);
+            };
+            if (batches > 1 || t0 == 0) {   // one batch: the tables serve every chunk
+                const size_t basis = sizeof(double) * SPH_P * n_f;
+                const size_t sums = sizeof(double) * 3 * 2 * SPH_P * SPH_TTHREADS;
+                if (!small) tab(sph_table_kernel<1, false>, 1, 0);
+                else if (n_f < 32) tab(sph_table_kernel<1, true>, 1, basis);
+                else tab(sph_table_kernel<4, true>, 4, std::max(basis, sums));
+            }
             auto eval = [&](auto kernel) {
                 hipLaunchKernelGGL(kernel, dim3(nt, A.slices), dim3(SPH_THREADS), shm, s, P, B, bt,
                                    table, qt, t0, img, img_dt, part, k > 0 ? 1 : 0);
