@@ -330,8 +330,8 @@ fbp_kernel(Problem P, const void *__restrict__ pres, void *__restrict__ img, int
                     }
                 }
                 // li lies in 0 .. win - 2 (fbp_window_holds;
-                // tests/host/fbp_window_check.cpp checks it over every workload
-                // geometry).  Where FP32 distances are too coarse for the proof,
+                // tests/host/fbp_index_check.cpp repeats these operations over the
+                // workloads' geometries and at the limit).  Where FP32 distances are too coarse for the proof,
                 // the unsigned minimum keeps the reads inside the row.
                 const float2 s = row[HELD ? (unsigned)li : min((unsigned)li, (unsigned)(win - 2))];
                 acc_a[v] = fmaf(inv, fmaf(fr, s.y, s.x), acc_a[v]);
