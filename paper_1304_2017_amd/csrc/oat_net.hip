@@ -216,7 +216,7 @@ net_c1_kernel(const void *__restrict__ x, int xdt, int D, int H, int W, const fl
     const unsigned vo = (unsigned)col * 16 + 4 * g;   // the lane's offset in a group's row
     // group k of the plane's 16 groups of 16 voxels along x
     auto group = [&](int lz, int k, auto with_large) {
-        const u16 *__restrict__ xz = xs + lz * C1HY * C1P;
+        const u16 *xz = xs + lz * C1HY * C1P;
         const int ly = k >> 1, lx = (k & 1) * 16;
         u32x4 v;
 #pragma unroll
@@ -309,7 +309,7 @@ net_c2_kernel(const u16 *__restrict__ x, int D, int H, int W, const u32x4 *__res
         if (z + 1 < z1) load(z + 2);
         // operands of input row 0: blocks 0 .. 2 (plane z - 1 + f, dx = g >> 1),
         // block 3 (plane z - 1 + (g >> 1), dx = 2), block 4 (plane z + 1, dx = 2)
-        const u32x4 *__restrict__ p[5];
+        const u32x4 *p[5];
 #pragma unroll
         for (int f = 0; f < 3; ++f) p[f] = xs + ((z - 1 + f) & 3) * C2SLOT + at + (g >> 1);
         p[3] = xs + ((z - 1 + (g >> 1)) & 3) * C2SLOT + at + 2;
@@ -393,7 +393,7 @@ net_c3_kernel(const u16 *__restrict__ a, const void *__restrict__ x, int xdt, in
     const int lx = threadIdx.x % C3X, ly = threadIdx.x / C3X;
     const int gx = x0 + lx, gy = y0 + ly;
     const float b0 = bias ? bias[0] : 0.f;
-    const float *__restrict__ yr = ys + ly * C3HX + lx;
+    const float *yr = ys + ly * C3HX + lx;
     float acc[3] = {b0, b0, b0};   // output planes zi - 1, zi, zi + 1 of input plane zi
     u32x4 v[C3GW];
     auto load = [&](int zi) {
@@ -506,7 +506,7 @@ struct TileCl {
                                                         (i & 1) * 8);
         }
     }
-    __device__ __forceinline__ void store(u32x4 *__restrict__ dst) const
+    __device__ __forceinline__ void store(u32x4 *dst) const
     {
 #pragma unroll
         for (int k = 0; k < L; ++k)
@@ -530,8 +530,8 @@ net_wgrad16_kernel(const u16 *__restrict__ x, const u16 *__restrict__ dy, int D,
     __shared__ u32x4 xs[2 * GHV], gs[2 * GV];
     const int wave = wave_index(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     // address of this lane's 8 bytes of a transposed read at voxel 0
-    const u16 *__restrict__ xl = reinterpret_cast<const u16 *>(xs) + (4 * g + (col >> 2)) * 16 + (col & 3) * 4;
-    const u16 *__restrict__ gl = reinterpret_cast<const u16 *>(gs) + (4 * g + (col >> 2)) * 16 + (col & 3) * 4;
+    const u16 *xl = reinterpret_cast<const u16 *>(xs) + (4 * g + (col >> 2)) * 16 + (col & 3) * 4;
+    const u16 *gl = reinterpret_cast<const u16 *>(gs) + (4 * g + (col >> 2)) * 16 + (col & 3) * 4;
     f32x4 acc[7];
     int toff[7];
 #pragma unroll
@@ -561,7 +561,7 @@ net_wgrad16_kernel(const u16 *__restrict__ x, const u16 *__restrict__ dy, int D,
             const u32x2 a0 = tr_read(gl + (lz * GY + ly) * GX * 16),
                         a1 = tr_read(gl + (lz * GY + ly + 1) * GX * 16);
             const u32x4 av = {a0[0], a0[1], a1[0], a1[1]};
-            const u16 *__restrict__ xr = xl + (lz * GHY + ly) * GHX * 16;
+            const u16 *xr = xl + (lz * GHY + ly) * GHX * 16;
 #pragma unroll
             for (int k = 0; k < 7; ++k) {
                 const u32x2 b0 = tr_read(xr + toff[k]), b1 = tr_read(xr + toff[k] + GHX * 16);
@@ -620,9 +620,9 @@ net_wgrad1_kernel(const u16 *__restrict__ sv, const u16 *__restrict__ tv, int D,
     __shared__ float red[4][2][64][4];
     __shared__ float bred[4];
     const int wave = wave_index(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
-    const u16 *__restrict__ sl = reinterpret_cast<const u16 *>(ss) + (4 * g + (col >> 2)) * 16 + (col & 3) * 4;
+    const u16 *sl = reinterpret_cast<const u16 *>(ss) + (4 * g + (col >> 2)) * 16 + (col & 3) * 4;
     f32x4 acc[2];
-    const u16 *__restrict__ tp[2];
+    const u16 *tp[2];
     bool one[2], none[2];
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
@@ -674,7 +674,7 @@ net_wgrad1_kernel(const u16 *__restrict__ sv, const u16 *__restrict__ tv, int D,
             const u32x4 bv = {b0[0], b0[1], b1[0], b1[1]};
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
-                const u16 *__restrict__ p = tp[m] + (lz * GHY + ly) * GX;
+                const u16 *p = tp[m] + (lz * GHY + ly) * GX;
                 const u32x2 a0 = *reinterpret_cast<const u32x2 *>(p),
                             a1 = *reinterpret_cast<const u32x2 *>(p + GX);
                 u32x4 av = {a0[0], a0[1], a1[0], a1[1]};
