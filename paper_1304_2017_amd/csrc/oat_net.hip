@@ -58,7 +58,7 @@ __device__ __forceinline__ unsigned split_term(float w, int s)
     unsigned b = f_bf(w);
     for (int i = 0; i < s; ++i) {
         const float r = w - bf_f(b);
-        w = fabsf(r) <= 3.4028235e38f ? r : 0.f;   // no remainder of a first term that is not finite
+        w = fabsf(r) <= 0x1.fffffep127f ? r : 0.f;   // no remainder of a first term that is not finite
         b = f_bf(w);
     }
     return b;
@@ -66,15 +66,16 @@ __device__ __forceinline__ unsigned split_term(float w, int s)
 
 // Infinities in a product with a split weight's terms, or with the zeros in
 // unused slots, give NaN where the product with the weight itself is an
-// infinity.  So where values or weights are large enough for that, or not
-// finite, the product with the first terms alone is formed too and stands for
-// the results that it does not leave finite.
-constexpr float LARGE_VALUE = 0x1p90f, LARGE_WEIGHT = 0x1p30f;
-constexpr unsigned LARGE_BITS = 0x6c80;   // LARGE_VALUE as BF16
+// infinity.  C1 forms the product with the first terms alone, too, in tiles whose
+// values or weights are large enough for that, and lets it stand for the results
+// that it does not leave finite; C3 and its gradient take a result that is not
+// finite again from single products.
+constexpr float MAX_F = 3.4028235e38f, LARGE_WEIGHT = 0x1p30f;
+constexpr unsigned LARGE_BITS = 0x6c80;   // 2^90 as BF16
 __device__ __forceinline__ f32x4 first_if_not_finite(f32x4 first, f32x4 all)
 {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) all[r] = fabsf(first[r]) <= 3.4028235e38f ? all[r] : first[r];
+    for (int r = 0; r < 4; ++r) all[r] = fabsf(first[r]) <= MAX_F ? all[r] : first[r];
     return all;
 }
 
@@ -176,8 +177,8 @@ net_c1_kernel(const void *__restrict__ x, int xdt, int D, int H, int W, const fl
     static_assert(C1_THREADS / 64 == 4, "wave_large");
     const int x0 = blockIdx.x * C1X, y0 = blockIdx.y * C1Y, z0 = blockIdx.z * C1Z;
     const size_t plane = (size_t)H * W;
-    unsigned top = 0;   // the largest |value| of this thread's, as bits
-    bool large = false;
+    unsigned top = 0;   // the largest |value| of this thread's, as bits, and |weight|
+    float top_w = 0.f;
     for (int r = threadIdx.x >> 5; r < C1HZ * C1HY; r += C1_THREADS / 32) {
         const int gy = y0 - 1 + r % C1HY, gz = z0 - 1 + r / C1HY;
         const bool in = gy >= 0 && gy < H && gz >= 0 && gz < D;
@@ -201,7 +202,7 @@ net_c1_kernel(const void *__restrict__ x, int xdt, int D, int H, int W, const fl
         off[j] = ((tt / 9) * C1HY + (tt / 3) % 3) * C1P + tt % 3 + col;
         if (t < 27) {
             const float f = w[col * 27 + (flip ? 26 - t : t)];
-            large |= !(fabsf(f) < LARGE_WEIGHT);
+            top_w = fmaxf(top_w, fabsf(f));
 #pragma unroll
             for (int s = 0; s < 3; ++s) a[s][j >> 1] |= split_term(f, s) << (16 * (j & 1));
         }
@@ -209,10 +210,10 @@ net_c1_kernel(const void *__restrict__ x, int xdt, int D, int H, int W, const fl
     f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
     if (bias) b4 = *reinterpret_cast<const f32x4 *>(bias + 4 * g);
     if (frag && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0) write_fragments(w16, flip, frag);
-    const uint64_t lanes = __ballot(large || top >= LARGE_BITS);
+    const uint64_t lanes = __ballot(top_w >= LARGE_WEIGHT || top >= LARGE_BITS);
     if (lane == 0) wave_large[wave] = lanes != 0;
     __syncthreads();
-    large = wave_large[0] | wave_large[1] | wave_large[2] | wave_large[3];
+    const int large = wave_large[0] | wave_large[1] | wave_large[2] | wave_large[3];
     const unsigned vo = (unsigned)col * 16 + 4 * g;   // the lane's offset in a group's row
     // group k of the plane's 16 groups of 16 voxels along x
     auto group = [&](int lz, int k, auto with_large) {
@@ -356,6 +357,21 @@ constexpr int C3G = (C3HV + 15) / 16;            // groups of 16 voxels
 constexpr int C3P = C3G * 16 + 4;                // row pitch of Y: 4 rows apart are 16 banks apart
 constexpr int C3GW = (C3G + C3_WAVES - 1) / C3_WAVES;
 
+// C3 at one voxel from single FP32 products: the value where the split weights'
+// sum is not finite.
+__device__ __attribute__((noinline)) float c3_value(const u16 *__restrict__ a, int D, int H, int W,
+                                                    const float *__restrict__ w, float bias, int x, int y, int z)
+{
+    float sum = bias;
+    for (int ci = 0; ci < 16 && sum == sum; ++ci)
+        for (int t = 0; t < 27; ++t) {
+            const int px = x + t % 3 - 1, py = y + t / 3 % 3 - 1, pz = z + t / 9 - 1;
+            const bool in = px >= 0 && px < W && py >= 0 && py < H && pz >= 0 && pz < D;
+            sum = fmaf(w[ci * 27 + t], in ? bf_f(a[(((size_t)pz * H + py) * W + px) * 16 + ci]) : 0.f, sum);
+        }
+    return sum;
+}
+
 __global__ void __launch_bounds__(C3_THREADS) __attribute__((amdgpu_waves_per_eu(4, 4)))
 net_c3_kernel(const u16 *__restrict__ a, const void *__restrict__ x, int xdt, int D, int H, int W,
               const float *__restrict__ w, const float *__restrict__ bias, u16 *__restrict__ z, int zr)
@@ -367,7 +383,6 @@ net_c3_kernel(const u16 *__restrict__ a, const void *__restrict__ x, int xdt, in
     const int wave = wave_index(), lane = threadIdx.x & 63, col = lane & 15, g = lane >> 4;
     // weights: [tap tile][terms 1 and 2 | term 3]
     u32x4 wt[2][2];
-    bool large_w = false;
 #pragma unroll
     for (int m = 0; m < 2; ++m)
 #pragma unroll
@@ -376,11 +391,9 @@ net_c3_kernel(const u16 *__restrict__ a, const void *__restrict__ x, int xdt, in
             const int t = 16 * m + col;
             if (t < 27 && (p == 0 || g < 2))
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float f = w[(8 * (g & 1) + j) * 27 + t];
-                    large_w |= !(fabsf(f) < LARGE_WEIGHT);
-                    wt[m][p][j >> 1] |= split_term(f, p == 0 ? g >> 1 : 2) << (16 * (j & 1));
-                }
+                for (int j = 0; j < 8; ++j)
+                    wt[m][p][j >> 1] |= split_term(w[(8 * (g & 1) + j) * 27 + t], p == 0 ? g >> 1 : 2)
+                                        << (16 * (j & 1));
         }
     // this wave's halo voxels: groups wave, wave + 8, ...
     int idx[C3GW];        // offset in the plane, -1 outside the volume
@@ -404,17 +417,8 @@ net_c3_kernel(const u16 *__restrict__ a, const void *__restrict__ x, int xdt, in
                 v[k] = *reinterpret_cast<const u32x4 *>(a + (zi * plane + idx[k]) * 16 + (g & 1) * 8);
         }
     };
-    auto put = [&](int grp, f32x4 r0, f32x4 r1) {
-        float *dst = ys + grp * 16 + col;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            dst[(4 * g + r) * C3P] = r0[r];
-            if (16 + 4 * g + r < 27) dst[(16 + 4 * g + r) * C3P] = r1[r];
-        }
-    };
     load(z0 - 1);
     for (int zi = z0 - 1; zi <= z1; ++zi) {
-        bool large = large_w;
 #pragma unroll
         for (int k = 0; k < C3GW; ++k) {
             const int grp = wave + k * C3_WAVES;
@@ -424,21 +428,11 @@ net_c3_kernel(const u16 *__restrict__ a, const void *__restrict__ x, int xdt, in
             r1 = mfma(wt[1][1], v[k], r1);
             r0 = mfma(wt[0][0], v[k], r0);
             r1 = mfma(wt[1][0], v[k], r1);
-            large |= !(fabsf(r0[0]) < LARGE_VALUE);   // (a value that large makes every row so)
-            put(grp, r0, r1);
-        }
-        if (__any(large)) {
+            float *dst = ys + grp * 16 + col;
 #pragma unroll
-            for (int k = 0; k < C3GW; ++k) {
-                const int grp = wave + k * C3_WAVES;
-                if (grp >= C3G) break;
-                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-                const u32x4 first = g < 2 ? v[k] : u32x4{0u, 0u, 0u, 0u};
-                f32x4 r0 = mfma(wt[0][0], v[k], mfma(wt[0][1], v[k], zero));
-                f32x4 r1 = mfma(wt[1][0], v[k], mfma(wt[1][1], v[k], zero));
-                r0 = first_if_not_finite(mfma(wt[0][0], first, zero), r0);
-                r1 = first_if_not_finite(mfma(wt[1][0], first, zero), r1);
-                put(grp, r0, r1);
+            for (int r = 0; r < 4; ++r) {
+                dst[(4 * g + r) * C3P] = r0[r];
+                if (16 + 4 * g + r < 27) dst[(16 + 4 * g + r) * C3P] = r1[r];
             }
         }
         if (zi < z1) load(zi + 1);   // in flight while the sums run
@@ -454,7 +448,9 @@ net_c3_kernel(const u16 *__restrict__ a, const void *__restrict__ x, int xdt, in
         const int zo = zi - 1;
         if (zo >= z0 && gx < W && gy < H) {
             const size_t o = zo * plane + (size_t)gy * W + gx;
-            z[o] = (u16)f_bf(bf_f(in_bits(x, o, xdt)) + bf_f(f_bf(acc[0])));
+            float r = acc[0];
+            if (!(fabsf(r) <= MAX_F)) r = c3_value(a, D, H, W, w, b0, gx, gy, zo);
+            z[o] = (u16)f_bf(bf_f(in_bits(x, o, xdt)) + bf_f(f_bf(r)));
         }
         acc[0] = acc[1];
         acc[1] = acc[2];
@@ -699,7 +695,7 @@ net_wgrad1_kernel(const u16 *__restrict__ sv, const u16 *__restrict__ tv, int D,
         const int t = 16 * m + 4 * (l >> 4) + r, ch = l & 15;
         float v = (red[0][m][l][r] + red[1][m][l][r]) + (red[2][m][l][r] + red[3][m][l][r]);
         // an infinite activation times the zeros around t is no part of C3's sum
-        if (C3 && t < 27 && !(fabsf(v) <= 3.4028235e38f))
+        if (C3 && t < 27 && !(fabsf(v) <= MAX_F))
             v = pair_sum(sv, tv, D, H, W, tx, ty, tiles, ch, t);
         if (t < 27)
             dst[ch * 27 + (C3 ? 26 - t : t)] = v;
