@@ -1169,11 +1169,14 @@ static hipError_t launch_sph_moments(const Problem &P, const SphBand &B, const v
                                n_f, f_min, df, u);
         };
         // Frequencies share the loads of the moments where enough waves are
-        // left without it; few blocks split the intervals over more waves.
+        // left without it; few blocks split the intervals over more waves, each
+        // of which pays for the basis of its frequencies (5% phantoms: 24^3 / 209 /
+        // 81, 418 blocks: 4 waves 40, 8 34, 16 38 us; 200 blocks 37, 30, 28; 800
+        // blocks 38, 41, 54; shares of a wave, 12^3 / 500 / 16: 18, 20, 24).
         const long long blocks = (long long)nq * ((n_f + 63) / 64);
-        const int nw = blocks >= 1024 ? 4 : (blocks >= 512 ? 8 : 16);
-        if (n_f <= 16) synth(sph_synth_kernel<NM, 1, 4>, 1, nw);
-        else if (n_f <= 32) synth(sph_synth_kernel<NM, 1, 2>, 1, nw);
+        const int nw = blocks >= 768 ? 4 : (blocks >= 256 ? 8 : 16);
+        if (n_f <= 16) synth(sph_synth_kernel<NM, 1, 4>, 1, 4);
+        else if (n_f <= 32) synth(sph_synth_kernel<NM, 1, 2>, 1, 4);
         else if (blocks >= 2048 && n_f > 128) synth(sph_synth_kernel<SPH_M, 4, 1>, 4, 4);
         else if (blocks >= 2048 && n_f > 64) synth(sph_synth_kernel<SPH_M, 2, 1>, 2, 4);
         else synth(sph_synth_kernel<SPH_M, 1, 1>, 1, nw);

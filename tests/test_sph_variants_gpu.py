@@ -1,7 +1,7 @@
 """H_sph and H_sph^T by their kernels' variants.  H_sph: the variants of its list, moment and synthesis kernels: voxel counts around the list from
 one workgroup (8192) and the moments' two block sizes (24576 terms), frequency counts around the
-shares of a wave (16, 32) and the frequencies a lane takes (64, 128), transducer counts around the
-waves of a block (512, 1024, 2048 blocks).  H_sph^T: frequency counts around those that the table kernel takes in one
+shares of a wave (16, 32) and the frequencies a lane takes (64, 128), block counts around the
+waves of a block (256, 768, 2048).  H_sph^T: frequency counts around those that the table kernel takes in one
 group of threads, in four, and with the basis from a launch of its own (32, 512), transducer counts
 around the slices of 4 to 8.  Sampled rows and voxels against FP64 at 5e-7, the gate of the other
 interval-polynomial tests, and the same bits again."""
@@ -18,7 +18,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("shape,q,n_f,f_min,df", [
     ((32, 16, 16), 3, 15, 0.4, 0.3), ((32, 16, 16), 1100, 16, 0.3, 0.3), ((11, 27, 28), 600, 17, 0.3, 0.25),
     ((33, 16, 16), 5, 1, 2.0, 0.1), ((24, 32, 32), 40, 31, 0.2, 0.15), ((25, 32, 32), 40, 32, 0.2, 0.15),
-    ((20, 20, 20), 1100, 33, 0.2, 0.1), ((12, 12, 12), 520, 9, 0.0, 0.4), ((12, 12, 12), 1030, 20, 0.0, 0.2),
+    ((20, 20, 20), 1100, 33, 0.2, 0.1),
+    ((13, 12, 12), 255, 40, 0.2, 0.1), ((13, 12, 12), 384, 70, 0.2, 0.05), ((12, 12, 12), 520, 9, 0.0, 0.4), ((12, 12, 12), 1030, 20, 0.0, 0.2),
     # two and four frequencies a lane, ragged in the last block
     ((14, 12, 10), 1100, 100, 0.05, 0.05), ((14, 12, 10), 600, 257, 0.02, 0.02), ((9, 8, 7), 2048, 65, 0.1, 0.05)])
 def test_variants(shape, q, n_f, f_min, df):
