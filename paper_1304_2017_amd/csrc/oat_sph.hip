@@ -68,6 +68,10 @@ constexpr int SPH_MTHREADS = 1024;
 // phantom of 28^3 / 2048, 32 frequencies: 78 -> 72 us; every voxel set: 198 -> 202,
 // at 64^3 1573 -> 1653).
 constexpr int SPH_FEW = 24576;
+// Intervals up to which 17 to 32 frequencies take two shares a wave: their moments
+// come in vector loads then, two addresses a wave, which bind in long shares (64 x
+// 13 x 47 / 1329 / 27, 915 intervals: 72 us for 65).
+constexpr int SPH_SUB_N = 768;
 constexpr int SPH_RUN = 1 << 20;         // terms summed in integers at a time
 constexpr int SPH_TX = 16, SPH_TZ = 8;   // voxel tile of the table adjoint: 16 x 16 x 8
 constexpr int SPH_TVOX = SPH_TX * SPH_TX * SPH_TZ;
@@ -392,8 +396,13 @@ __device__ __forceinline__ void sph_dist(double r2, double &d, double &rd)
 }
 
 // --- H_sph -----------------------------------------------------------------
-// Voxels per block of the list, and values per thread of one.
-constexpr int SPH_LIST = 8 * SPH_THREADS;
+// Voxels per block of the list.  A block's entries go thread by thread, each
+// thread's voxels a quarter of the block apart: neighbours in the list are then
+// not neighbours in the image, whose equal distances would meet in the same moments
+// (voxels in order: 31 x 54 x 41 / 76 / 84 with 9 face nodes 326 us, 284; 64^3 / 512 /
+// 64 499, 413; eight voxels a thread 237 and 433, but 4 us more for the list of a
+// phantom).
+constexpr int SPH_LIST = 4 * SPH_THREADS;
 
 // A thread's values of the block's voxels n0 .. n1 - 1; returns the block's
 // count of non-zero ones, and in wcnt each wave's.
@@ -478,17 +487,16 @@ sph_list_kernel(Problem P, const void *__restrict__ img, int img_dt, long long n
     }
     for (int w = 0; w < wave; ++w) pos += wcnt[w];
 #pragma unroll
-    for (int i = 0; i < SPH_LIST / SPH_THREADS; ++i) {
-        const uint64_t bal = __ballot(v[i] != 0.f);
+    for (int i = 0; i < SPH_LIST / SPH_THREADS; ++i)   // the lanes before this one
+        pos += __popcll(__ballot(v[i] != 0.f) & ((1ull << lane) - 1ull));
+#pragma unroll
+    for (int i = 0; i < SPH_LIST / SPH_THREADS; ++i)
         if (v[i] != 0.f) {
             const long long n = n0 + (long long)blockIdx.x * SPH_LIST + i * SPH_THREADS + threadIdx.x;
             const long long xy = (long long)P.nx * P.ny;
             const int iz = (int)(n / xy), r = (int)(n - iz * xy), iy = r / P.nx;
-            list[pos + __popcll(bal & ((1ull << lane) - 1ull))] =
-                make_int4(r - iy * P.nx, iy, iz, (int)__float_as_uint(v[i]));
+            list[pos++] = make_int4(r - iy * P.nx, iy, iz, (int)__float_as_uint(v[i]));
         }
-        pos += __popcll(bal);
-    }
 }
 
 // The same list and header of at most SPH_ONE voxels from one workgroup: one
@@ -527,16 +535,14 @@ sph_list_one_kernel(Problem P, const void *__restrict__ img, int img_dt, int N, 
             base += c;
         }
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const uint64_t bal = __ballot(v[i] != 0.f);
+        for (int i = 0; i < PER; ++i) pos += __popcll(__ballot(v[i] != 0.f) & ((1ull << lane) - 1ull));
+#pragma unroll
+        for (int i = 0; i < PER; ++i)
             if (v[i] != 0.f) {
                 const int n = b0 + i * SPH_ONE_THREADS + threadIdx.x;
                 const int row = n / P.nx, iz = row / P.ny;
-                list[pos + __popcll(bal & ((1ull << lane) - 1ull))] =
-                    make_int4(n - row * P.nx, row - iz * P.ny, iz, (int)__float_as_uint(v[i]));
+                list[pos++] = make_int4(n - row * P.nx, row - iz * P.ny, iz, (int)__float_as_uint(v[i]));
             }
-            pos += __popcll(bal);
-        }
     }
     for (int o = 32; o > 0; o >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, o));
     if (lane == 0) wmax[wave] = m;
@@ -556,6 +562,16 @@ __device__ __forceinline__ int sph_parts(long long n, int parts, int fixed)
     return fixed ? parts : (int)max(1ll, min((long long)parts, n >> 14));
 }
 
+// Few listed terms: the synthesis then sums over the terms themselves, and the
+// moments are not formed.  most: as many as the intervals, a third where there are
+// enough blocks to fill the device (a term's own exponentials are three times an
+// interval's operations: 56 x 16 x 16 / 976 / 139, 154 us for 102); 0 where the
+// voxels come in several passes.
+__device__ __forceinline__ bool sph_direct(int total, int ns, int most)
+{
+    return (long long)total * ns <= most;
+}
+
 // Moments of one transducer (q = q0 + blockIdx.x) over a part of the listed
 // voxels (blockIdx.y of sph_parts): M[part][q - q0][i][m] = sum over the (voxel, face
 // node) terms in interval i of w t^m, w = value x node weight / (2 pi d),
@@ -572,7 +588,7 @@ __device__ __forceinline__ int sph_parts(long long n, int parts, int fixed)
 template <int NM>
 __global__ void __launch_bounds__(SPH_MTHREADS)
 sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int *__restrict__ hdr,
-                  int q0, double *__restrict__ M, int add, int fixed)
+                  int q0, double *__restrict__ M, int add, int fixed, int most)
 {
     constexpr int MROW = sph_mrow(NM);
     extern __shared__ unsigned long long mom[];   // [n][MROW]
@@ -580,7 +596,7 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
     const int total = hdr[0];
     const unsigned amax = (unsigned)hdr[1];
     const int parts = sph_parts((long long)total * NS, gridDim.y, fixed);
-    if ((int)blockIdx.y >= parts) return;
+    if ((int)blockIdx.y >= parts || (most > 0 && sph_direct(total, NS, most))) return;
     const int len = (total + parts - 1) / parts;
     const int i0 = (int)blockIdx.y * len, i1 = min(total, i0 + len);
     const int run = min(max(len, 1), SPH_RUN / NS);
@@ -642,15 +658,17 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
 // through the scalar cache (LF frequencies share a load); the sum over a
 // wave's intervals is Horner's rule in exp(-j 2 pi f step / c0), FP64, times
 // one accurate phase.  The waves split the intervals evenly and are added in
-// wave order.  SUB > 1 (at most 64 / SUB frequencies): a wave's lanes are SUB
-// such shares, so that none is idle (a 5% phantom of 12^3 / 2048, 16 frequencies:
+// wave order.  Where sph_direct holds (images with few voxels set), the shares are
+// of the terms, each with its own exponential (phantoms of 34 x 15 x 55 / 931 / 77
+// and 35 x 22 x 45 / 243 / 263: the calls 101 -> 30 and 60 -> 50 us).  SUB > 1 (at
+// most 64 / SUB frequencies): a wave's lanes are SUB such shares, so that none is idle (a 5% phantom of 12^3 / 2048, 16 frequencies:
 // the call 47 -> 31 us).  Bound by FP64 VALU issue: 10 operations per (interval,
 // frequency).
 template <int NM, int LF, int SUB>
 __global__ void __launch_bounds__(LF == 1 ? 1024 : 256)
 sph_synth_kernel(Problem P, SphBand B, const double *__restrict__ M, const int *__restrict__ hdr,
-                 int q0, int max_parts, int fixed, int n_f, double f_min, double df,
-                 float2 *__restrict__ u)
+                 const int4 *__restrict__ list, int q0, int max_parts, int fixed, int most, int n_f,
+                 double f_min, double df, float2 *__restrict__ u)
 {
     static_assert(SUB == 1 || LF == 1, "shares of a wave have one frequency a lane");
     constexpr int F = 64 / SUB;
@@ -664,49 +682,81 @@ sph_synth_kernel(Problem P, SphBand B, const double *__restrict__ M, const int *
     const double tau = B.step / P.c0d;   // us per interval
     const int share = (B.n + NS - 1) / NS, ia = min(B.n, sh * share), ib = min(B.n, ia + share);
     const int first = sph_first(P, B, q);
-    double a[LF][NM], zc[LF], zs[LF], tr[LF], ti[LF];
+    double tr[LF], ti[LF];
 #pragma unroll
-    for (int v = 0; v < LF; ++v) {
-        const double f = f_min + df * (double)min(lb + v * 64 + lane, n_f - 1);
-        sph_basis<NM>(B, f, a[v]);
-        sincos_turns_d(frac_turn(f * tau), zc[v], zs[v]);
-        tr[v] = ti[v] = 0.0;
-    }
-    for (int c = 0; c < parts; ++c) {
-        const double *__restrict__ row = M + (((size_t)c * gridDim.x + blockIdx.x) * B.n + ib) * NM;
-        double sr[LF], si[LF];
-#pragma unroll
-        for (int v = 0; v < LF; ++v) sr[v] = si[v] = 0.0;
-#pragma unroll 2
-        for (int i = ib; i > ia; --i) {
-            row -= NM;
+    for (int v = 0; v < LF; ++v) tr[v] = ti[v] = 0.0;
+    if (most > 0 && sph_direct(hdr[0], P.sph_ns, most)) {
+        // (d / c0, w) of every term in LDS, a share's terms one after the other
+        const int terms = hdr[0] * P.sph_ns;
+        double2 *term = red + (size_t)NS * LF * F;
+        for (int k = threadIdx.x; k < terms; k += blockDim.x) {
+            const int4 en = list[k / P.sph_ns];
+            const double4 fp = P.sph_pts[(size_t)q * P.sph_ns + k % P.sph_ns];
+            const double dx = fma((double)en.x, P.dxd, P.x0) - fp.x, dy = fma((double)en.y, P.dxd, P.y0) - fp.y,
+                         dz = fma((double)en.z, P.dxd, P.z0) - fp.z;
+            double d, rd;
+            sph_dist<true>(fma(dz, dz, fma(dy, dy, dx * dx)), d, rd);
+            term[k] = make_double2(d / P.c0d, (double)__uint_as_float((unsigned)en.w) * fp.w * rd *
+                                                  0.15915494309189535);
+        }
+        __syncthreads();
+        for (int k = sh; k < terms; k += NS) {
+            const double2 t = term[k];
 #pragma unroll
             for (int v = 0; v < LF; ++v) {
-                // S <- (even - j odd) + S (zc - j zs)
-                double r = fma(sr[v], zc[v], fma(si[v], zs[v], a[v][0] * row[0]));
-                double m = fma(si[v], zc[v], fma(-sr[v], zs[v], -(a[v][1] * row[1])));
+                const double f = f_min + df * (double)min(lb + v * 64 + lane, n_f - 1);
+                double c, s;
+                sincos_turns_d(frac_turn(f * t.x), c, s);
+                tr[v] = fma(t.y, c, tr[v]);
+                ti[v] = fma(-t.y, s, ti[v]);
+            }
+        }
 #pragma unroll
-                for (int k = 2; k < NM; k += 2) {
-                    r = fma(a[v][k], row[k], r);
-                    m = fma(-a[v][k + 1], row[k + 1], m);
+        for (int v = 0; v < LF; ++v) red[(sh * LF + v) * F + lane] = make_double2(tr[v], ti[v]);
+    } else {
+        double a[LF][NM], zc[LF], zs[LF];
+#pragma unroll
+        for (int v = 0; v < LF; ++v) {
+            const double f = f_min + df * (double)min(lb + v * 64 + lane, n_f - 1);
+            sph_basis<NM>(B, f, a[v]);
+            sincos_turns_d(frac_turn(f * tau), zc[v], zs[v]);
+        }
+        for (int c = 0; c < parts; ++c) {
+            const double *__restrict__ row = M + (((size_t)c * gridDim.x + blockIdx.x) * B.n + ib) * NM;
+            double sr[LF], si[LF];
+#pragma unroll
+            for (int v = 0; v < LF; ++v) sr[v] = si[v] = 0.0;
+#pragma unroll 2
+            for (int i = ib; i > ia; --i) {
+                row -= NM;
+#pragma unroll
+                for (int v = 0; v < LF; ++v) {
+                    // S <- (even - j odd) + S (zc - j zs)
+                    double r = fma(sr[v], zc[v], fma(si[v], zs[v], a[v][0] * row[0]));
+                    double m = fma(si[v], zc[v], fma(-sr[v], zs[v], -(a[v][1] * row[1])));
+#pragma unroll
+                    for (int k = 2; k < NM; k += 2) {
+                        r = fma(a[v][k], row[k], r);
+                        m = fma(-a[v][k + 1], row[k + 1], m);
+                    }
+                    sr[v] = r;
+                    si[v] = m;
                 }
-                sr[v] = r;
-                si[v] = m;
+            }
+#pragma unroll
+            for (int v = 0; v < LF; ++v) {
+                tr[v] += sr[v];
+                ti[v] += si[v];
             }
         }
 #pragma unroll
         for (int v = 0; v < LF; ++v) {
-            tr[v] += sr[v];
-            ti[v] += si[v];
+            // times exp(-j theta) of the share's first interval
+            const double f = f_min + df * (double)min(lb + v * 64 + lane, n_f - 1);
+            double c, s;
+            sincos_turns_d(frac_turn(f * tau * (double)(first + ia)), c, s);
+            red[(sh * LF + v) * F + lane] = make_double2(fma(tr[v], c, ti[v] * s), fma(ti[v], c, -(tr[v] * s)));
         }
-    }
-#pragma unroll
-    for (int v = 0; v < LF; ++v) {
-        // times exp(-j theta) of the share's first interval
-        const double f = f_min + df * (double)min(lb + v * 64 + lane, n_f - 1);
-        double c, s;
-        sincos_turns_d(frac_turn(f * tau * (double)(first + ia)), c, s);
-        red[(sh * LF + v) * F + lane] = make_double2(fma(tr[v], c, ti[v] * s), fma(ti[v], c, -(tr[v] * s)));
     }
     __syncthreads();
     for (int t = threadIdx.x; t < F * LF && lb + t < n_f; t += blockDim.x) {
@@ -1044,13 +1094,15 @@ static double sph_fwd_phase(int n_f, double f_min, double df)
 // 1.58, 0.4: 1.55, 0.45: 1.55; eight at 0.5: 2.13): their error, 1 to 2e-8 of the
 // output, is below that of the plain sums, whose runs of SPH_FB frequencies
 // start from FP32 exponentials (together with the outputs' rounding of 2.5e-8, 3
-// to 5e-8 against 7 to 11e-8).  A single run that starts at or near the frequency
-// 0 starts exactly, and leaves the plain sums nothing but that rounding: eight
+// to 5e-8 against 7 to 11e-8).  A run that starts at or near the frequency 0
+// starts exactly, and leaves the plain sums nothing but that rounding: eight
 // moments at 0.5 add as little (40 x 37 x 33 voxels, 16 frequencies from 0 to 4.7
-// MHz: 2.54e-8 either way, six moments 3.30e-8).
+// MHz: 2.54e-8 either way, six moments 3.30e-8).  A few frequencies of a second
+// run leave them ahead of six moments (19 x 58 x 43, 36 frequencies: 2.81e-8 against
+// 3.07e-8; 40: 3.48e-8 against 3.11e-8).
 static int sph_moments(const SphBand &B, const Problem &P, int n_f, double f_min)
 {
-    return n_f <= SPH_FB && f_min * B.reach < 0.25 * P.c0d ? SPH_M8 : SPH_M;
+    return n_f <= SPH_FB + 8 && f_min * B.reach < 0.25 * P.c0d ? SPH_M8 : SPH_M;
 }
 
 // The moment path is taken when a transducer's moments fit the LDS and its work
@@ -1145,6 +1197,8 @@ static hipError_t launch_sph_moments(const Problem &P, const SphBand &B, const v
     const int threads_m = N * P.sph_ns <= SPH_FEW ? SPH_MTHREADS / 2 : SPH_MTHREADS;
     for (int q0 = 0; q0 < P.nq; q0 += qb) {
         const int nq = std::min(qb, P.nq - q0);
+        const long long blocks = (long long)nq * ((n_f + 63) / 64);
+        const int most = fixed ? 0 : (blocks >= 768 ? B.n / 3 : B.n);
         for (long long n0 = 0; n0 < N; n0 += SPH_PASS) {
             const long long n1 = std::min(N, n0 + SPH_PASS);
             // (one pass: its list serves every batch of transducers)
@@ -1159,27 +1213,29 @@ static hipError_t launch_sph_moments(const Problem &P, const SphBand &B, const v
             }
             hipLaunchKernelGGL(sph_moment_kernel<NM>, dim3(nq, parts), dim3(threads_m),
                                sizeof(unsigned long long) * sph_mrow(NM) * B.n, s, P, B, list, hdr, q0, M,
-                               n0 > 0 ? 1 : 0, fixed);
+                               n0 > 0 ? 1 : 0, fixed, most);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
         }
         auto synth = [&](auto kernel, int lf, int nw) {
             hipLaunchKernelGGL(kernel, dim3(nq, (n_f + 64 * lf - 1) / (64 * lf)), dim3(64 * nw),
-                               sizeof(double2) * (size_t)(64 * lf * nw), s, P, B, M, hdr, q0, parts, fixed,
-                               n_f, f_min, df, u);
+                               sizeof(double2) * (size_t)(64 * lf * nw + most), s, P, B, M, hdr, list, q0,
+                               parts, fixed, most, n_f, f_min, df, u);
         };
         // Frequencies share the loads of the moments where enough waves are
         // left without it; few blocks split the intervals over more waves, each
         // of which pays for the basis of its frequencies (5% phantoms: 24^3 / 209 /
         // 81, 418 blocks: 4 waves 40, 8 34, 16 38 us; 200 blocks 37, 30, 28; 800
-        // blocks 38, 41, 54; shares of a wave, 12^3 / 500 / 16: 18, 20, 24).
-        const long long blocks = (long long)nq * ((n_f + 63) / 64);
-        const int nw = blocks >= 768 ? 4 : (blocks >= 256 ? 8 : 16);
-        if (n_f <= 16) synth(sph_synth_kernel<NM, 1, 4>, 1, 4);
-        else if (n_f <= 32) synth(sph_synth_kernel<NM, 1, 2>, 1, 4);
+        // blocks 38, 41, 54; shares of a wave, 12^3 / 500 / 16: 18, 20, 24).  Where
+        // the voxels come in parts there is a set of moments for each (64^3 / 64 /
+        // 256, every voxel set, 256 blocks: 8 waves 178, 16 133).
+        const bool sets = parts > 1;
+        const int nw = blocks >= (sets ? 1024 : 768) ? 4 : (blocks >= (sets ? 512 : 256) ? 8 : 16);
+        if (n_f <= 16) synth(sph_synth_kernel<NM, 1, 4>, 1, sets ? 8 : 4);
+        else if (n_f <= 32 && B.n <= SPH_SUB_N) synth(sph_synth_kernel<NM, 1, 2>, 1, sets ? 8 : 4);
         else if (blocks >= 2048 && n_f > 128) synth(sph_synth_kernel<SPH_M, 4, 1>, 4, 4);
         else if (blocks >= 2048 && n_f > 64) synth(sph_synth_kernel<SPH_M, 2, 1>, 2, 4);
-        else synth(sph_synth_kernel<SPH_M, 1, 1>, 1, nw);
+        else synth(sph_synth_kernel<NM, 1, 1>, 1, nw);
     }
     return hipGetLastError();
 }

@@ -1,5 +1,5 @@
-"""H_sph of one short run of frequencies from 0 (or from where every phase is a fraction of a turn):
-the plain sums over such a band are exact to their outputs' rounding to FP32, and so has the interval
+"""H_sph of one short run of frequencies from 0 (or from where every phase is a fraction of a turn),
+and a few more: the plain sums over such a band are exact to their outputs' rounding to FP32, and so has the interval
 path to be.  The error against FP64 may exceed that of the exact values rounded once by no more than
 5e-9 of the 2-norm (eight moments an interval: about 1e-9; six: 2e-8) in quadrature."""
 import numpy as np
@@ -13,6 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n_f,f_min,df,faces", [(16, 0.0, 0.3125, 0), (32, 0.0, 0.15625, 0), (7, 0.0, 0.1, 0),
+                                                (36, 0.0, 0.139, 0),
                                                 (16, 0.002, 0.05, 0), (20, 0.0, 0.2, 2), (1, 0.01, 0.5, 0)])
 @pytest.mark.parametrize("image", ["iterate", "phantom", "smooth"])
 def test_as_exact_as_the_plain_sums(n_f, f_min, df, faces, image):
