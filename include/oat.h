@@ -184,7 +184,9 @@ int oat_backproject(oat_plan *plan, const void *data, oat_dtype data_dtype, void
  *   img_n = -1/(pi Gamma c0 dt) sum_q a_q/|r_q| { [(k+1+tau)/(kt+tau) - 1.5] p[q,k]
  *                                              + [1.5 - (k+tau)/(kt+tau)] p[q,k+1] }
  * with kt = (|r_n - r_q|/c0 - t0)/dt, k = floor(kt), tau = t0/dt and p = 0
- * outside [0, n_t).  pres: device [n_det][n_t]; img: device [nz][ny][nx]. */
+ * outside [0, n_t).  pres: device [n_det][n_t]; img: device [nz][ny][nx].
+ * The samples that a 16 x 16 x 8 block of voxels can meet, ceil(22.3 dx/(c0 dt))
+ * + 6, must not exceed 8192 (dx up to 367 samples); OAT_ERR_DEVICE otherwise. */
 int oat_fbp(oat_plan *plan, const void *pres, oat_dtype pres_dtype, void *img,
             oat_dtype img_dtype, uint32_t flags, void *stream);
 
@@ -223,12 +225,16 @@ int oat_deconvolve(oat_plan *plan, const void *u, oat_dtype u_dtype, void *p, oa
  * alpha_n is the voxel's absorbed-energy density; r_n are the plan's nodes.
  * img: device [nz][ny][nx] (oat_dtype); u: device [n_det][n_f] complex FP32,
  * interleaved (re, im).  A transducer's sum over frequencies is a function
- * of the distance alone: larger problems form it once per transducer, as
+ * of the distance alone: most problems form it once per transducer, as
  * polynomials on intervals of the distance, and H_sph bins the voxels'
- * weights into the same intervals' moments; smaller ones evaluate every
- * (transducer, frequency, voxel) term.  Phases and sums are FP64 on both
- * paths; errors against FP64 are about 3e-8 (H_sph) and 5e-8 (H_sph^T) of
- * the output's 2-norm with the polynomials, 1e-7 and 1e-6 with the plain sums.
+ * weights into the same intervals' moments; the smallest ones evaluate every
+ * (transducer, frequency, voxel) term.  So does H_sph, at up to twenty times
+ * the cost, where a transducer's moments exceed the LDS: (half diagonal of the
+ * grid + that of the faces) x highest frequency / c0 above 170 (a half diagonal
+ * of 51 mm at 5 MHz and 1.5 mm/us), 137 for a narrow band.  Phases and sums are
+ * FP64 on all paths; errors against FP64 are 2.5 to 5e-8 (H_sph) and 5e-8
+ * (H_sph^T) of the output's 2-norm with the polynomials, up to 1e-7 and 1e-6
+ * with the plain sums.
  * 1 <= n_f <= 4096, f_min >= 0, df > 0,
  * flags: 0 or OAT_FLAG_DETERMINISTIC.  The two calls share a workspace in
  * the plan and may allocate or grow it.  Results are deterministic (sums in a

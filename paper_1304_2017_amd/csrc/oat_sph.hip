@@ -14,14 +14,16 @@
 // transducer).  The polynomials' errors, as a share of a term, stay below
 // 4e-8 rms over the band (H_sph, degree 5; 1 to 2e-8 of the output, whose
 // rounding to FP32 is 2.5e-8; degree 7 where the plain sums have no other error
-// than that) and 7e-9 (H_sph^T, degree 7, whose tables are rounded to FP32).  Measured at 64^3 / 2048 transducers / 256
-// frequencies against the plain sums: H_sph of an iterate 29.0 -> 1.55 ms, of
-// a phantom (4.7% of its voxels set) 1.29 -> 0.30 ms, H_sph^T 18.2 -> 0.76 ms.
+// than that) and 7e-9 (H_sph^T, degree 7, whose tables are rounded to FP32).
+// Measured at 64^3 / 2048 transducers / 256 frequencies against the plain sums:
+// H_sph of an iterate 29.0 -> 1.49 ms, of a phantom (4.7% of its voxels set)
+// 1.75 -> 0.31 ms, H_sph^T 18.2 -> 0.75 ms.
 //
-// Small problems take the plain sums over every (transducer, frequency,
-// voxel) term (sph_fwd_kernel, sph_adj_kernel): distances and phases in FP64
-// (a phase of hundreds of turns must keep ~1e-7 turn), an accurate sincos of
-// the phase's fractional turn followed by short recurrences along l (an FP64
+// The plain sums over every (transducer, frequency, voxel) term (sph_fwd_kernel,
+// sph_adj_kernel) remain for the smallest problems, for H_sph^T of one frequency
+// and for H_sph where a transducer's moments exceed the LDS: distances and phases
+// in FP64 (a phase of hundreds of turns must keep ~1e-7 turn), an accurate sincos
+// of the phase's fractional turn followed by short recurrences along l (an FP64
 // rotation by an FP64 step in the forward kernel, FP32 Horner's rule in the
 // adjoint), sums in FP64.
 #include <algorithm>
