@@ -232,7 +232,7 @@ int oat_deconvolve(oat_plan *plan, const void *u, oat_dtype u_dtype, void *p, oa
  * the cost, where a transducer's moments exceed the LDS: (half diagonal of the
  * grid + that of the faces) x highest frequency / c0 above 170 (a half diagonal
  * of 51 mm at 5 MHz and 1.5 mm/us), 137 for a narrow band.  Phases and sums are
- * FP64 on all paths; errors against FP64 are 2.5 to 5e-8 (H_sph) and 5e-8
+ * FP64 on all paths; errors against FP64 are 2.5 to 7e-8 (H_sph) and 5e-8
  * (H_sph^T) of the output's 2-norm with the polynomials, up to 1e-7 and 1e-6
  * with the plain sums.
  * 1 <= n_f <= 4096, f_min >= 0, df > 0,

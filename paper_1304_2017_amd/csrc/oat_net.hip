@@ -159,8 +159,9 @@ __device__ __forceinline__ int wave_index()
 // 32 x 8 x C1Z voxels, one or two planes a wave; B: column = voxel, k = tap (27 of 32), gathered from the
 // halo tile in LDS; A: the weights' three terms.  Workgroup (0, 0, 0) also
 // writes the 16 -> 16 fragments of the layer that follows.
-// 172 us at 256^3 (3.1 TB/s of output; 298 us on the VALU); bound by VALU issue
-// (four fifths), the gather of the taps and the stores' share of it.
+// 158 us at 256^3 (3.4 TB/s of output, 4.7 with its reads; 298 us on the VALU):
+// HBM at 90% of a copy's rate, VALU issue three quarters busy with the gather of
+// the taps and the stores.
 // ---------------------------------------------------------------------------
 constexpr int C1X = 32, C1Y = 8, C1_THREADS = 256;
 constexpr int C1P = C1X + 4, C1HY = C1Y + 2;   // LDS row pitch, halo rows

@@ -586,7 +586,7 @@ __device__ __forceinline__ bool sph_direct(int total, int ns, int most)
 // terms of which one is large (all of them in one run: 1e-5).  A value that
 // is not finite makes the moments NaN.
 // Bound by the LDS atomics, NM a term at about 12 cycles per wave (two
-// thirds of it bank conflicts of random intervals).
+// thirds of it bank conflicts of random intervals): 1466 us at 64^3 / 2048.
 template <int NM>
 __global__ void __launch_bounds__(SPH_MTHREADS)
 sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int *__restrict__ hdr,
@@ -663,9 +663,10 @@ sph_moment_kernel(Problem P, SphBand B, const int4 *__restrict__ list, const int
 // wave order.  Where sph_direct holds (images with few voxels set), the shares are
 // of the terms, each with its own exponential (phantoms of 34 x 15 x 55 / 931 / 77
 // and 35 x 22 x 45 / 243 / 263: the calls 101 -> 30 and 60 -> 50 us).  SUB > 1 (at
-// most 64 / SUB frequencies): a wave's lanes are SUB such shares, so that none is idle (a 5% phantom of 12^3 / 2048, 16 frequencies:
-// the call 47 -> 31 us).  Bound by FP64 VALU issue: 10 operations per (interval,
-// frequency).
+// most 64 / SUB frequencies): a wave's lanes are SUB such shares, so that none is
+// idle (a 5% phantom of 12^3 / 2048, 16 frequencies: the call 47 -> 31 us).  Bound
+// by FP64 VALU issue: 10 operations per (interval, frequency); 259 us at 64^3 /
+// 2048 / 256.
 template <int NM, int LF, int SUB>
 __global__ void __launch_bounds__(LF == 1 ? 1024 : 256)
 sph_synth_kernel(Problem P, SphBand B, const double *__restrict__ M, const int *__restrict__ hdr,
@@ -1271,8 +1272,8 @@ hipError_t launch_sph_project(const Problem &P, const void *img, int img_dt, flo
 // Work split of the table adjoint: tiles of 16 x 16 x 8 voxels, taken
 // 1024 at a time; fewer tiles than that take the transducers in `slices`
 // slices of at least 8 (4 where that makes no more than 16: 12^3 / 64 / 16
-// frequencies, the evaluation 12.7 -> 7.9 us).  The tables of a batch of `per` transducers of every
-// slice, and the partial sums, stay within the fixed scratch.
+// frequencies, the evaluation 12.7 -> 7.9 us).  The tables of a batch of `per`
+// transducers of every slice, and the partial sums, stay within the fixed scratch.
 struct SphAdjPlan {
     long long tiles;
     int chunk, slices, qps, per;
